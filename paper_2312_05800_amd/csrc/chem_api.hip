@@ -205,6 +205,52 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
     return CHEM_EUNSUPPORTED;
   }
 
+  std::vector<SpPack> tp(K);
+  for (int k = 0; k < K; ++k) {
+    for (int r = 0; r < 2; ++r) {
+      double *c = tp[k].c[r];
+      memcpy(c, (r == 0 ? lo : hi).data() + 7 * k, 5 * 8);
+      memcpy(c + 5, (r == 0 ? nh : nhh).data() + 7 * k, 6 * 8);
+      memcpy(c + 11, (r == 0 ? ns : nsh).data() + 7 * k, 6 * 8);
+    }
+    tp[k].Tmid = Tmid[k];
+    tp[k].invW = invW[k];
+  }
+  RxnPack null{{K, K, K, K}, {0, 0, 0, 0}, {0, 0, 0, 0}, -1e9, 0.0, 0.0, 0.0};
+  std::vector<RxnPack> rx((R + RATES_PER_WAVE - 1) / RATES_PER_WAVE * RATES_PER_WAVE, null);
+  for (int r = 0; r < R; ++r) {
+    const int s4[4] = {sp4[r].x, sp4[r].y, sp4[r].z, sp4[r].w};
+    const int n4[4] = {nu4[r].x, nu4[r].y, nu4[r].z, nu4[r].w};
+    for (int t = 0; t < 4; ++t) {
+      rx[r].sp[t] = s4[t];
+      rx[r].nu[t] = n4[t];
+      rx[r].cf[t] = (t < 2 ? -1.0 : 1.0) * n4[t];
+    }
+    rx[r].lnA = lnA[r];
+    rx[r].b = bb[r];
+    rx[r].EaR = EaR[r];
+    rx[r].dn = dn[r];
+  }
+  // per chunk of reactions and species: the reactions it takes part in (see
+  // DevMech::rs_start); the species of a reaction are distinct
+  std::vector<int> rs_start, rs_row;
+  std::vector<double> rs_coef;
+  for (int c0 = 0; c0 < R; c0 += RATES_CHUNK)
+    for (int k = 0; k < K; ++k) {
+      rs_start.push_back((int)rs_row.size());
+      for (int r = c0; r < R && r < c0 + RATES_CHUNK; ++r)
+        for (int t = 0; t < 4; ++t)
+          if (d->rsp[4 * r + t] == k) {
+            rs_row.push_back(r - c0);
+            rs_coef.push_back((t < 2 ? -1.0 : 1.0) * d->rnu[4 * r + t]);
+          }
+      while (rs_row.size() % 4) {
+        rs_row.push_back(RATES_CHUNK);
+        rs_coef.push_back(0.0);
+      }
+    }
+  rs_start.push_back((int)rs_row.size());
+
   Packer pk;
   size_t oW = pk.add(W.data(), K * 8), oiW = pk.add(invW.data(), K * 8),
          oTm = pk.add(Tmid.data(), K * 8), olo = pk.add(lo.data(), 7 * K * 8),
@@ -216,6 +262,13 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
          ons = pk.add(ns.data(), ns.size() * 8), onsh = pk.add(nsh.data(), nsh.size() * 8),
          ocpT = pk.add(cpT.data(), cpT.size() * 8), ohT = pk.add(hT.data(), hT.size() * 8),
          osT = pk.add(sT.data(), sT.size() * 8), ocd = pk.add(compd.data(), compd.size() * 8);
+
+  const size_t described = pk.buf.size();  // the sections whose digest names the mechanism
+  const size_t otp = pk.add(tp.data(), tp.size() * sizeof(SpPack));
+  const size_t orx = pk.add(rx.data(), rx.size() * sizeof(RxnPack));
+  const size_t orst = pk.add(rs_start.data(), rs_start.size() * sizeof(int)),
+               orsr = pk.add(rs_row.data(), rs_row.size() * sizeof(int)),
+               orsc = pk.add(rs_coef.data(), rs_coef.size() * 8);
 
   chem_mech *m = new chem_mech();
   m->K = K;
@@ -235,7 +288,7 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
     set_error("chem_mech_create: device allocation: %s", hipGetErrorString(e));
     return CHEM_ENOMEM;
   }
-  m->digest = fnv1a(pk.buf.data(), pk.buf.size());
+  m->digest = fnv1a(pk.buf.data(), described);
   e = hipMemcpy(m->blob, pk.buf.data(), pk.buf.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemset(m->counters, 0, 64 * sizeof(unsigned long long));
   if (e != hipSuccess) {
@@ -270,6 +323,11 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
   dm.hT = (const double *)(base + ohT);
   dm.sT = (const double *)(base + osT);
   dm.compd = (const double *)(base + ocd);
+  dm.tp = (const SpPack *)(base + otp);
+  dm.rx = (const RxnPack *)(base + orx);
+  dm.rs_start = (const int *)(base + orst);
+  dm.rs_row = (const int *)(base + orsr);
+  dm.rs_coef = (const double *)(base + orsc);
   *out = m;
   return CHEM_OK;
 }

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <string>
@@ -13,6 +14,8 @@ namespace chem {
 constexpr int KMAX = 63;  // species limit: n = K + 1 <= 64 lanes per cell
 
 // Device-resident mechanism constants (one allocation, see chem_api.hip).
+struct RxnPack;
+struct SpPack;
 struct DevMech {
   int K, R, E, n;
   const double *W;        // [K] kg/mol
@@ -38,7 +41,64 @@ struct DevMech {
   const double *cpT;      // [2][7][K] the c_p/R, h/RT and s/R polynomials above,
   const double *hT;       //   low range then high range, coefficient-major
   const double *sT;
+  // k_rates_cells: the species (tp [K]), the reactions (rx, R rounded up to a
+  // multiple of RATES_PER_WAVE by null reactions), and per chunk of RATES_CHUNK reactions and species, the
+  // reactions that the species takes part in: entries rs_start[chunk K + k] ..
+  // rs_start[chunk K + k + 1], a multiple of four of them (padded with the zero row),
+  // each a reaction's row in the chunk and the species' net coefficient
+  const SpPack *tp;
+  const RxnPack *rx;
+  const int *rs_start;
+  const int *rs_row;
+  const double *rs_coef;
 };
+constexpr int RATES_CHUNK = 32, RATES_PER_WAVE = 4;
+
+// What k_rates_cells reads of a reaction, contiguous for the scalar cache.
+struct RxnPack {
+  int sp[4], nu[4];  // as DevMech::sp and DevMech::nu (a null reaction: all slots empty)
+  double cf[4];      // net coefficients: minus the reactants', plus the products'
+  double lnA, b, EaR, dn;
+};
+// The same of a species: the c_p/R (5), h/RT (6) and s/R (6) polynomials of
+// the low and the high range.
+struct SpPack {
+  double c[2][17];
+  double Tmid, invW;
+};
+
+// A constant kept in scalar registers: the FMA takes it as an operand
+// instead of a copy of it in vector registers that each use overwrites.
+__device__ __forceinline__ double scalar_const(double c) {
+  asm("" : "+s"(c));
+  return c;
+}
+
+// e^x: x = n ln 2 + r with |r| <= ln 2 / 2, 1 + r + r^2 P(r) with P the Chebyshev
+// interpolant of degree 9 of (e^r - 1 - r) / r^2 (relative error 1.6e-17 before
+// rounding), scaled by 2^n.  Above 1024 infinity, below -1075 zero, NaN stays
+// NaN.  24 vector instructions where the library's exp, whose
+// coefficients are copied into vector registers at every use, takes about 40.
+__device__ __forceinline__ double exp_f64(double x) {
+  const double n = __builtin_rint(x * scalar_const(1.4426950408889634));
+  double r = __builtin_fma(n, scalar_const(-0.69314718055994529), x);
+  r = __builtin_fma(n, scalar_const(-2.3190468138462996e-17), r);
+  double p = __builtin_fma(r, scalar_const(2.5100375832561234e-08),
+                           scalar_const(2.7620075879983367e-07));
+  p = __builtin_fma(r, p, scalar_const(2.7557268480310024e-06));
+  p = __builtin_fma(r, p, scalar_const(2.4801521322368692e-05));
+  p = __builtin_fma(r, p, scalar_const(0.00019841269863040545));
+  p = __builtin_fma(r, p, scalar_const(0.0013888888917196719));
+  p = __builtin_fma(r, p, scalar_const(0.008333333333330065));
+  p = __builtin_fma(r, p, scalar_const(0.041666666666624164));
+  p = __builtin_fma(r, p, scalar_const(0.16666666666666669));
+  p = __builtin_fma(r, p, scalar_const(0.50000000000000011));
+  p = __builtin_fma(r, p, 1.0);
+  p = __builtin_fma(r, p, 1.0);
+  p = __builtin_amdgcn_ldexp(p, (int)n);
+  p = x > scalar_const(1024.0) ? INFINITY : p;
+  return x < scalar_const(-1075.0) ? 0.0 : p;
+}
 
 struct StepOpts {
   double rtol, atol_Y, atol_T, h0, h_min;
@@ -164,6 +224,10 @@ StepOpts resolve_opts(const chem_step_opts *o);
 chem_status launch_rates(const chem_mech *m, int64_t n, int64_t ld, const double *T,
                          const double *p, const double *Y, double *wdot, double *dTdt,
                          double *kfkr, hipStream_t s);
+// the same, one cell per lane (rates.hip)
+chem_status launch_rates_cells(const chem_mech *m, int64_t n, int64_t ld, const double *T,
+                               const double *p, const double *Y, double *wdot, double *dTdt,
+                               double *kfkr, hipStream_t s);
 // smallest lane group (16, 32 or 64) that holds n = K + 1 components
 int group_size(int n);
 // LDS bytes of one integrator wavefront with G lanes per cell
