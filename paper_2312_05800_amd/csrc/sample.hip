@@ -44,15 +44,22 @@ __global__ void k_ranges_part(int64_t n, int64_t ld, const double *T, const doub
   if (threadIdx.x < 6) part[blockIdx.x * 6 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ void k_ranges_fin(const double *part, int nparts, double *out) {
-  if (threadIdx.x >= 6) return;
-  const int q = threadIdx.x;
-  double v = part[q];
-  for (int b = 1; b < nparts; ++b) {
+// One wave per quantity: 64 lanes take the partials in turn, then meet in
+// shuffles (a single lane's loop over 512 partials took longer than the
+// samples of a small batch).
+__global__ __launch_bounds__(6 * 64) void k_ranges_fin(const double *part, int nparts,
+                                                       double *out) {
+  const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double v = (q & 1) ? -INFINITY : INFINITY;
+  for (int b = lane; b < nparts; b += 64) {
     const double x = part[b * 6 + q];
     v = (q & 1) ? fmax(v, x) : fmin(v, x);
   }
-  out[q] = v;
+  for (int off = 32; off > 0; off >>= 1) {
+    const double x = __shfl_xor(v, off);
+    v = (q & 1) ? fmax(v, x) : fmin(v, x);
+  }
+  if (lane == 0) out[q] = v;
 }
 
 struct SampleArgs {
@@ -67,6 +74,51 @@ struct SampleArgs {
   chem_sample_opts o;
 };
 
+// ln x of a finite positive x: x = 2^e m with m in [1/sqrt 2, sqrt 2),
+// ln m = 2 atanh(s) = 2 s + s z P(z) with s = (m - 1) / (m + 1), z = s^2 and P the
+// Chebyshev interpolant of degree 6 (relative error 4.2e-18 before rounding).
+__device__ __forceinline__ double ln_f64(double x) {
+  double m = __builtin_amdgcn_frexp_mant(x);
+  int e = __builtin_amdgcn_frexp_exp(x);
+  const bool up = m < 0.70710678118654752;
+  m = up ? 2.0 * m : m;
+  e = up ? e - 1 : e;
+  // the quotient by Newton's reciprocal (the divisor is in [1.7, 2.5])
+  const double num = m - 1.0, den = m + 1.0;
+  double r = __builtin_amdgcn_rcp(den);
+  r = fma(fma(-den, r, 1.0), r, r);
+  r = fma(fma(-den, r, 1.0), r, r);
+  double s = num * r;
+  s = fma(fma(-den, s, num), r, s);
+  const double z = s * s;
+  double P = fma(z, scalar_const(0.14617807153417325), scalar_const(0.15331611722055008));
+  P = fma(z, P, scalar_const(0.18182892432536871));
+  P = fma(z, P, scalar_const(0.22222211089379496));
+  P = fma(z, P, scalar_const(0.28571428626253836));
+  P = fma(z, P, scalar_const(0.39999999999898889));
+  P = fma(z, P, scalar_const(0.66666666666666696));
+  const double k = (double)e;
+  const double lo = fma(s * z, P, k * scalar_const(2.3190468138462996e-17));
+  return fma(k, scalar_const(0.69314718055994529), fma(2.0, s, lo));
+}
+
+// 1 + gamma c of Eq. (Yrand), the product rounded: where |ln y| is large, the
+// last bit of the exponent is most of the power's error.
+__device__ __forceinline__ double exponent(double gamma, double c) {
+#pragma clang fp contract(off)
+  return 1.0 + gamma * c;
+}
+
+// y^x = y e^(d ln y) with d = x - 1.  The exponents of Eq. (Yrand) stay near 1,
+// so the rounding of d ln y (|d ln y| eps) is all that the general pow's extended
+// logarithm would save.  Sets `far` where that is not small or y not finite.
+__device__ __forceinline__ double pow_near(double y, double x, bool &far) {
+  const double t = (x - 1.0) * ln_f64(y);
+  far = far || !(fabs(t) < 4.0) || !(y < 1e300);
+  return y * exp_f64(t);
+}
+
+// One sample through memory, with the general power.
 __device__ void sample_one(const DevMech &M, const SampleArgs &a, int64_t i) {
   const int K = M.K, n2 = a.o.n2;
   const int64_t ld = a.ld;
@@ -88,7 +140,7 @@ __device__ void sample_one(const DevMech &M, const SampleArgs &a, int64_t i) {
     for (int k = 0; k < K; ++k) {
       if (k == n2) continue;
       const double y = a.Y[(int64_t)k * ld + i];
-      const double yp = y > 0.0 ? pow(y, 1.0 + a.o.gamma * a.c[(int64_t)(3 + k) * ld + i]) : 0.0;
+      const double yp = y > 0.0 ? pow(y, exponent(a.o.gamma, a.c[(int64_t)(3 + k) * ld + i])) : 0.0;
       a.Yo[(int64_t)k * ld + i] = yp;
       sum += yp;
     }
@@ -125,10 +177,96 @@ __device__ void sample_one(const DevMech &M, const SampleArgs &a, int64_t i) {
   a.keep[i] = ok ? 1 : 0;
 }
 
-__global__ void k_sample(DevMech M, SampleArgs a) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n;
-       i += (int64_t)gridDim.x * blockDim.x)
+// KP >= K: species slots per sample.  One pass over the species: the chunk's
+// loads (Y and c of eight species) go out together and the raw values stay in
+// registers until the sum that scales them is known, so that Y and c are read
+// once and Y_out is written once.  Samples outside pow_near's range go through
+// sample_one.
+template <int KP>
+__global__ __launch_bounds__(256) void k_sample(DevMech M, SampleArgs a) {
+  constexpr int CHK = 8;
+  const int K = M.K, n2 = a.o.n2;
+  const int64_t ld = a.ld;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.n) return;
+  const double s = a.s ? a.s[i] : -1.0;
+  const bool line = s >= 0.0;  // a state on the line between the two ends
+  const double cT = a.c[i], cp = a.c[ld + i], cn = a.c[2 * ld + i];
+  const double T0 = a.T[i], p0 = a.p[i];
+  double v[KP];
+  bool far = false;
+  double sum = 0.0, yn2 = 0.0;
+#pragma unroll
+  for (int k0 = 0; k0 < KP; k0 += CHK) {
+    if (k0 >= K) break;
+    double y[CHK], c[CHK];
+#pragma unroll
+    for (int t = 0; t < CHK; ++t) {
+      const int k = min(k0 + t, K - 1);
+      y[t] = a.Y[(int64_t)k * ld + i];
+      c[t] = a.c[(int64_t)(3 + k) * ld + i];
+    }
+#pragma unroll
+    for (int t = 0; t < CHK; ++t) {
+      const int k = k0 + t;
+      v[k] = 0.0;
+      if (k < K) {
+        if (k == n2) {
+          yn2 = y[t];
+        } else {
+          // Eq. (Yrand)
+          v[k] = y[t] > 0.0 ? pow_near(y[t], exponent(a.o.gamma, c[t]), far) : 0.0;
+          sum += v[k];
+        }
+      }
+    }
+  }
+  if (far) {  // nothing is written yet: the outputs may be the inputs' arrays
     sample_one(M, a, i);
+    return;
+  }
+  const double *r = a.ranges;
+  // Eqs. (Trand), (Prand), (N2rand)
+  double T = T0 + a.o.alpha * cT * (r[1] - r[0]);
+  double p = p0 + a.o.beta * cp * (r[3] - r[2]);
+  yn2 += a.o.alpha * cn * (r[5] - r[4]);
+  // every species but N2 rescaled so that the mass fractions sum to one
+  const double scale = (1.0 - yn2) / sum;
+  if (a.s) {
+    T = line ? (1.0 - s) * a.end_eq[0] + s * a.end_air[0] : T;
+    p = line ? (1.0 - s) * a.end_eq[1] + s * a.end_air[1] : p;
+  }
+  a.To[i] = T;
+  a.po[i] = p;
+  // element moles per kg, the ratios of Table 1 and the equivalence ratio
+  // (2 n_C + n_H / 2) / n_O
+  double nC = 0.0, nH = 0.0, nO = 0.0, nN = 0.0, yn2o = 0.0;
+  bool ok = isfinite(T) && T >= a.o.T_min;
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    if (k < K) {
+      double y = k == n2 ? yn2 : v[k] * scale;
+      if (a.s) {
+        const double yl = (1.0 - s) * a.end_eq[2 + k] + s * a.end_air[2 + k];
+        y = line ? yl : y;
+      }
+      a.Yo[(int64_t)k * ld + i] = y;
+      if (k == n2) yn2o = y;
+      ok = ok && isfinite(y) && y >= 0.0;
+      // moles per kg (a non-finite y has cleared `ok`, whatever 0 y gives)
+      const double x = y * M.invW[k];
+      nC = fma(M.compd[a.o.el_C * K + k], x, nC);
+      nH = fma(M.compd[a.o.el_H * K + k], x, nH);
+      nO = fma(M.compd[a.o.el_O * K + k], x, nO);
+      nN = fma(M.compd[a.o.el_N * K + k], x, nN);
+    }
+  }
+  ok = ok && yn2o >= 0.0 && yn2o < 1.0;
+  const double hc = nH / nC, on = nO / nN, phi = (2.0 * nC + 0.5 * nH) / nO;
+  ok = ok && isfinite(hc) && hc >= a.o.hc_min && hc <= a.o.hc_max;
+  ok = ok && isfinite(on) && on >= a.o.on_min && on <= a.o.on_max;
+  ok = ok && isfinite(phi) && phi >= a.o.phi_min && phi <= a.o.phi_max;
+  a.keep[i] = ok ? 1 : 0;
 }
 
 }  // namespace
@@ -189,14 +327,20 @@ extern "C" chem_status chem_sample_states(const chem_mech *m, chem_batch seeds, 
   hipStream_t st = (hipStream_t)stream;
   double *part = m->sample_buf, *ranges = m->sample_buf + RANGE_BLOCKS * 6;
   ProfScope prof("sample_states", st);
-  hipLaunchKernelGGL(k_ranges_part, dim3(RANGE_BLOCKS), dim3(RANGE_THREADS), 0, st, n, seeds.ld,
-                     T, p, Y, o.n2, part);
-  hipLaunchKernelGGL(k_ranges_fin, dim3(1), dim3(64), 0, st, part, RANGE_BLOCKS, ranges);
+  const int64_t rows = (n + RANGE_THREADS - 1) / RANGE_THREADS;
+  const int parts = (int)(rows < RANGE_BLOCKS ? rows : RANGE_BLOCKS);
+  hipLaunchKernelGGL(k_ranges_part, dim3(parts), dim3(RANGE_THREADS), 0, st, n, seeds.ld, T, p, Y,
+                     o.n2, part);
+  hipLaunchKernelGGL(k_ranges_fin, dim3(1), dim3(6 * 64), 0, st, part, parts, ranges);
   SampleArgs a{n, seeds.ld, T, p, Y, c, s, end_eq, end_air, ranges, T_out, p_out, Y_out,
                keep, o};
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > (1 << 20)) blocks = 1 << 20;  // larger batches loop over the grid
-  hipLaunchKernelGGL(k_sample, dim3((unsigned)blocks), dim3(256), 0, st, m->d, a);
+  const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+  if (m->K <= 16)
+    hipLaunchKernelGGL(k_sample<16>, grid, block, 0, st, m->d, a);
+  else if (m->K <= 32)
+    hipLaunchKernelGGL(k_sample<32>, grid, block, 0, st, m->d, a);
+  else
+    hipLaunchKernelGGL(k_sample<64>, grid, block, 0, st, m->d, a);
   CHEM_HIP(hipGetLastError());
   return CHEM_OK;
 }
