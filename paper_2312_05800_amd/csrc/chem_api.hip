@@ -6,11 +6,11 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <fstream>
 #include <mutex>
 #include <sstream>
 #include <utility>
-#include <vector>
 #include <vector>
 
 #include "chem_internal.h"
@@ -75,6 +75,83 @@ struct Packer {
     return off;
   }
 };
+
+// The integrator's order of the species: by enthalpy per mass at 298.15 K, the
+// most stable first.  The elimination takes its pivots on the diagonal as long as
+// that holds the largest entry of the column, and repeats with a search where it
+// does not: with this order on none of the attempts sampled on the 30-species
+// mechanism at dt = 1e-5 and 1e-4 s or on the 44-species one at 1e-5 s; as the
+// species are listed it is 5, 30 and 38 %, by descending reaction count 9, 36 and 39 %.
+std::vector<int> species_order(const chem_mech_desc *d) {
+  std::vector<double> h(d->K);
+  std::vector<int> order(d->K);
+  const double T = 298.15;
+  for (int k = 0; k < d->K; ++k) {
+    const double *a = d->nasa + 17 * k + (T <= d->nasa[17 * k + 1] ? 3 : 10);
+    h[k] = (T * (a[0] + T * (a[1] / 2 + T * (a[2] / 3 + T * (a[3] / 4 + T * a[4] / 5)))) + a[5]) /
+           d->W[k];
+    order[k] = k;
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return h[a] < h[b]; });
+  return order;
+}
+
+// The integrator's order of the reactions.  A lane group takes G reactions per
+// pass, one per lane, and each lane adds to its slots' species in LDS, one slot
+// after the other; lanes that add to the same word are served one by one.  So
+// reactions go, those with the most common species first, to the pass and the order of
+// their two reactants and two products where they meet the fewest lanes with the
+// same species in the same slot (30-species mechanism: the largest counts of the
+// 20 slots sum to 55 instead of 97).
+std::vector<std::pair<int, std::array<int, 4>>> pass_order(const chem_mech_desc *d, int G) {
+  const int K = d->K, R = d->R, P = (R + G - 1) / G;
+  std::vector<int> uses(K, 0), rank(R);
+  auto species = [&](int r, int t) { return d->rsp[4 * r + t]; };
+  for (int r = 0; r < R; ++r)
+    for (int t = 0; t < 4; ++t)
+      if (species(r, t) >= 0) uses[species(r, t)]++;
+  std::vector<int> common(R, 0);
+  for (int r = 0; r < R; ++r) {
+    rank[r] = r;
+    for (int t = 0; t < 4; ++t)
+      if (species(r, t) >= 0) common[r] = std::max(common[r], uses[species(r, t)]);
+  }
+  std::stable_sort(rank.begin(), rank.end(), [&](int a, int b) { return common[a] > common[b]; });
+  std::vector<int> count((size_t)P * 4 * K, 0);
+  std::vector<std::vector<std::pair<int, std::array<int, 4>>>> pass(P);
+  for (int r : rank) {
+    // an empty slot stays the second of its side
+    std::vector<std::array<int, 4>> orders;
+    for (int f = 0; f < 2; ++f)
+      for (int g = 0; g < 2; ++g) {
+        const std::array<int, 4> o = {f, 1 - f, 2 + g, 3 - g};
+        if (species(r, o[0]) >= 0 && species(r, o[2]) >= 0) orders.push_back(o);
+      }
+    double best = -1.0;
+    int bp = 0;
+    std::array<int, 4> bo = orders[0];
+    for (int p = 0; p < P; ++p) {
+      if ((int)pass[p].size() >= std::min(G, R - p * G)) continue;
+      for (const auto &o : orders) {
+        double c = 0.0;
+        for (int t = 0; t < 4; ++t)
+          if (species(r, o[t]) >= 0)
+            c += pow(4.0, std::min(count[((size_t)p * 4 + t) * K + species(r, o[t])], 200));
+        if (best < 0.0 || c < best) {
+          best = c;
+          bp = p;
+          bo = o;
+        }
+      }
+    }
+    pass[bp].push_back({r, bo});
+    for (int t = 0; t < 4; ++t)
+      if (species(r, bo[t]) >= 0) count[((size_t)bp * 4 + t) * K + species(r, bo[t])]++;
+  }
+  std::vector<std::pair<int, std::array<int, 4>>> out;
+  for (auto &q : pass) out.insert(out.end(), q.begin(), q.end());
+  return out;
+}
 
 }  // namespace
 
@@ -162,7 +239,7 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
     int dnn = 0;
     int s4[4], n4[4];
     for (int s = 0; s < 4; ++s) {
-      s4[s] = sp[s] < 0 ? K : sp[s];  // empty slot: the dummy species K (see DevMech::sp)
+      s4[s] = sp[s] < 0 ? K : sp[s];  // empty slot: the dummy species K (see RxnPack::sp)
       n4[s] = sp[s] < 0 ? 0 : nu[s];
       dnn += (s < 2 ? -1 : 1) * n4[s];
     }
@@ -205,6 +282,27 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
     return CHEM_EUNSUPPORTED;
   }
 
+  std::vector<int4> xsp(R + 1, make_int4(0, 0, 0, 0));
+  std::vector<double2> xab(R + 1, make_double2(0.0, 0.0)), xeb(R + 1, make_double2(0.0, 0.0));
+  const std::vector<int> species = species_order(d);
+  std::vector<int> component(K);
+  for (int c = 0; c < K; ++c) component[species[c]] = c + 1;
+  const auto order = pass_order(d, group_size(K + 1));
+  for (int i = 0; i < R; ++i) {
+    const int r = order[i].first;
+    int c[4];
+    uint64_t bits = (uint64_t)r << 16;
+    for (int t = 0; t < 4; ++t) {
+      const int o = 4 * r + order[i].second[t];
+      c[t] = d->rsp[o] < 0 ? 0 : component[d->rsp[o]];
+      if (c[t]) bits |= (uint64_t)d->rnu[o] << (2 * t);
+    }
+    xsp[i] = make_int4(c[0], c[1], c[2], c[3]);
+    xab[i] = make_double2(lnA[r], bb[r]);
+    double bd;
+    memcpy(&bd, &bits, 8);
+    xeb[i] = make_double2(EaR[r], bd);
+  }
   std::vector<SpPack> tp(K);
   for (int k = 0; k < K; ++k) {
     for (int r = 0; r < 2; ++r) {
@@ -251,19 +349,42 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
     }
   rs_start.push_back((int)rs_row.size());
 
+  // what the digest that keys the tuning cache covers: the mechanism as described
+  Packer named;
+  named.add(W.data(), K * 8);
+  named.add(invW.data(), K * 8);
+  named.add(Tmid.data(), K * 8);
+  named.add(lo.data(), 7 * K * 8);
+  named.add(hi.data(), 7 * K * 8);
+  named.add(lnA.data(), R * 8);
+  named.add(bb.data(), R * 8);
+  named.add(EaR.data(), R * 8);
+  named.add(dn.data(), R * 8);
+  named.add(sp4.data(), R * sizeof(int4));
+  named.add(nu4.data(), R * sizeof(int4));
+  named.add(Mel.data(), Mel.size() * 8);
+  named.add(nh.data(), nh.size() * 8);
+  named.add(nhh.data(), nhh.size() * 8);
+  named.add(ns.data(), ns.size() * 8);
+  named.add(nsh.data(), nsh.size() * 8);
+  named.add(cpT.data(), cpT.size() * 8);
+  named.add(hT.data(), hT.size() * 8);
+  named.add(sT.data(), sT.size() * 8);
+  named.add(compd.data(), compd.size() * 8);
+
   Packer pk;
   size_t oW = pk.add(W.data(), K * 8), oiW = pk.add(invW.data(), K * 8),
          oTm = pk.add(Tmid.data(), K * 8), olo = pk.add(lo.data(), 7 * K * 8),
-         ohi = pk.add(hi.data(), 7 * K * 8), olnA = pk.add(lnA.data(), R * 8),
-         ob = pk.add(bb.data(), R * 8), oEa = pk.add(EaR.data(), R * 8),
-         odn = pk.add(dn.data(), R * 8), osp = pk.add(sp4.data(), R * sizeof(int4)),
-         onu = pk.add(nu4.data(), R * sizeof(int4)), oM = pk.add(Mel.data(), Mel.size() * 8),
+         ohi = pk.add(hi.data(), 7 * K * 8), oM = pk.add(Mel.data(), Mel.size() * 8),
          onh = pk.add(nh.data(), nh.size() * 8), onhh = pk.add(nhh.data(), nhh.size() * 8),
          ons = pk.add(ns.data(), ns.size() * 8), onsh = pk.add(nsh.data(), nsh.size() * 8),
          ocpT = pk.add(cpT.data(), cpT.size() * 8), ohT = pk.add(hT.data(), hT.size() * 8),
          osT = pk.add(sT.data(), sT.size() * 8), ocd = pk.add(compd.data(), compd.size() * 8);
 
-  const size_t described = pk.buf.size();  // the sections whose digest names the mechanism
+  const size_t oord = pk.add(species.data(), species.size() * sizeof(int));
+  const size_t oxsp = pk.add(xsp.data(), xsp.size() * sizeof(int4)),
+               oxab = pk.add(xab.data(), xab.size() * sizeof(double2)),
+               oxeb = pk.add(xeb.data(), xeb.size() * sizeof(double2));
   const size_t otp = pk.add(tp.data(), tp.size() * sizeof(SpPack));
   const size_t orx = pk.add(rx.data(), rx.size() * sizeof(RxnPack));
   const size_t orst = pk.add(rs_start.data(), rs_start.size() * sizeof(int)),
@@ -288,7 +409,7 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
     set_error("chem_mech_create: device allocation: %s", hipGetErrorString(e));
     return CHEM_ENOMEM;
   }
-  m->digest = fnv1a(pk.buf.data(), described);
+  m->digest = fnv1a(named.buf.data(), named.buf.size());
   e = hipMemcpy(m->blob, pk.buf.data(), pk.buf.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemset(m->counters, 0, 64 * sizeof(unsigned long long));
   if (e != hipSuccess) {
@@ -308,12 +429,6 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
   dm.Tmid = (const double *)(base + oTm);
   dm.nasa_lo = (const double *)(base + olo);
   dm.nasa_hi = (const double *)(base + ohi);
-  dm.lnA = (const double *)(base + olnA);
-  dm.b = (const double *)(base + ob);
-  dm.EaR = (const double *)(base + oEa);
-  dm.dn = (const double *)(base + odn);
-  dm.sp = (const int4 *)(base + osp);
-  dm.nu = (const int4 *)(base + onu);
   dm.Mel = (const double *)(base + oM);
   dm.nasa_h = (const double *)(base + onh);
   dm.nasa_hh = (const double *)(base + onhh);
@@ -323,6 +438,10 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
   dm.hT = (const double *)(base + ohT);
   dm.sT = (const double *)(base + osT);
   dm.compd = (const double *)(base + ocd);
+  dm.order = (const int *)(base + oord);
+  dm.xsp = (const int4 *)(base + oxsp);
+  dm.xab = (const double2 *)(base + oxab);
+  dm.xeb = (const double2 *)(base + oxeb);
   dm.tp = (const SpPack *)(base + otp);
   dm.rx = (const RxnPack *)(base + orx);
   dm.rs_start = (const int *)(base + orst);

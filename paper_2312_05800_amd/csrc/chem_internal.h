@@ -23,15 +23,6 @@ struct DevMech {
   const double *Tmid;     // [K]
   const double *nasa_lo;  // [K][7]
   const double *nasa_hi;  // [K][7]
-  const double *lnA;      // [R]
-  const double *b;        // [R]
-  const double *EaR;      // [R] Ea / R_gas, K
-  const double *dn;       // [R] sum of product minus reactant coefficients
-  const int4 *sp;         // [R] species of slots reactant0, reactant1, product0, product1;
-                          //   an empty slot names the dummy species K (the kernels keep
-                          //   C = 1 and h = g = 0 for it, so it drops out of every product
-                          //   and sum without a branch)
-  const int4 *nu;         // [R] their coefficients (0 for empty slots)
   const double *Mel;      // [E][K] element mass per unit mass fraction, A_e a_ek / W_k
   const double *nasa_h;   // [K][7] low-range h/RT polynomial: a1, a2/2, a3/3, a4/4, a5/5, a6, 0
   const double *nasa_hh;  // [K][7] same for the high range
@@ -41,6 +32,14 @@ struct DevMech {
   const double *cpT;      // [2][7][K] the c_p/R, h/RT and s/R polynomials above,
   const double *hT;       //   low range then high range, coefficient-major
   const double *sT;
+  // the integrator's lane groups: component c >= 1 is species order[c - 1] (see
+  // species_order); the reactions in the order of their passes (see pass_order),
+  // slots by component (0 = empty)
+  const int *order;    // [K]
+  const int4 *xsp;     // [R]
+  const double2 *xab;  // [R] ln A, b
+  const double2 *xeb;  // [R] E_a/R, bits: coefficients (2 bits per slot), from bit 16 the
+                       //   reaction's index
   // k_rates_cells: the species (tp [K]), the reactions (rx, R rounded up to a
   // multiple of RATES_PER_WAVE by null reactions), and per chunk of RATES_CHUNK reactions and species, the
   // reactions that the species takes part in: entries rs_start[chunk K + k] ..
@@ -56,7 +55,11 @@ constexpr int RATES_CHUNK = 32, RATES_PER_WAVE = 4;
 
 // What k_rates_cells reads of a reaction, contiguous for the scalar cache.
 struct RxnPack {
-  int sp[4], nu[4];  // as DevMech::sp and DevMech::nu (a null reaction: all slots empty)
+  // species of slots reactant0, reactant1, product0, product1 and their
+  // coefficients; an empty slot names the dummy species K with coefficient 0 (C = 1
+  // and h = g = 0 are kept for it, so it drops out of every product and sum without
+  // a branch), a null reaction has all slots empty
+  int sp[4], nu[4];
   double cf[4];      // net coefficients: minus the reactants', plus the products'
   double lnA, b, EaR, dn;
 };
@@ -98,6 +101,34 @@ __device__ __forceinline__ double exp_f64(double x) {
   p = __builtin_amdgcn_ldexp(p, (int)n);
   p = x > scalar_const(1024.0) ? INFINITY : p;
   return x < scalar_const(-1075.0) ? 0.0 : p;
+}
+
+// ln x of a finite positive x: x = 2^e m with m in [1/sqrt 2, sqrt 2),
+// ln m = 2 atanh(s) = 2 s + s z P(z) with s = (m - 1) / (m + 1), z = s^2 and P the
+// Chebyshev interpolant of degree 6 (relative error 4.2e-18 before rounding).
+__device__ __forceinline__ double ln_f64(double x) {
+  double m = __builtin_amdgcn_frexp_mant(x);
+  int e = __builtin_amdgcn_frexp_exp(x);
+  const bool up = m < 0.70710678118654752;
+  m = up ? 2.0 * m : m;
+  e = up ? e - 1 : e;
+  // the quotient by Newton's reciprocal (the divisor is in [1.7, 2.5])
+  const double num = m - 1.0, den = m + 1.0;
+  double r = __builtin_amdgcn_rcp(den);
+  r = fma(fma(-den, r, 1.0), r, r);
+  r = fma(fma(-den, r, 1.0), r, r);
+  double s = num * r;
+  s = fma(fma(-den, s, num), r, s);
+  const double z = s * s;
+  double P = fma(z, scalar_const(0.14617807153417325), scalar_const(0.15331611722055008));
+  P = fma(z, P, scalar_const(0.18182892432536871));
+  P = fma(z, P, scalar_const(0.22222211089379496));
+  P = fma(z, P, scalar_const(0.28571428626253836));
+  P = fma(z, P, scalar_const(0.39999999999898889));
+  P = fma(z, P, scalar_const(0.66666666666666696));
+  const double k = (double)e;
+  const double lo = fma(s * z, P, k * scalar_const(2.3190468138462996e-17));
+  return fma(k, scalar_const(0.69314718055994529), fma(2.0, s, lo));
 }
 
 struct StepOpts {

@@ -3,15 +3,13 @@
 //
 // Mapping.  A cell is handled by a group of G lanes (G = 16, 32 or 64, the
 // smallest power of two >= n = K + 1), so a 64-wide wavefront carries 64/G
-// cells.  Lane l of a group owns component l of the state y = [T, Y_1..Y_K]
-// (lane 0 is T) and, during the linear algebra, row l of the Newton matrix
-// M = I/(gamma h) - J, held in registers.  Reactions are spread over the
-// lanes of the group (lane l takes r = l, l+G, ...); species lanes gather
-// their net production rate from the per-reaction rates of progress in LDS
-// through a fixed per-species reaction list in ascending reaction order.
-// Every cross-lane exchange stays inside one wavefront (DS permutes for
-// broadcasts and butterflies, LDS for gathers), so no workgroup barrier is
-// needed and groups may diverge freely.
+// cells.  Lane l of a group owns component l of the state y = [T, Y..] (lane 0 is
+// T, lane c >= 1 the species DevMech::order[c - 1]).  Reactions are spread over the
+// lanes of the group (lane l takes l, l + G, ... of the passes' order); their rates of
+// progress and Jacobian terms are added to the group's LDS slice by LDS atomics.  The
+// Newton matrix M = I/(gamma h) - J is inverted in registers.  Every cross-lane
+// exchange stays inside one wavefront (DPP, permlane swaps, LDS), so no workgroup
+// barrier is needed and groups may diverge freely.
 //
 // Scheduling.  The step kernel is persistent: every group takes a cell from a
 // device-wide atomic counter, integrates it with per-cell adaptive substeps,
@@ -27,7 +25,7 @@ namespace chem {
 namespace {
 
 constexpr double RG = 8.314462618;  // J/(mol K)
-constexpr double PREF = 101325.0;   // Pa
+constexpr double LN_PREF_RG = 9.408091968961747;  // ln(101325 Pa / RG)
 
 // RODAS3 (Sandu et al. 1997), transformed form (Hairer & Wanner IV.7):
 // (I/(gamma h) - J) K_i = f(y + sum_j a_ij K_j) + (1/h) sum_j c_ij K_j.
@@ -195,76 +193,107 @@ __device__ __forceinline__ double grp_first(double v) {
   return out;
 }
 
-// Per-group LDS scratch (doubles): concentrations, (g/RT, h/RT) pairs of the
-// species (one 16-byte gather per reaction slot), the net production rates
-// being accumulated, and the Jacobian / Newton matrix (n rows of odd
-// stride).  In chem_rates the matrix region holds k_f, k_r instead; in the
-// solves the concentration slots hold the permuted right-hand side.
+// 1/x by Newton's iteration; `miss` is 1 - x/x as it came out, NaN or far from 0
+// where x is zero, not finite or beyond the range of the iteration.
+__device__ __forceinline__ double rcp_newton(double x, double &miss) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  r = fma(fma(-x, r, 1.0), r, r);
+  miss = fma(-x, r, 1.0);
+  return r;
+}
+
+// Per-group LDS scratch (doubles), indexed by component (0 = T, c >= 1 the species
+// DevMech::order[c - 1]; component 0 of the first two doubles as the dummy of empty reaction slots,
+// C = 1 and g = h = 0): (concentration, g/RT) pairs (one 16-byte gather per reaction
+// slot), h/RT, the net production rates being accumulated, and the Jacobian /
+// Newton matrix (n rows of odd stride).  In chem_rates the matrix region holds
+// k_f, k_r instead (and nothing reads iw); in the solves the h slots hold the permuted right-hand side.  iw: 1/W by component (0 for T and past n), shared by the
+// wave's groups.
 template <int G>
 struct GLds {
-  double *C;
-  double2 *gh;  // 16-byte aligned: the slice starts so, and C holds G doubles
-  double *wa, *J;
+  double2 *cg;  // 16-byte aligned: the slice starts so
+  double *h, *wa, *J, *iw;
   int js;  // row stride of J
-  __device__ GLds(double *base, int R, int n) {
-    C = base;
-    gh = (double2 *)(C + G);
-    wa = C + 3 * G;
+  __device__ GLds(double *base, int g, int R, int n) {
+    cg = (double2 *)(base + g * doubles(R, n));
+    h = (double *)(cg + G);
+    wa = h + G;
     J = wa + G;
     js = stride(n);
+    iw = base + (64 / G) * doubles(R, n);
   }
   // odd row stride (2 js banks apart: lanes reading one column hit distinct
   // banks) and only the n rows of the n x n matrix
   __host__ __device__ static int stride(int n) { return n | 1; }
-  // even, so that every group's slice starts 16-byte aligned
+  // even, so that every group's slice starts 16-byte aligned; R: reactions whose
+  // rate constants the slice takes (0 in the step)
   __host__ __device__ static size_t doubles(int R, int n) {
     const size_t j = (size_t)n * stride(n), k = 2 * (size_t)R;
     return (4 * G + (j > k ? j : k) + 1) & ~(size_t)1;
   }
+  __device__ void fill_iw(const DevMech &M) const {
+    const int t = threadIdx.x & 63;
+    if (t < G) iw[t] = (t >= 1 && t < M.n) ? M.invW[M.order[t - 1]] : 0.0;
+  }
 };
 
-// C^nu of a reaction slot (nu = 1 or 2; an empty slot names the dummy
-// species, whose C is 1)
-__device__ __forceinline__ double slot_fac(int s, int nu, const double *C) {
-  const double c = C[s];
-  return nu == 2 ? c * c : c;
+// A reaction as the lanes load it (three 16-byte loads): its slots' components
+// (reactant0, reactant1, product0, product1; the first of either side is never
+// empty), {ln A, b}, and {E_a/R, bits}.
+struct RxnIn {
+  int4 sp;
+  double2 ab, eb;
+};
+__device__ __forceinline__ RxnIn rxn_load(const DevMech &M, int i) {
+  return RxnIn{M.xsp[i], M.xab[i], M.xeb[i]};
 }
 
-// Rate constants and one-way rates of progress of reaction r from the
-// species data in LDS: ln k_f = ln A + b ln T - E_a/(R T),
-// ln K_c = -dG/RT + dn ln(p_ref/RT), k_r = exp(ln k_f - ln K_c).
+// Rate constants and one-way rates of progress of a reaction from the species
+// data in LDS: ln k_f = ln A + b ln T - E_a/(R T), ln K_c = -dG/RT + dn ln(p_ref/RT),
+// k_r = exp(ln k_f - ln K_c).
 struct Rxn {
-  int4 sp, nu;
-  double kf, kr, fwd, rev, dH, dn;
+  int4 sp;
+  double nu[4];        // coefficients, reactants' negative
+  double c[4];         // concentrations of the slots
+  double kf, kr, fwd, rev;
+  double b, EaR, dn;
+  unsigned bits;
 };
 
+// C^nu of a reaction slot (nu = 1 or 2; 1 for an empty slot, whose C is 1)
+__device__ __forceinline__ double slot_fac(double nu, double c) {
+  return fabs(nu) == 2.0 ? c * c : c;
+}
+
 template <int G>
-__device__ __forceinline__ Rxn rxn_eval(const DevMech &M, const GLds<G> &L, int r, double lnT,
+__device__ __forceinline__ Rxn rxn_eval(const GLds<G> &L, const RxnIn &in, double lnT,
                                         double invT, double lnPRT) {
   Rxn x;
-  x.sp = M.sp[r];
-  x.nu = M.nu[r];
-  // empty slots gather the dummy species (g = h = 0, coefficient 0): no branches,
-  // so the eight LDS reads of a reaction (four (g, h) pairs, four
-  // concentrations) issue together
-  double dG = 0.0, dH = 0.0;
-  const double2 a0 = L.gh[x.sp.x], a1 = L.gh[x.sp.y], a2 = L.gh[x.sp.z], a3 = L.gh[x.sp.w];
-  dG -= x.nu.x * a0.x;
-  dH -= x.nu.x * a0.y;
-  dG -= x.nu.y * a1.x;
-  dH -= x.nu.y * a1.y;
-  dG += x.nu.z * a2.x;
-  dH += x.nu.z * a2.y;
-  dG += x.nu.w * a3.x;
-  dH += x.nu.w * a3.y;
-  x.dH = dH;
-  x.dn = M.dn[r];
-  const double lnkf = M.lnA[r] + M.b[r] * lnT - M.EaR[r] * invT;
+  x.sp = in.sp;
+  x.bits = (unsigned)__double_as_longlong(in.eb.y);
+  x.b = in.ab.y;
+  x.EaR = in.eb.x;
+  // empty slots gather the dummy (g = h = 0, coefficient 0): no branches, so the
+  // LDS reads of a reaction issue together
+  const double2 a0 = L.cg[x.sp.x], a1 = L.cg[x.sp.y], a2 = L.cg[x.sp.z], a3 = L.cg[x.sp.w];
+  x.c[0] = a0.x;
+  x.c[1] = a1.x;
+  x.c[2] = a2.x;
+  x.c[3] = a3.x;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const double v = (double)(int)((x.bits >> (2 * t)) & 3u);
+    x.nu[t] = t < 2 ? -v : v;
+  }
+  x.dn = (x.nu[0] + x.nu[1]) + (x.nu[2] + x.nu[3]);
+  const double dG = x.nu[0] * a0.y + x.nu[1] * a1.y + x.nu[2] * a2.y + x.nu[3] * a3.y;
+  const double lnkf = in.ab.x + x.b * lnT - x.EaR * invT;
   const double lnKc = -dG + x.dn * lnPRT;
-  x.kf = exp(lnkf);
-  x.kr = exp(lnkf - lnKc);
-  x.fwd = x.kf * slot_fac(x.sp.x, x.nu.x, L.C) * slot_fac(x.sp.y, x.nu.y, L.C);
-  x.rev = x.kr * slot_fac(x.sp.z, x.nu.z, L.C) * slot_fac(x.sp.w, x.nu.w, L.C);
+  x.kf = exp_f64(lnkf);
+  x.kr = exp_f64(lnkf - lnKc);
+  x.fwd = x.kf * slot_fac(x.nu[0], x.c[0]) * slot_fac(x.nu[1], x.c[1]);
+  x.rev = x.kr * slot_fac(x.nu[2], x.c[2]) * slot_fac(x.nu[3], x.c[3]);
   return x;
 }
 
@@ -272,51 +301,63 @@ __device__ __forceinline__ Rxn rxn_eval(const DevMech &M, const GLds<G> &L, int 
 // adds: lanes of the group process different reactions that share species).
 // q = k_f prod C^nu' - k_r prod C^nu'', so dq/dC of a slot species is the
 // product of the other factors times the derivative of its own factor.  Per
-// slot species k_a (net coefficient nu_a: - for reactants, + for products)
-// and slot species k_b: row 1 + k_a, column 1 + k_b gets nu_a dq/dC_kb and
-// column 0 gets nu_a dq/dT; row 0, column 1 + k_b gets dH_r dq/dC_kb.
+// slot component a (net coefficient nu_a) and slot component b: row a, column b
+// gets nu_a dq/dC_b and column 0 gets nu_a dq/dT.  Only the second slots can be
+// empty: three masked regions.
 template <int G>
-__device__ __forceinline__ void jac_scatter(const GLds<G> &L, const Rxn &x, double dqT,
-                                            double dHr) {
-  const double f0 = slot_fac(x.sp.x, x.nu.x, L.C), f1 = slot_fac(x.sp.y, x.nu.y, L.C);
-  const double f2 = slot_fac(x.sp.z, x.nu.z, L.C), f3 = slot_fac(x.sp.w, x.nu.w, L.C);
-  // empty slots (coefficient 0) name the dummy species, which has no row or
-  // column in the matrix: they are skipped
-  const int sp[4] = {x.sp.x, x.sp.y, x.sp.z, x.sp.w};
-  const bool has[4] = {x.nu.x > 0, x.nu.y > 0, x.nu.z > 0, x.nu.w > 0};
-  double dq[4];
-  dq[0] = x.kf * (x.nu.x == 2 ? 2.0 * L.C[sp[0]] : 1.0) * f1;
-  dq[1] = x.kf * f0 * (x.nu.y == 2 ? 2.0 * L.C[sp[1]] : 1.0);
-  dq[2] = -x.kr * (x.nu.z == 2 ? 2.0 * L.C[sp[2]] : 1.0) * f3;
-  dq[3] = -x.kr * f2 * (x.nu.w == 2 ? 2.0 * L.C[sp[3]] : 1.0);
-  const double nu[4] = {-(double)x.nu.x, -(double)x.nu.y, (double)x.nu.z, (double)x.nu.w};
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    if (!has[a]) continue;
-    double *row = L.J + (1 + sp[a]) * L.js;
-    lds_add(row, nu[a] * dqT);
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-      if (has[b]) lds_add(row + 1 + sp[b], nu[a] * dq[b]);
+__device__ __forceinline__ void jac_scatter(const GLds<G> &L, const Rxn &x, double dqT) {
+  const double f0 = slot_fac(x.nu[0], x.c[0]), f1 = slot_fac(x.nu[1], x.c[1]);
+  const double f2 = slot_fac(x.nu[2], x.c[2]), f3 = slot_fac(x.nu[3], x.c[3]);
+  auto dfac = [](double nu, double c) { return fabs(nu) == 2.0 ? 2.0 * c : 1.0; };
+  const double q0 = x.kf * dfac(x.nu[0], x.c[0]) * f1;
+  const double q1 = x.kf * f0 * dfac(x.nu[1], x.c[1]);
+  const double q2 = -x.kr * dfac(x.nu[2], x.c[2]) * f3;
+  const double q3 = -x.kr * f2 * dfac(x.nu[3], x.c[3]);
+  const int c0 = x.sp.x, c1 = x.sp.y, c2 = x.sp.z, c3 = x.sp.w;
+  double *const r0 = L.J + c0 * L.js, *const r2 = L.J + c2 * L.js;
+  lds_add(r0, x.nu[0] * dqT);
+  lds_add(r2, x.nu[2] * dqT);
+  lds_add(r0 + c0, x.nu[0] * q0);
+  lds_add(r2 + c0, x.nu[2] * q0);
+  lds_add(r0 + c2, x.nu[0] * q2);
+  lds_add(r2 + c2, x.nu[2] * q2);
+  double *const r1 = L.J + c1 * L.js, *const r3 = L.J + c3 * L.js;
+  if (c1) {
+    lds_add(r1, x.nu[1] * dqT);
+    lds_add(r1 + c0, x.nu[1] * q0);
+    lds_add(r1 + c1, x.nu[1] * q1);
+    lds_add(r1 + c2, x.nu[1] * q2);
+    lds_add(r0 + c1, x.nu[0] * q1);
+    lds_add(r2 + c1, x.nu[2] * q1);
   }
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-    if (has[b]) lds_add(L.J + 1 + sp[b], dHr * dq[b]);
+  if (c3) {
+    lds_add(r3, x.nu[3] * dqT);
+    lds_add(r3 + c0, x.nu[3] * q0);
+    lds_add(r3 + c2, x.nu[3] * q2);
+    lds_add(r3 + c3, x.nu[3] * q3);
+    lds_add(r0 + c3, x.nu[0] * q3);
+    lds_add(r2 + c3, x.nu[2] * q3);
+    if (c1) {
+      lds_add(r1 + c3, x.nu[1] * q3);
+      lds_add(r3 + c1, x.nu[3] * q1);
+    }
+  }
 }
 
 // sum_j x[j] y[j] over j < n (LDS arrays), one FMA per term in index order.
 // The operands are read eight at a time, so a chunk costs one LDS round trip
 // instead of one per term; the last chunk reads with its indices clamped to
 // n - 1 and adds only its terms below n.
-__device__ __forceinline__ double dot_lds(const double *x, const double *y, int n) {
+template <int SX = 1, int SY = 1>
+__device__ __forceinline__ double dot_lds(const double *x, const double *y, int n, int sx = SX) {
   double acc = 0.0;
   int j0 = 0;
   for (; j0 + 8 <= n; j0 += 8) {
     double a[8], c[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      a[u] = x[j0 + u];
-      c[u] = y[j0 + u];
+      a[u] = x[(j0 + u) * sx];
+      c[u] = y[(j0 + u) * SY];
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) acc = fma(a[u], c[u], acc);
@@ -326,8 +367,8 @@ __device__ __forceinline__ double dot_lds(const double *x, const double *y, int 
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int j = min(j0 + u, n - 1);
-      a[u] = x[j];
-      c[u] = y[j];
+      a[u] = x[j * sx];
+      c[u] = y[j * SY];
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u)
@@ -336,18 +377,31 @@ __device__ __forceinline__ double dot_lds(const double *x, const double *y, int 
   return acc;
 }
 
-// Right-hand side (and optionally the Jacobian) of one cell.  Lane l holds
-// y_l in yl.  On return lane l holds f_l; species lanes hold wdot_k in wdl.
-// With JAC, LDS row l (l < n) of L.J holds row l of M = I*dg - J.  With KOUT
-// the rate constants are left in L.J (k_f at [r], k_r at [R + r]).
-template <int G, bool JAC, bool KOUT>
-__device__ __forceinline__ void eval_cell(const DevMech &M, const GLds<G> &L, int l, double p,
-                                          double yl, double &f, double &wdl, double dg) {
+// What the Newton matrix takes from an evaluation, per lane (row l).  With J the
+// LDS matrix and u = wd - sum_{c >= 1} J_lc C_c (0 in row 0): entry (l, c) for c >= 1
+// is [l == c] dg - (W J_lc + c2 u) iw_c, entry (l, 0) is col + cT u.
+struct NewtonRow {
+  double W, wd, c2, cT, col, dg;
+};
+
+// Right-hand side of one cell, and (jac, uniform over the wave) the species
+// rows of its Jacobian.  Lane l holds y_l in yl (species lanes: of species k).  On return lane l holds f_l;
+// species lanes hold wdot_k in wdl.  With jac, the LDS matrix holds d wdot_k/dC_j at
+// the species' components, and in row 0 the temperature's entries of M times W_j, so that
+// all rows of the Newton matrix M = I dg - J follow from NewtonRow.  With KOUT the rate
+// constants are left in L.J (k_f at [r], k_r at [R + r]).
+template <int G, bool KOUT>
+__device__ __forceinline__ void eval_cell(const DevMech &M, const GLds<G> &L, int l, int k,
+                                          double p, double yl, double &f, double &wdl, bool jac, double dg,
+                                          NewtonRow &nr) {
   const int K = M.K, R = M.R, n = M.n;
+  // the first reactions' constants, under way during the thermodynamics
+  const int last = max(R - 1, 0);
+  RxnIn in0 = rxn_load(M, min(l, last)), in1 = rxn_load(M, min(l + G, last));
   const double T = grp_first<G>(yl);
-  const double lnT = log(T), invT = 1.0 / T;
+  double miss;
+  const double lnT = T > 0.0 ? ln_f64(T) : NAN, invT = rcp_newton(T, miss);
   const bool isSp = (l >= 1) && (l <= K);
-  const int k = isSp ? l - 1 : 0;
   double cpR = 0.0, hRT = 0.0, sR = 0.0, dcpR = 0.0, Wk = 1.0, iWk = 1.0, Yk = 0.0;
   if (isSp) {
     Wk = M.W[k];
@@ -361,113 +415,125 @@ __device__ __forceinline__ void eval_cell(const DevMech &M, const GLds<G> &L, in
           hc[5 * K] * invT;
     sR = sc[0] * lnT + T * (sc[K] + T * (sc[2 * K] + T * (sc[3 * K] + T * sc[4 * K]))) +
          sc[5 * K];
-    if (JAC) dcpR = a[K] + T * (2.0 * a[2 * K] + T * (3.0 * a[3 * K] + T * (4.0 * a[4 * K])));
+    dcpR = a[K] + T * (2.0 * a[2 * K] + T * (3.0 * a[3 * K] + T * (4.0 * a[4 * K])));
   }
   const double S = grp_sum<G>(Yk * iWk);
-  const double rho = p / (RG * T * S);
-  const double irho = 1.0 / rho;
+  const double rho = p * rcp_newton(RG * T * S, miss);
   const double Ck = rho * Yk * iWk;
   const double cp = grp_sum<G>(Yk * RG * cpR * iWk);
-  if (isSp) {
-    L.C[k] = Ck;
-    L.gh[k] = make_double2(hRT - sR, hRT);
-  }
-  if (l == 0) {  // the dummy species of empty reaction slots
-    L.C[K] = 1.0;
-    L.gh[K] = make_double2(0.0, 0.0);
-  }
+  // component 0 is the empty slots' dummy
+  L.cg[l] = l == 0 ? make_double2(1.0, 0.0) : make_double2(Ck, hRT - sR);
+  L.h[l] = hRT;
   L.wa[l] = 0.0;
-  double *Jrow = L.J + l * L.js;
-  if (JAC && l < n)
-    for (int j = 0; j < n; ++j) Jrow[j] = 0.0;
+  if (jac) {
+    double2 *const J2 = (double2 *)L.J;
+    const int m2 = (n * L.js + 1) / 2;
+    for (int i = l; i < m2; i += G) J2[i] = make_double2(0.0, 0.0);
+  }
   wave_sync();
 
-  const double lnPRT = log(PREF / (RG * T));
-  double sumHq = 0.0;
-  // two reactions per pass: their loads and gathers are independent and
+  const double lnPRT = LN_PREF_RG - lnT;
+  // two reactions per pass: their gathers and exponentials are independent and
   // issue together before the adds to LDS
-  auto finish_rxn = [&](const Rxn &x, int r) {
+  auto finish_rxn = [&](const Rxn &x) __attribute__((always_inline)) {
     // wdot_k = sum_r (nu''_kr - nu'_kr) q_r, added from the reaction's lane
-    // (the dummy species of empty slots takes the zero terms)
+    // (the dummy of empty slots takes the zero terms)
     const double q = x.fwd - x.rev;
-    lds_add(L.wa + x.sp.x, -x.nu.x * q);
-    lds_add(L.wa + x.sp.y, -x.nu.y * q);
-    lds_add(L.wa + x.sp.z, x.nu.z * q);
-    lds_add(L.wa + x.sp.w, x.nu.w * q);
+    lds_add(L.wa + x.sp.x, x.nu[0] * q);
+    lds_add(L.wa + x.sp.y, x.nu[1] * q);
+    lds_add(L.wa + x.sp.z, x.nu[2] * q);
+    lds_add(L.wa + x.sp.w, x.nu[3] * q);
     if (KOUT) {
+      const int r = (int)(x.bits >> 16);
       L.J[r] = x.kf;
       L.J[R + r] = x.kr;
     }
-    if (JAC) {
+    if (!KOUT && jac) {
       // dq/dT at fixed C: d ln kf/dT = b/T + Ea/(R T^2), d ln Kc/dT = dH_r/(R T^2) - dn/T
-      const double dlnkf = M.b[r] * invT + M.EaR[r] * invT * invT;
-      const double dlnKc = (x.dH - x.dn) * invT;
+      const double dlnkf = x.b * invT + x.EaR * invT * invT;
+      const double dH = x.nu[0] * L.h[x.sp.x] + x.nu[1] * L.h[x.sp.y] + x.nu[2] * L.h[x.sp.z] +
+                        x.nu[3] * L.h[x.sp.w];
+      const double dlnKc = (dH - x.dn) * invT;
       const double dqT = x.fwd * dlnkf - x.rev * (dlnkf - dlnKc);
-      sumHq += RG * T * x.dH * dqT;
-      jac_scatter<G>(L, x, dqT, RG * T * x.dH);
+      jac_scatter<G>(L, x, dqT);
     }
   };
-  for (int r0 = l; r0 < R; r0 += 2 * G) {
-    const int r1 = r0 + G;
-    const bool two = r1 < R;
-    const Rxn x0 = rxn_eval<G>(M, L, r0, lnT, invT, lnPRT);
-    const Rxn x1 = rxn_eval<G>(M, L, two ? r1 : r0, lnT, invT, lnPRT);
-    finish_rxn(x0, r0);
-    if (two) finish_rxn(x1, r1);
+  for (int b0 = 0; b0 < R; b0 += 2 * G) {
+    const int r0 = b0 + l, r1 = r0 + G;
+    const bool pair = b0 + G < R;  // uniform
+    Rxn x0, x1;
+    x0 = rxn_eval<G>(L, in0, lnT, invT, lnPRT);
+    if (pair) x1 = rxn_eval<G>(L, in1, lnT, invT, lnPRT);
+    if (b0 + 2 * G < R) {
+      in0 = rxn_load(M, min(r0 + 2 * G, last));
+      in1 = rxn_load(M, min(r1 + 2 * G, last));
+    }
+    if (r0 < R) finish_rxn(x0);
+    if (r1 < R) finish_rxn(x1);
   }
   wave_sync();
 
-  const double wd = isSp ? L.wa[k] : 0.0;
+  const double wd = isSp ? L.wa[l] : 0.0;
   wdl = wd;
-  const double Q = grp_sum<G>(isSp ? RG * T * hRT * wd : 0.0);
-  const double fT = -Q * irho / cp;
+  const double Hk = isSp ? RG * T * hRT : 0.0;
+  const double Q = grp_sum<G>(Hk * wd);
+  const double irho = rcp_newton(rho, miss), icp = rcp_newton(cp, miss);
+  const double fT = -Q * irho * icp;
   f = (l == 0) ? fT : (isSp ? Wk * wd * irho : 0.0);
-  if (!JAC) return;
+  if (KOUT || !jac) return;
 
   // ---- analytic Jacobian ----
-  // The reaction loop left, per species row k (LDS row 1 + k): d wdot_k/dC_j
-  // at column 1 + j and sum_r nu_kr dq_r/dT at column 0; and in row 0,
-  // column 1 + j: sum_r dH_r dq_r/dC_j.
-  const double dcpdT = grp_sum<G>(Yk * RG * dcpR * iWk);
-  const double sumCpW = grp_sum<G>(isSp ? RG * cpR * wd : 0.0);
-  const double sumHqT = grp_sum<G>(sumHq);
-  double a = 0.0, dwdTC = 0.0, JwT = 0.0;
-  if (isSp) {
-    a = dot_lds(Jrow + 1, L.C, K);
-    dwdTC = Jrow[0];
-    JwT = L.J[1 + k];
-  }
-  const double aT = grp_sum<G>(isSp ? JwT * Ck : 0.0);
-  wave_sync();
   // chain rule through C_j(rho(T, Y), Y): dC_j/dY_i = rho d_ij/W_j - C_j/(S W_i),
-  // dC_j/dT = -C_j/T; each entry is written once, as the Newton matrix
-  // M = I/(gamma h) - J
-  const double irhocp = irho / cp;
+  // dC_j/dT = -C_j/T; the temperature's row is -1/(rho c_p) sum_k h_k times the
+  // species rows, and the terms of 1/(rho c_p), h_k(T)
+  double JwT = 0.0, dwdTC = 0.0;
   if (isSp) {
-    const double c2 = Wk * (wd - a) * irho / S;
-    // eight entries of the row read, then eight written: one LDS round trip
-    // per chunk (the last chunk reads with its indices clamped to K - 1)
-    for (int i0 = 0; i0 < K; i0 += 8) {
+    dwdTC = L.J[l * L.js];
+    JwT = RG * T * dot_lds(L.J + L.js + l, L.h + 1, K, L.js);
+  }
+  const double dcpdT = grp_sum<G>(Yk * RG * dcpR * iWk);
+  const double sumCpW = grp_sum<G>(RG * cpR * wd);
+  const double sumHqT = grp_sum<G>(Hk * dwdTC);
+  const double aT = grp_sum<G>(JwT * Ck);
+  const double irhocp = irho * icp, iS = rcp_newton(S, miss);
+  nr.dg = dg;
+  nr.W = isSp ? Wk : (l == 0 ? -1.0 : 0.0);
+  nr.wd = wd;
+  nr.c2 = isSp ? Wk * irho * iS : 0.0;
+  nr.cT = isSp ? -(Wk * irho * invT) : 0.0;
+  nr.col = isSp ? -(Wk * irho * dwdTC)
+                : (l == 0 ? dg - (-(sumCpW + sumHqT - aT * invT) * irhocp -
+                                  fT * (-invT + dcpdT * icp))
+                          : 0.0);
+  if (isSp) L.J[l] = (rho * JwT - aT * iS) * irhocp + fT * (RG * cpR * icp - iS);
+  wave_sync();
+}
+
+// The Newton matrix written out in LDS, row l by lane l.
+template <int G>
+__device__ __forceinline__ void newton_lds(const GLds<G> &L, int l, int n, const NewtonRow &nr) {
+  if (l < n) {
+    double *const row = L.J + l * L.js;
+    const double u =
+        l == 0 ? 0.0 : nr.wd - dot_lds<1, 2>(row + 1, (const double *)(L.cg + 1), n - 1);
+    const double c2 = nr.c2 * u;
+    // eight entries read, then eight written: one LDS round trip per chunk
+    for (int c0 = 1; c0 < n; c0 += 8) {
       double jr[8], iw[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = min(i0 + u, K - 1);
-        jr[u] = Jrow[1 + i];
-        iw[u] = M.invW[i];
+      for (int t = 0; t < 8; ++t) {
+        const int c = min(c0 + t, n - 1);
+        jr[t] = row[c];
+        iw[t] = L.iw[c];
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = i0 + u;
-        if (i < K) {
-          const double Jki = (Wk * jr[u] + c2) * iw[u];
-          Jrow[1 + i] = ((i == k) ? dg : 0.0) - Jki;
-        }
+      for (int t = 0; t < 8; ++t) {
+        const int c = c0 + t;
+        if (c < n) row[c] = (c == l ? nr.dg : 0.0) - (nr.W * jr[t] + c2) * iw[t];
       }
     }
-    Jrow[0] = -(Wk * irho * (dwdTC + (wd - a) * invT));
-    L.J[1 + k] = ((rho * JwT - aT / S) * iWk) * irhocp + fT * (-iWk / S + RG * cpR * iWk / cp);
+    row[0] = nr.col + nr.cT * u;
   }
-  if (l == 0) L.J[0] = dg - (-(sumCpW + sumHqT - aT * invT) * irhocp - fT * (-invT + dcpdT / cp));
   wave_sync();
 }
 
@@ -532,200 +598,259 @@ __device__ __forceinline__ bool gj_factor(double *A, int l, int n, int &mystep, 
   return ok;
 }
 
-// Largest of 32-bit integer values over the caller's group (one DPP max per
-// stage, as in grp_max).
-template <int G>
-__device__ __forceinline__ int grp_max_i32(int v) {
-  v = max(v, dpp_i32<0xB1>(v));
-  v = max(v, dpp_i32<0x4E>(v));
-  v = max(v, dpp_i32<0x141>(v));
-  v = max(v, dpp_i32<0x140>(v));
-  if (G >= 32) {
-    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
-    v = max((int)r[0], (int)r[1]);
-  }
-  if (G == 64) {
-    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
-    v = max((int)r[0], (int)r[1]);
-  }
-  return v;
-}
-template <int G>
-__device__ __forceinline__ unsigned grp_max_u32(unsigned v) {
-  v = max(v, (unsigned)dpp_i32<0xB1>((int)v));
-  v = max(v, (unsigned)dpp_i32<0x4E>((int)v));
-  v = max(v, (unsigned)dpp_i32<0x141>((int)v));
-  v = max(v, (unsigned)dpp_i32<0x140>((int)v));
-  if (G >= 32) {
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = max((unsigned)r[0], (unsigned)r[1]);
-  }
-  if (G == 64) {
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    v = max((unsigned)r[0], (unsigned)r[1]);
-  }
-  return v;
-}
-
-// Lowest lane (index within the caller's group) whose b is set; G if none.
-template <int G>
-__device__ __forceinline__ int grp_first_lane(bool b) {
-  const unsigned long long m = __ballot(b);
-  if (G == 64) return m ? __builtin_ctzll(m) : G;
-  const int g = ((int)threadIdx.x & 63) / G;
-  int out = G;
-#pragma unroll
-  for (int gg = 0; gg < 64 / G; ++gg) {
-    // bit G stands in for "no lane"
-    const unsigned long long part =
-        ((m >> (gg * G)) & ((1ull << (G & 63)) - 1ull)) | (1ull << (G & 63));
-    const int f = __builtin_ctzll(part);
-    out = (g == gg) ? f : out;
-  }
-  return out;
-}
-
-// Pivot lane of an elimination step: the lane with the largest v in the
-// group, the lowest lane among equal values.  v is +0 ... +inf (a candidate
-// row's |entry|) or -1 (a row already used), never NaN; on these values the
-// order of the doubles is the order of the pair (high word as a signed
-// integer, low word as an unsigned one), so the search runs on 32-bit words
-// and ends in a ballot of the lanes holding the maximum.
-template <int G>
-__device__ __forceinline__ bool grp_is_max(double v) {
+// ---- elimination with the diagonal as the pivots
+// The Newton matrix is I/(gamma h) - J: at the step sizes the error control
+// accepts, the diagonal is nearly always the largest entry left in its column
+// (with the components in DevMech::order, in all of the attempts sampled).  So the
+// pivots are taken on the diagonal without a search, each step verifies off the
+// chain that the search would have chosen it (ties to the lowest row are the
+// diagonal's), and only a group that fails repeats the elimination with the search.
+//
+// With the pivot row known at compile time its broadcast needs no LDS: lane p of
+// every 16-lane row reaches its row as the DPP operand of the FMAs (row_newbcast).
+// A group of 16 lanes holds one matrix row per lane.  In a group of 32, 16-lane row
+// h holds columns 16 h .. 16 h + 15 of all rows, two per lane: lane (h, i) has rows i
+// and 16 + i; the multipliers (column k, in one half only) cross to the other half by
+// v_permlane16_swap.
+//
+// A step is about 75 instructions (32 of them the FMAs); with the searched pivot
+// and its row's way through LDS (14 16-byte writes and reads) it took 2800 cycles of a
+// wave with eight others on the CU, now about 500.  30011 CH4/air cells, dt = 1e-5 s:
+// 58.9 -> 40.1 ms by this, 30.3 ms with the changes around it (reactions' order and
+// scatter, one copy of the evaluation, the factors kept in registers).
+template <int P>
+__device__ __forceinline__ double bcast16(double v) {
   const long long b = __double_as_longlong(v);
-  const int hi = (int)(b >> 32);
-  const unsigned lo = (unsigned)b;
-  const int mh = grp_max_i32<G>(hi);
-  const unsigned ml = grp_max_u32<G>(hi == mh ? lo : 0u);
-  return hi == mh && lo == ml;
-}
-template <int G>
-__device__ __forceinline__ int grp_argmax(double v) {
-  return grp_first_lane<G>(grp_is_max<G>(v));
-}
-// the wave's ballot of the lanes holding their group's maximum
-template <int G>
-__device__ __forceinline__ unsigned long long grp_argmax_mask(double v) {
-  return __ballot(grp_is_max<G>(v));
+  return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, b, 0x150 + P, 0xf, 0xf, false));
 }
 
-// c - m a as a three-address FMA: its result may go to another register than
-// c, so the rotation of the register row below costs no copies.
-__device__ __forceinline__ double fma_nm(double m, double a, double c) {
-  double d;
-  asm("v_fma_f64 %0, -%1, %2, %3" : "=v"(d) : "v"(m), "v"(a), "v"(c));
-  return d;
+// x[q] += m y[q](lane P of the 16-lane row), then y[q] likewise with my, for
+// four columns q: FMAs whose DPP operand is the broadcast.  The wait states
+// let a y[q] written just before reach the DPP read.
+template <int P>
+__device__ __forceinline__ void fma_bcast4(double &x0, double &x1, double &x2, double &x3,
+                                           double &y0, double &y1, double &y2, double &y3,
+                                           double mx, double my) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %4, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %5, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %6, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %7, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %4, %4, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %5, %5, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %6, %6, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %7, %7, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf"
+      : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3), "+v"(y0), "+v"(y1), "+v"(y2), "+v"(y3)
+      : "v"(mx), "v"(my), "n"(P));
+}
+// the same without the x rows (one matrix row per lane)
+template <int P>
+__device__ __forceinline__ void fma_bcast4(double &y0, double &y1, double &y2, double &y3,
+                                           double my) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %0, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %1, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+      : "+v"(y0), "+v"(y1), "+v"(y2), "+v"(y3)
+      : "v"(my), "n"(P));
 }
 
-// pairs of the pivot row broadcast by v_readlane instead of LDS (G = 32)
-constexpr int GJ_RL = 2;
+// lane i > P of each 16-lane row
+constexpr unsigned long long rows_after(int P) {
+  return ((0xfffeull << P) & 0xffffull) * 0x0001000100010001ull;
+}
 
-// gj_factor with each lane's row held in registers (groups of up to 32
-// lanes): slot 0 always holds the column being eliminated (the row is
-// rotated by one slot per step, so every index is a compile-time constant),
-// and the pivot row reaches the other lanes through pbuf (G doubles of LDS)
-// as one broadcast per step; the only LDS round trip left on a step's
-// dependency chain.  Every lane forms the reciprocal of its own candidate
-// pivot while the pivot is searched for, and the pivot lane sends its
-// reciprocal in place of the pivot (slot 0): the division leaves the chain.
-// Same arithmetic, in the same order, as gj_factor; the factors are written
-// back to the LDS rows at the end.
-template <int G>
-__device__ __forceinline__ bool gj_factor_reg(double *A, double *pbuf, int l, int n, int &mystep,
-                                              double &invd) {
-  static_assert(G <= 32, "the register row holds G doubles");
-  const int JS = GLds<G>::stride(n);
-  double *rowp = A + l * JS;
-  const bool real = l < n;
-  double r[G];
-#pragma unroll
-  for (int i = 0; i < G; ++i) r[i] = (real && i < n) ? rowp[i] : 0.0;
-  bool done = !real;
-  mystep = done ? l : -1;
-  invd = 1.0;
-  bool ok = true;  // this lane's pivot (if it was one) is finite and non-zero
-  // the reciprocal of slot 0, formed as soon as the slot is (at the end of
-  // the previous step)
-  double rinv = 1.0 / r[0];
-  for (int k = 0; k < n; ++k) {
-    double v = done ? -1.0 : fabs(r[0]);
-    if (v != v) v = INFINITY;
-    // the first GJ_RL pairs of the pivot row (slot 0 carrying the
-    // reciprocal) reach the other lanes by v_readlane from the pivot lanes of
-    // the wave's two groups, the rest through LDS: the LDS pipe, shared by
-    // every wave of the CU, is the integrator's busiest unit, and moving two
-    // of the sixteen pairs to the VALU was the fastest split measured
-    constexpr int RP = (G == 32) ? GJ_RL : 0;
-    int idx, q0 = 0, q1 = 0;
-    if constexpr (RP > 0) {
-      const unsigned long long bm = grp_argmax_mask<G>(v);
-      q0 = __builtin_ctzll((bm & 0xffffffffull) | (1ull << 32));
-      q1 = __builtin_ctzll((bm >> 32) | (1ull << 32));
-      idx = (((int)threadIdx.x & 63) < 32) ? q0 : q1;
-      q0 &= 31;
-      q1 = 32 + (q1 & 31);
-    } else {
-      idx = grp_argmax<G>(v);
+// Elimination steps K, K + 1, ...: a[x] is the lane's row 16 x + (l & 15).
+template <int K, int G>
+__device__ __forceinline__ void gj_diag_steps(double (&a)[2][16], int l, int n, double &invd,
+                                              unsigned long long &bad) {
+  if constexpr (K < G) {
+    // every fourth step may be the last (past n the padding's pivots are 1): the
+    // steps between are one block for the scheduler
+    if (K % 4 == 0 && K >= n) return;  // uniform
+    constexpr int P = K % 16, S = K / 16;
+    double(&piv)[16] = a[S];
+    double(&oth)[16] = a[S ^ 1];
+    double c = piv[P], d = 0.0;
+    if constexpr (G == 32) {
+      double e, o;
+      swap16(c, e, o);
+      c = S == 0 ? e : o;
+      swap16(oth[P], e, o);
+      d = S == 0 ? e : o;
     }
-    const bool isp = (l == idx);
-    // pbuf is 16-byte aligned: the row moves as G / 2 pairs (b128 accesses)
-    double2 *const pb2 = (double2 *)pbuf;
-    if (isp) {
-      if (RP == 0) pb2[0] = make_double2(rinv, r[1]);
+    const double pv = bcast16<P>(c);
+    double miss;
+    const double inv = rcp_newton(pv, miss);
+    // the lane compares are made here, not kept as masks across the steps (the
+    // scalar registers do not hold them): l and n are made to depend on the step
+    asm("" : "+v"(l), "+s"(n) : "v"(pv));
+    // a larger or NaN entry in a row not yet used, or an unusable pivot
+    bad |= __ballot(!(fabs(c) <= fabs(pv))) & rows_after(P);
+    if constexpr (G == 32 && S == 0) bad |= __ballot(!(fabs(d) <= fabs(pv)));
+    bad |= __ballot(!(fabs(miss) <= 1e-12));
+    invd = l == K ? inv : invd;
+    const bool isp = (l & 15) == P;
+    // minus the multipliers; the pivot row itself stays as it is
+    double mp = -(c * inv);
+    const double mo = -(d * inv);
+    const double cp = isp ? 1.0 : mp;
+    mp = isp ? 0.0 : mp;
 #pragma unroll
-      for (int i = (RP > 0 ? RP : 1); i < G / 2; ++i)
-        pb2[i] = make_double2(r[2 * i], r[2 * i + 1]);
-      if (!(fabs(r[0]) > 0.0) || !isfinite(r[0])) ok = false;
-      done = true;
-      mystep = k;
-      invd = rinv;
+    for (int t = 0; t < 16; t += 4) {
+      // the next step's column first
+      const int j0 = (P + 1 + t) & 15, j1 = (P + 2 + t) & 15, j2 = (P + 3 + t) & 15,
+                j3 = (P + 4 + t) & 15;
+      if constexpr (G == 32)
+        fma_bcast4<P>(oth[j0], oth[j1], oth[j2], oth[j3], piv[j0], piv[j1], piv[j2], piv[j3], mo,
+                      mp);
+      else
+        fma_bcast4<P>(piv[j0], piv[j1], piv[j2], piv[j3], mp);
+    }
+    const bool mine = G == 16 || (l >> 4) == S;
+    piv[P] = mine ? cp : piv[P];
+    if constexpr (G == 32) oth[P] = mine ? mo : oth[P];
+    gj_diag_steps<K + 1, G>(a, l, n, invd, bad);
+  }
+}
+
+// Gauss-Jordan factors of the Newton matrix (see NewtonRow) in registers: afterwards
+// a holds the rows of the inverse by unknown (laid out as in gj_diag_steps), not yet
+// scaled by the reciprocal pivots (invd: lane l's unknown l), with their columns in
+// pivot order: lane l's right-hand side belongs to column mystep.  They stay there
+// for the four solves (parked in LDS between the solves an attempt took 6 % longer).
+template <int G>
+__device__ __forceinline__ bool gj_factor_diag(const GLds<G> &L, int l, int n,
+                                               const NewtonRow &nr, double (&a)[2][16],
+                                               int &mystep, double &invd) {
+  static_assert(G <= 32, "one or two 16-lane rows");
+  constexpr int NS = G / 16;
+  const int i = l & 15, h = G == 32 ? (l >> 4) & 1 : 0;
+  // rows and columns past n read the last one and take W = c2 = 0 or iw = 0: zero
+  // off the diagonal, which is 1 there
+#pragma unroll
+  for (int x = 0; x < NS; ++x) {
+    const double *const src = L.J + min(16 * x + i, n - 1) * L.js;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) a[x][j] = src[min(16 * h + j, n - 1)];
+  }
+  // u of the lane's own row (NewtonRow): the row's sum over both halves' columns
+  double u;
+  {
+    double e[NS];
+#pragma unroll
+    for (int x = 0; x < NS; ++x) e[x] = 0.0;
+    const double2 *const C = L.cg + 16 * h;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      // C_0 is the empty slots' dummy, and past n nothing counts
+      const int c = 16 * h + j;
+      const double w = (c >= 1 && c < n) ? C[j].x : 0.0;
+#pragma unroll
+      for (int x = 0; x < NS; ++x) e[x] = fma(a[x][j], w, e[x]);
+    }
+    u = e[0];
+    if constexpr (G == 32) {
+      double e0, o0, e1, o1;
+      swap16(e[0], e0, o0);
+      swap16(e[1], e1, o1);
+      u = h ? e1 + o1 : e0 + o0;
+    }
+    u = l == 0 ? 0.0 : nr.wd - u;
+  }
+  // the lane's rows' coefficients
+  const double c2l = nr.c2 * u, coll = nr.col + nr.cT * u;
+  double W[2], c2[2], col[2];
+  if constexpr (G == 32) {
+    swap16(nr.W, W[0], W[1]);
+    swap16(c2l, c2[0], c2[1]);
+    swap16(coll, col[0], col[1]);
+  } else {
+    W[0] = nr.W;
+    c2[0] = c2l;
+    col[0] = coll;
+  }
+  const double2 *const iw = (const double2 *)(L.iw + 16 * h);
+#pragma unroll
+  for (int x = 0; x < NS; ++x) {
+    const int row = 16 * x + i;
+    const double dg = h != x ? 0.0 : (row < n ? nr.dg : 1.0);
+#pragma unroll
+    for (int j = 0; j < 16; j += 2) {
+      const double2 w = iw[j / 2];
+      a[x][j] = (i == j ? dg : 0.0) - (W[x] * a[x][j] + c2[x]) * w.x;
+      a[x][j + 1] = (i == j + 1 ? dg : 0.0) - (W[x] * a[x][j + 1] + c2[x]) * w.y;
+    }
+    a[x][0] = h == 0 ? (row < n ? col[x] : 0.0) : a[x][0];
+  }
+  invd = 1.0;
+  mystep = l;
+  unsigned long long bad = 0;
+  gj_diag_steps<0, G>(a, l, n, invd, bad);
+  const int gbase = ((int)threadIdx.x & 63) & ~(G - 1);
+  bool ok = true;
+  if ((bad >> gbase) & ((1ull << G) - 1ull)) {
+    // the search's elimination leaves the rows in their places: L.h takes the
+    // row of each unknown, L.wa the reciprocal pivots
+    newton_lds<G>(L, l, n, nr);
+    double id;
+    ok = gj_factor<G>(L.J, l, n, mystep, id);
+    ok = ok && !grp_any<G>(mystep < 0);
+    if (ok && l < n) {
+      L.h[mystep] = (double)l;
+      L.wa[mystep] = id;
     }
     wave_sync();
-    double2 q[G / 2];
 #pragma unroll
-    for (int i = RP; i < G / 2; ++i) q[i] = pb2[i];
-    if constexpr (RP > 0) {
-      const bool g0 = ((int)threadIdx.x & 63) < 32;
+    for (int x = 0; x < NS; ++x) {
+      const int row = 16 * x + i;
+      const double *const src = L.J + (ok && row < n ? (int)L.h[row] : 0) * L.js;
 #pragma unroll
-      for (int i = 0; i < RP; ++i) {
-        const double e0 = (i == 0) ? rinv : r[2 * i], e1 = r[2 * i + 1];
-        const double a0 = readlane_f64(e0, q0), b0 = readlane_f64(e0, q1);
-        const double a1 = readlane_f64(e1, q0), b1 = readlane_f64(e1, q1);
-        q[i] = make_double2(g0 ? a0 : b0, g0 ? a1 : b1);
+      for (int j = 0; j < 16; ++j) {
+        const int c = 16 * h + j;
+        const double v = src[min(c, n - 1)];
+        a[x][j] = (row < n && c < n) ? v : 0.0;
       }
     }
-    const double inv = q[0].x;
-    const double m = isp ? 0.0 : r[0] * inv;
-    double pr[G];
-#pragma unroll
-    for (int i = 1; i < G; ++i) pr[i] = (i & 1) ? q[i / 2].y : q[i / 2].x;
-    const double c0 = isp ? 1.0 : -m;
-    // the next step's column first, so that its reciprocal (formed here by
-    // every lane, not sunk into the pivot's branch) overlaps the other updates
-    r[0] = fma_nm(m, pr[1], r[1]);
-    rinv = 1.0 / r[0];
-    asm volatile("" : "+v"(rinv));
-#pragma unroll
-    for (int i = 1; i < G - 1; ++i) r[i] = fma_nm(m, pr[i + 1], r[i + 1]);
-    r[G - 1] = c0;
-    wave_sync();  // every lane has read pbuf before the next pivot row goes there
+    invd = ok && l < n ? L.wa[l] : 1.0;
   }
-  // after n rotations slot i holds column (n + i) mod G: G - n more put
-  // column i back in slot i, so the stores take constant offsets
-  for (int t = n; t < G; ++t) {
-    const double c0 = r[0];
-#pragma unroll
-    for (int i = 0; i < G - 1; ++i) r[i] = r[i + 1];
-    r[G - 1] = c0;
-  }
-  if (real) {
-#pragma unroll
-    for (int i = 0; i < G; ++i)
-      if (i < n) rowp[i] = r[i];
-  }
+  wave_sync();  // the matrix has been read
+  return ok;
+}
+
+// Solve M x = b with these factors.  Lane l passes b_l, gets x_l.
+template <int G>
+__device__ __forceinline__ double gj_solve_diag(const GLds<G> &L, const double (&a)[2][16], int l, int n, int mystep,
+                                                double invd, double b) {
+  double *const v = L.h;  // G doubles, 16-byte aligned: b in pivot order
+  v[l < n ? mystep : l] = l < n ? b : 0.0;
   wave_sync();
-  return !grp_any<G>(!ok);
+  const double2 *const w = (const double2 *)(v + (G == 16 ? 0 : (l & 16)));
+  double acc[G / 16], odd[G / 16];
+#pragma unroll
+  for (int x = 0; x < G / 16; ++x) acc[x] = odd[x] = 0.0;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const double2 q = w[t];
+#pragma unroll
+    for (int x = 0; x < G / 16; ++x) {
+      acc[x] = fma(a[x][2 * t], q.x, acc[x]);
+      odd[x] = fma(a[x][2 * t + 1], q.y, odd[x]);
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < G / 16; ++x) acc[x] += odd[x];
+  wave_sync();
+  double x = acc[0];
+  if constexpr (G == 32) {
+    // the two halves' columns, rows i to the first 16 lanes, 16 + i to the others
+    double e0, o0, e1, o1;
+    swap16(acc[0], e0, o0);
+    swap16(acc[1], e1, o1);
+    x = (l & 16) ? e1 + o1 : e0 + o0;
+  }
+  return l < n ? x * invd : 0.0;
 }
 
 // Solve M x = b with the factors of gj_factor.  Lane l passes b_l, gets x_l.
@@ -791,20 +916,22 @@ __global__ __launch_bounds__(64) void k_rates(DevMech M, int64_t N, int64_t ld, 
   constexpr int CPW = 64 / G;
   const int lane = threadIdx.x;
   const int g = lane / G, l = lane % G;
-  GLds<G> L(lds + g * GLds<G>::doubles(M.R, M.n), M.R, M.n);
+  GLds<G> L(lds, g, M.R, M.n);
+  const int k = (l >= 1 && l <= M.K) ? M.order[l - 1] : 0;
+  NewtonRow nr;
   for (int64_t base = (int64_t)blockIdx.x * CPW; base < N; base += (int64_t)gridDim.x * CPW) {
     const int64_t cell = base + g;
     if (cell >= N) break;  // group-uniform
     double yl = 0.0;
     if (l == 0) yl = T[cell];
-    else if (l <= M.K) yl = Y[(int64_t)(l - 1) * ld + cell];
+    else if (l <= M.K) yl = Y[(int64_t)k * ld + cell];
     const double pc = p[cell];
     double f, wd;
     if (kfkr)
-      eval_cell<G, false, true>(M, L, l, pc, yl, f, wd, 0.0);
+      eval_cell<G, true>(M, L, l, k, pc, yl, f, wd, false, 0.0, nr);
     else
-      eval_cell<G, false, false>(M, L, l, pc, yl, f, wd, 0.0);
-    if (l >= 1 && l <= M.K) wdot[(int64_t)(l - 1) * ld + cell] = wd;
+      eval_cell<G, false>(M, L, l, k, pc, yl, f, wd, false, 0.0, nr);
+    if (l >= 1 && l <= M.K) wdot[(int64_t)k * ld + cell] = wd;
     if (l == 0 && dTdt) dTdt[cell] = f;
     if (kfkr) {
       for (int r = l; r < M.R; r += G) {
@@ -820,9 +947,12 @@ template <int G>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step(DevMech M, StepArgs A) {
   extern __shared__ double lds[];
   const int lane = threadIdx.x;
-  const int g = lane / G, l = lane % G;
+  const int g = lane / G, l = lane % G, lane_in_group = l;
   const int n = M.n;
-  GLds<G> L(lds + g * GLds<G>::doubles(M.R, M.n), M.R, M.n);
+  GLds<G> L(lds, g, 0, M.n);
+  L.fill_iw(M);
+  wave_sync();
+  const int k = (l >= 1 && l < n) ? M.order[l - 1] : 0;  // the lane's species
   const StepOpts &o = A.o;
 
   // per-cell state (group-uniform scalars are replicated in every lane)
@@ -861,7 +991,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     gcell = cr.i;
     yl = 0.0;
     if (l == 0) yl = cr.T[gcell];
-    else if (l < n) yl = cr.Y[(int64_t)(l - 1) * cr.ld + gcell];
+    else if (l < n) yl = cr.Y[(int64_t)k * cr.ld + gcell];
     y0 = yl;
     p = cr.p[gcell];
     dt = cr.dt;
@@ -878,7 +1008,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     if (bad || !(T0 > 0.0) || !isfinite(p) || !(p > 0.0) || !(dt > 0.0) || !isfinite(dt))
       status = CELL_NONFINITE;
     // density at the initial state, for the rates output
-    const double s = grp_sum<G>((l >= 1 && l < n) ? yl / M.W[l - 1] : 0.0);
+    const double s = grp_sum<G>((l >= 1 && l < n) ? yl / M.W[k] : 0.0);
     rho0 = p / (RG * T0 * s);
   };
 
@@ -886,10 +1016,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const bool ok = (status == CELL_OK);
     if (ok && l < n) {
       if (l == 0) cr.T[gcell] = yl;
-      else cr.Y[(int64_t)(l - 1) * cr.ld + gcell] = yl;
+      else cr.Y[(int64_t)k * cr.ld + gcell] = yl;
     }
     if (cr.RR && l >= 1 && l < n)
-      cr.RR[(int64_t)(l - 1) * cr.ld + gcell] = ok ? rho0 * (yl - y0) / dt : 0.0;
+      cr.RR[(int64_t)k * cr.ld + gcell] = ok ? rho0 * (yl - y0) / dt : 0.0;
     if (l == 0) {
       if (cr.hh && ok) cr.hh[gcell] = h;
       if (cr.stats) {
@@ -901,8 +1031,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
   };
 
-  fetch();
-  while (__any(active)) {
+  bool want = true;  // the group has no cell and the queue may have one
+  for (;;) {
+    if (want) {
+      fetch();
+      want = false;
+    }
+    if (!__any(active)) break;
     if (active) {
       bool end = (status != CELL_OK) || !(t < dt);
       if (!end) {
@@ -924,37 +1059,51 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       }
       if (!end) {
         // ---- one RODAS3 attempt of size h from yl ----
-        double F, wd;
-        eval_cell<G, true, false>(M, L, l, p, yl, F, wd, 1.0 / (GAMMA * h));
-        int mystep;
-        double invd;
-        bool ok;
-        if constexpr (G <= 32)
-          ok = gj_factor_reg<G>(L.J, L.wa, l, n, mystep, invd);
-        else
-          ok = gj_factor<G>(L.J, l, n, mystep, invd);
+        // Stage loop kept rolled so that one copy of the right-hand side, of the
+        // elimination and of the solve is emitted: an attempt walks through all of
+        // the code, which has to stay in the instruction cache.  Terms with j >= s
+        // add exact zeros, so the sums equal the oracle's sums over j < s.
+        const double ih = 1.0 / h;
+        double F = 0.0, wd, K0 = 0.0, K1 = 0.0, K2 = 0.0, K3 = 0.0;
+        int mystep = l;
+        double invd = 1.0;
+        NewtonRow nr;
+        double fa[2][16];
+        bool ok = true;
+#pragma nounroll
+        for (int s = 0; s < 4; ++s) {
+          // addresses that follow from the lane are formed anew in each stage: kept
+          // across the loop they would push the reactions' values out of the registers
+          int l = lane_in_group;
+          asm volatile("" : "+v"(l));
+          if (s != 1) {
+            const double v = yl + TA_S(s, 0) * K0 + TA_S(s, 1) * K1 + TA_S(s, 2) * K2;
+            eval_cell<G, false>(M, L, l, k, p, v, F, wd, s == 0, ih / GAMMA, nr);
+          }
+          if (s == 0) {
+            if constexpr (G <= 32) {
+              ok = gj_factor_diag<G>(L, l, n, nr, fa, mystep, invd);
+            } else {
+              newton_lds<G>(L, l, n, nr);
+              ok = gj_factor<G>(L.J, l, n, mystep, invd);
+            }
+            if (!ok) break;
+          }
+          const double c = TC_S(s, 0) * K0 + TC_S(s, 1) * K1 + TC_S(s, 2) * K2;
+          double x;
+          if constexpr (G <= 32)
+            x = gj_solve_diag<G>(L, fa, l, n, mystep, invd, F + c * ih);
+          else
+            x = gj_solve<G>(L.J, L.h, l, n, mystep, invd, F + c * ih);
+          K0 = (s == 0) ? x : K0;
+          K1 = (s == 1) ? x : K1;
+          K2 = (s == 2) ? x : K2;
+          K3 = (s == 3) ? x : K3;
+        }
         if (!ok) {
           status = CELL_SINGULAR;
           end = true;
         } else {
-          // Stage loop kept rolled so that one copy of the right-hand side and
-          // of the triangular solve is emitted (the unrolled form overflows the
-          // instruction cache).  Terms with j >= s add exact zeros, so the
-          // sums equal the oracle's sums over j < s.
-          double K0 = 0.0, K1 = 0.0, K2 = 0.0, K3 = 0.0;
-#pragma nounroll
-          for (int s = 0; s < 4; ++s) {
-            if (TNEWF_S(s)) {
-              const double v = yl + TA_S(s, 0) * K0 + TA_S(s, 1) * K1 + TA_S(s, 2) * K2;
-              eval_cell<G, false, false>(M, L, l, p, v, F, wd, 0.0);
-            }
-            const double c = TC_S(s, 0) * K0 + TC_S(s, 1) * K1 + TC_S(s, 2) * K2;
-            const double x = gj_solve<G>(L.J, L.C, l, n, mystep, invd, F + c / h);
-            K0 = (s == 0) ? x : K0;
-            K1 = (s == 1) ? x : K1;
-            K2 = (s == 2) ? x : K2;
-            K3 = (s == 3) ? x : K3;
-          }
           double ynew = yl, errv = 0.0;
           ynew += TM[0] * K0;
           errv += TE[0] * K0;
@@ -972,17 +1121,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             r2 = rr * rr;
           }
           const double err = sqrt(grp_sum<G>(r2) / n);
+          // 0.9 err^(-1/3) where it is used (err positive and finite)
+          const double shrink = 0.9 * exp_f64(ln_f64(err) * (-1.0 / 3.0));
           if (isfinite(err) && err <= 1.0) {
             yl = ynew;
             t = last ? dt : t + h;
             ++nacc;
-            double fac = (err > 0.0) ? 0.9 * pow(err, -1.0 / 3.0) : fac_max;
+            double fac = (err > 0.0) ? shrink : fac_max;
             fac = fmin(fac_max, fmax(0.2, fac));
             h *= fac;
             fac_max = 6.0;
           } else {
             ++nrej;
-            double fac = isfinite(err) ? 0.9 * pow(err, -1.0 / 3.0) : 0.2;
+            double fac = isfinite(err) ? shrink : 0.2;
             fac = fmin(1.0, fmax(0.2, fac));
             h *= fac;
             fac_max = 1.0;
@@ -993,7 +1144,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       if (end) {
         if (status != CELL_OK) yl = y0;
         finish();
-        fetch();
+        active = false;
+        want = true;
       }
     }
   }
@@ -1025,8 +1177,9 @@ int group_size(int n) { return n <= 16 ? 16 : (n <= 32 ? 32 : 64); }
 
 size_t step_lds_bytes(const chem_mech *m, int G) {
   const int cpw = 64 / G;
-  return G == 16 ? lds_bytes<16>(m->R, m->d.n, cpw)
-                 : (G == 32 ? lds_bytes<32>(m->R, m->d.n, cpw) : lds_bytes<64>(m->R, m->d.n, cpw));
+  return (G == 16 ? lds_bytes<16>(0, m->d.n, cpw)
+                  : (G == 32 ? lds_bytes<32>(0, m->d.n, cpw) : lds_bytes<64>(0, m->d.n, cpw))) +
+         G * sizeof(double);
 }
 
 int max_waves_per_cu(size_t sh) {

@@ -74,34 +74,6 @@ struct SampleArgs {
   chem_sample_opts o;
 };
 
-// ln x of a finite positive x: x = 2^e m with m in [1/sqrt 2, sqrt 2),
-// ln m = 2 atanh(s) = 2 s + s z P(z) with s = (m - 1) / (m + 1), z = s^2 and P the
-// Chebyshev interpolant of degree 6 (relative error 4.2e-18 before rounding).
-__device__ __forceinline__ double ln_f64(double x) {
-  double m = __builtin_amdgcn_frexp_mant(x);
-  int e = __builtin_amdgcn_frexp_exp(x);
-  const bool up = m < 0.70710678118654752;
-  m = up ? 2.0 * m : m;
-  e = up ? e - 1 : e;
-  // the quotient by Newton's reciprocal (the divisor is in [1.7, 2.5])
-  const double num = m - 1.0, den = m + 1.0;
-  double r = __builtin_amdgcn_rcp(den);
-  r = fma(fma(-den, r, 1.0), r, r);
-  r = fma(fma(-den, r, 1.0), r, r);
-  double s = num * r;
-  s = fma(fma(-den, s, num), r, s);
-  const double z = s * s;
-  double P = fma(z, scalar_const(0.14617807153417325), scalar_const(0.15331611722055008));
-  P = fma(z, P, scalar_const(0.18182892432536871));
-  P = fma(z, P, scalar_const(0.22222211089379496));
-  P = fma(z, P, scalar_const(0.28571428626253836));
-  P = fma(z, P, scalar_const(0.39999999999898889));
-  P = fma(z, P, scalar_const(0.66666666666666696));
-  const double k = (double)e;
-  const double lo = fma(s * z, P, k * scalar_const(2.3190468138462996e-17));
-  return fma(k, scalar_const(0.69314718055994529), fma(2.0, s, lo));
-}
-
 // 1 + gamma c of Eq. (Yrand), the product rounded: where |ln y| is large, the
 // last bit of the exponent is most of the power's error.
 __device__ __forceinline__ double exponent(double gamma, double c) {
