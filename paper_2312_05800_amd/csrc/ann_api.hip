@@ -774,6 +774,86 @@ chem_status forward_members(ann_model *m, const InferWs &w, int64_t n, float *U,
   return CHEM_OK;
 }
 
+// The K-blocked weight copies, rebuilt after a weight change.
+chem_status refresh_tiled(ann_model *m, hipStream_t s) {
+  if (!m->wt_stale) return CHEM_OK;
+  chem_status st;
+  for (int l = 1; l <= 2; ++l)
+    if ((st = ann::tile_bf16(m->L[l].doutp, m->L[l].dinp, m->Wb[l], m->Wt[l], s)) != CHEM_OK)
+      return st;
+  if ((st = ann::tile_bf16(m->L[1].doutp, m->L[1].dinp, m->Wb[1], m->W2p, s, true)) != CHEM_OK)
+    return st;
+  m->wt_stale = false;
+  return CHEM_OK;
+}
+
+// Batches that mlp12's 128-cell tiles (one block per CU, 50 serial K-steps: 85 us from
+// the first cell on) would leave on fewer than three quarters of the CUs: each layer
+// as its own launch of small tiles, same arithmetic and bits.  First two layers
+// with the inputs, against the prologue and mlp12: 64 cells 22 against 99 us, 2003 33
+// against 106, 8000 50 against 110, 16000 79 against 113; 32000 cells 132 against 120.
+constexpr int64_t SMALL_CELLS = 192 * 128;
+bool small_path(const ann_model *m, const InferWs &w, int64_t n) {
+  ann::Mlp12Args f{};
+  f.N = m->L[1].doutp;
+  f.K = m->L[1].dinp;
+  f.X = w.X;
+  f.W1 = m->Wb[0];
+  f.b1 = m->bm[0];
+  f.W2p = m->W2p;
+  f.ldw2 = (long)m->L[1].doutp * 32;
+  f.b2 = m->bm[1];
+  f.H = w.H[1];
+  f.ldh = m->L[1].doutp;
+  return m->G == 1 && !m->use_fp8 && n < SMALL_CELLS && m->L[0].dinp == 32 &&
+         m->L[0].doutp == m->L[1].dinp && ann::mlp12_ok(f);
+}
+
+chem_status forward_small(ann_model *m, const InferWs &w, int64_t n, const ann::FeatArgs &fa,
+                          float *U, int ldu, hipStream_t s) {
+  chem_status st;
+  if ((st = refresh_tiled(m, s)) != CHEM_OK) return st;
+  const long cap = (long)w.cap;
+  if ((st = ann::feat_l1(fa, m->Wb[0], m->bm[0], m->L[0].doutp / 32, w.H[0], cap * 32, s)) !=
+      CHEM_OK)
+    return st;
+  ann::GemmArgs g{};
+  g.M = (int)n;
+  g.N = m->L[1].doutp;
+  g.K = m->L[1].dinp;
+  g.A = w.H[0];
+  g.lda = cap * 32;
+  g.B = m->W2p;
+  g.ldb = (long)m->L[1].doutp * 32;
+  g.bias = m->bm[1];
+  g.Cb = w.H[1];
+  g.ldcb = cap * 32;
+  g.tiled = ann::TILED_A | ann::TILED_B | ann::TILED_C;
+  if ((st = ann::gemm(g, true, true, ann::EPI_GELU, s, "mlp_l2")) != CHEM_OK) return st;
+  g.N = m->L[2].doutp;
+  g.K = m->L[2].dinp;
+  g.A = w.H[1];
+  g.B = m->Wt[2];
+  g.ldb = (long)m->L[2].doutp * 32;
+  g.bias = m->bm[2];
+  g.Cb = w.H[2];
+  g.ldcb = m->L[2].doutp;
+  g.tiled = ann::TILED_A | ann::TILED_B;
+  if ((st = ann::gemm(g, true, true, ann::EPI_GELU, s, "mlp_l3")) != CHEM_OK) return st;
+  ann::GemmArgs o{};
+  o.M = (int)n;
+  o.N = ldu;
+  o.K = m->L[3].dinp;
+  o.A = w.H[2];
+  o.lda = m->L[3].dinp;
+  o.B = m->Wb[3];
+  o.ldb = m->L[3].dinp;
+  o.bias = m->bm[3];
+  o.Cf = U;
+  o.ldcf = ldu;
+  return ann::gemm(o, true, true, ann::EPI_F32, s, "mlp_l4");
+}
+
 // keep_h1: write the first two layers' activations row-major to H[0], H[1]
 // (no fused first two layers, no K-blocked layouts), for the FP8 calibration
 // that reads their first n rows
@@ -782,20 +862,13 @@ chem_status forward_chunk(ann_model *m, const InferWs &w, int64_t n, int64_t ld,
                           float ood_margin, hipStream_t s, bool keep_h1 = false) {
   ann::FeatArgs fa{n, ld, T, p, Y, nullptr, m->n_out, m->L[0].dinp, m->nm.mu_in, m->nm.sd_in,
                    m->nm.lambda, w.X, ood, m->nm.lo, m->nm.hi, ood_margin};
-  chem_status st = ann::features(fa, s);
-  if (st != CHEM_OK) return st;
+  chem_status st;
+  if (!keep_h1 && small_path(m, w, n)) return forward_small(m, w, n, fa, U, ldu, s);
+  if ((st = ann::features(fa, s)) != CHEM_OK) return st;
   if (m->G > 1) return forward_members(m, w, n, U, ldu, s);
   const bool tl = !keep_h1 && tiled_path(m, n);
   const long cap = (long)w.cap;  // rows between K-blocks of the activations
-  if (!m->use_fp8 && m->wt_stale) {
-    for (int l = 1; l <= 2; ++l)
-      if ((st = ann::tile_bf16(m->L[l].doutp, m->L[l].dinp, m->Wb[l], m->Wt[l], s)) != CHEM_OK)
-        return st;
-    if ((st = ann::tile_bf16(m->L[1].doutp, m->L[1].dinp, m->Wb[1], m->W2p, s, true)) !=
-        CHEM_OK)
-      return st;
-    m->wt_stale = false;
-  }
+  if (!m->use_fp8 && (st = refresh_tiled(m, s)) != CHEM_OK) return st;
   if (m->use_fp8) {
     // L1 (BF16) -> E4M3 activations; L2, L3 on FP8 MFMA; L4 (BF16)
     const ann::Layer &L0 = m->L[0], &L2 = m->L[2], &L3 = m->L[3];

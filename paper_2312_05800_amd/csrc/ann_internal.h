@@ -143,6 +143,11 @@ struct FeatArgs {
 };
 chem_status features(const FeatArgs &a, hipStream_t s);
 
+// Prologue and first layer of a small batch (see k_feat_l1): n_in <= 32 inputs, nk
+// blocks of 32 features into the K-blocked H with ldh elements between K-blocks.
+chem_status feat_l1(const FeatArgs &f, const u16 *W1, const float *b1, int nk, u16 *H, long ldh,
+                    hipStream_t s);
+
 struct TargetArgs {
   int64_t n, ld;
   const double *Y0, *Y1;

@@ -357,8 +357,8 @@ __global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
   constexpr int NPW = (NI + WM - 1) / WM;
   constexpr int NMIN = NI / WM;
   static_assert(BM % 16 == 0 && BN % 16 == 0, "tile rows must be multiples of 16");
-  static_assert(STAGES == 1 || STAGES == 2 || STAGES == 3,
-                "ring of 2 or 3 stages, or 1 for a single K-step");
+  static_assert(STAGES >= 1 && (STAGES - 1) * NPW < 64,
+                "a ring (or one stage for a single K-step) whose loads vmcnt can count");
   __shared__ __attribute__((aligned(1024))) u16 S[STAGES * ROWS * BK];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -427,20 +427,24 @@ __global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
   // STAGES - 1 K-steps in flight ahead of the one being multiplied (a single
   // stage serves layers with one K-step only; two stages leave the CU room
   // for a second block, whose work covers this one's waits)
-  issue(0, 0);
-  if (STAGES == 3 && nk > 1) issue(1, 1);
+#pragma unroll
+  for (int p = 0; p < (STAGES > 1 ? STAGES - 1 : 1); ++p)
+    if (p < nk) issue(p, p);
   for (int kt = 0; kt < nk; ++kt) {
-    // this wave's loads of stage kt are done once at most the next stage's
-    // (NMIN or more instructions) remain; the barrier publishes every wave's
-    if (STAGES == 3 && kt + 1 < nk)
-      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(NMIN) : "memory");
+    // this wave's loads of stage kt are done once at most those of the
+    // STAGES - 2 stages after it (NMIN or more instructions each) remain; the
+    // barrier publishes every wave's
+    if (STAGES > 2 && kt + STAGES - 2 < nk)
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier"
+                   :
+                   : "n"(STAGES > 2 ? (STAGES - 2) * NMIN : 0)
+                   : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" : : : "memory");
-    // STAGES = 3: the ring slot of stage kt + 2 was last read in iteration
-    // kt - 1, which every wave finished before the barrier above
-    if (STAGES == 3 && kt + 2 < nk) issue((kt + 2) % STAGES, kt + 2);
-    // STAGES = 2: the slot of stage kt + 1 was last read in iteration kt - 1
-    if (STAGES == 2 && kt + 1 < nk) issue((kt + 1) % STAGES, kt + 1);
+    // the ring slot of stage kt + STAGES - 1 was last read in iteration kt - 1,
+    // which every wave finished before the barrier above
+    if (STAGES > 1 && kt + STAGES - 1 < nk)
+      issue((kt + STAGES - 1) % STAGES, kt + STAGES - 1);
     const u16 *T = S + (kt % STAGES) * ROWS * BK;
     bf16x8 x[TM16];
 #pragma unroll
@@ -586,11 +590,13 @@ chem_status gemm_dma16_cfg(const GemmArgs &g, int epi, hipStream_t s) {
   else if (epi == EPI_GELU_Q8)
     hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_GELU_Q8, STAGES>), grid, block, 0, s,
                        g);
-  else if (epi == EPI_GELU_NEXT && g.N <= BN && g.N2 == 32 &&
-           g.N2 * (BN + 4) <= STAGES * (BM + BN) * 32 && g.ldcf % 4 == 0)
-    hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_GELU_NEXT, STAGES>), grid, block, 0, s,
-                       g);
-  else {
+  else if (TN16 == 26 && epi == EPI_GELU_NEXT && g.N <= BN && g.N2 == 32 &&
+           g.N2 * (BN + 4) <= STAGES * (BM + BN) * 32 && g.ldcf % 4 == 0) {
+    // only the 416-feature tiles hold all features of their cells
+    if constexpr (TN16 == 26)
+      hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_GELU_NEXT, STAGES>), grid, block, 0, s,
+                         g);
+  } else {
     chem::set_error("gemm: unsupported epilogue for K-contiguous operands");
     return CHEM_EUNSUPPORTED;
   }
@@ -1481,6 +1487,13 @@ __device__ __forceinline__ float boxcox_fast(float y, float lam) {
   return (yl - 1.0f) / lam;
 }
 
+// Whether input feature j lies outside the widened training range (NaN does).
+__device__ __forceinline__ bool ood_feature(const FeatArgs &a, int j, float x) {
+  const float lo = a.lo[j], hi = a.hi[j], span = hi - lo;
+  const float tol = span > 0.0f ? a.ood_margin * span : 1e-6f * fmaxf(fabsf(hi), 1e-30f);
+  return !(x >= lo - tol && x <= hi + tol);
+}
+
 // One thread per cell: raw features (T, p, Box-Cox of Y), the optional
 // out-of-distribution bit, z-scored BF16 row of X.  DINP > 0 fixes the padded
 // width at compile time, so all of a cell's loads are issued before the first
@@ -1516,12 +1529,7 @@ __global__ __launch_bounds__(BLK) void k_features(FeatArgs a) {
           if (j == 0) x = (float)a.T[c];
           else if (j == 1) x = (float)a.p[c];
           else x = boxcox_fast((float)a.Y[(int64_t)(j - 2) * a.ld + c], a.lambda);
-          if (a.ood) {
-            const float lo = a.lo[j], hi = a.hi[j], span = hi - lo;
-            const float tol =
-                span > 0.0f ? a.ood_margin * span : 1e-6f * fmaxf(fabsf(hi), 1e-30f);
-            if (!(x >= lo - tol && x <= hi + tol)) outside = true;
-          }
+          if (a.ood && ood_feature(a, j, x)) outside = true;
           z[t] = (x - a.mu[j]) / a.sd[j];
         }
       }
@@ -1581,6 +1589,85 @@ __global__ void k_targets(TargetArgs a) {
     } else {
       for (int j = 0; j < TGT_BATCH && k0 + j < a.doutp; ++j) out[k0 + j] = v[j];
     }
+  }
+}
+
+// The prologue and the first layer of a small batch in one launch: H1 =
+// GELU(W1 x + b1), the arithmetic of mlp12's first layer (bias as the MFMA's C
+// input), stored as the second layer reads it, K-blocked with each block in the
+// order of mlp12_slot.  A block takes FL1_CELLS cells x a.kper K-blocks of 32
+// features; the blocks of one cell tile each compute its inputs (16 values per
+// thread: less than a launch).  Wave w owns cells 16 w .. + 15.
+constexpr int FL1_CELLS = 64;
+struct FeatL1Args {
+  FeatArgs f;       // f.X unused
+  const u16 *W1;    // [nk 32][32]
+  const float *b1;  // [nk 32]
+  u16 *H;           // [nk][ldh / 32 cells][32]
+  long ldh;
+  int nk, kper;     // K-blocks of 32 features, and per block of the grid
+};
+__global__ __launch_bounds__(256) void k_feat_l1(FeatL1Args a) {
+  constexpr int LW = 40;  // row of 32 inputs padded to 80 bytes
+  __shared__ __attribute__((aligned(16))) u16 xs[FL1_CELLS * LW];
+  __shared__ unsigned char out_s[4][FL1_CELLS];
+  const FeatArgs &f = a.f;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t c0 = (int64_t)blockIdx.x * FL1_CELLS;
+  {
+    // inputs 8 wave .. + 7 of cell `lane` (rows past n clamped: never stored)
+    const int64_t c = c0 + lane < f.n ? c0 + lane : f.n - 1;
+    float x[8], z[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int j = min(8 * wave + t, f.K + 1);
+      x[t] = (float)(j == 0 ? f.T[c] : (j == 1 ? f.p[c] : f.Y[(int64_t)(j - 2) * f.ld + c]));
+    }
+    bool outside = false;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int j = 8 * wave + t;
+      z[t] = 0.0f;
+      if (j < f.K + 2) {
+        const float v = j < 2 ? x[t] : boxcox_fast(x[t], f.lambda);
+        if (f.ood) outside = outside || ood_feature(f, j, v);
+        z[t] = (v - f.mu[j]) / f.sd[j];
+      }
+    }
+    uint4 o;
+    o.x = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){z[0], z[1]}, bf16x2));
+    o.y = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){z[2], z[3]}, bf16x2));
+    o.z = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){z[4], z[5]}, bf16x2));
+    o.w = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){z[6], z[7]}, bf16x2));
+    *(uint4 *)&xs[lane * LW + 8 * wave] = o;
+    out_s[wave][lane] = outside ? 1 : 0;
+  }
+  __syncthreads();
+  if (f.ood && blockIdx.y == 0 && wave == 0 && c0 + lane < f.n)
+    f.ood[c0 + lane] = out_s[0][lane] | out_s[1][lane] | out_s[2][lane] | out_s[3][lane];
+  const int r = lane & 15, g = lane >> 4;
+  const bf16x8 xin = *(const bf16x8 *)&xs[(16 * wave + r) * LW + 8 * g];
+  const int64_t cell = c0 + 16 * wave + r;
+  const int k0 = blockIdx.y * a.kper, k1 = min(a.nk, k0 + a.kper);
+  for (int kt = k0; kt < k1; ++kt) {
+    const u16 *const w = a.W1 + ((long)kt * 32 + r) * 32 + 8 * g;
+    const bf16x8 w0 = *(const bf16x8 *)w, w1 = *(const bf16x8 *)(w + 16 * 32);
+    const float4 b0 = *(const float4 *)(a.b1 + kt * 32 + 4 * g);
+    const float4 b1 = *(const float4 *)(a.b1 + kt * 32 + 16 + 4 * g);
+    f32x4 z0 = (f32x4){b0.x, b0.y, b0.z, b0.w}, z1 = (f32x4){b1.x, b1.y, b1.z, b1.w};
+    z0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0, xin, z0, 0, 0, 0);
+    z1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, xin, z1, 0, 0, 0);
+    uint4 o;
+    o.x = __builtin_bit_cast(
+        unsigned, __builtin_convertvector((f32x2){gelu(z0[0]), gelu(z0[1])}, bf16x2));
+    o.y = __builtin_bit_cast(
+        unsigned, __builtin_convertvector((f32x2){gelu(z0[2]), gelu(z0[3])}, bf16x2));
+    o.z = __builtin_bit_cast(
+        unsigned, __builtin_convertvector((f32x2){gelu(z1[0]), gelu(z1[1])}, bf16x2));
+    o.w = __builtin_bit_cast(
+        unsigned, __builtin_convertvector((f32x2){gelu(z1[2]), gelu(z1[3])}, bf16x2));
+    if (cell < f.n) *(uint4 *)(a.H + (long)kt * a.ldh + cell * 32 + 8 * g) = o;
   }
 }
 
@@ -2288,6 +2375,43 @@ bool dma16_ok(const GemmArgs &g) {
 }
 }  // namespace
 
+namespace {
+// Forward layers below the large tiles' launch sizes (K-contiguous or K-blocked
+// operands).  These launches are bound by the latency of their K-steps, so the
+// ring is deep (up to five K-steps in flight, where the register-staged k_gemm
+// prefetches one), and the tile is the largest that still gives the CUs blocks:
+// measured at 64, 500, 2003, 8000, 32000 cells, second layer (K = 1600, N = 800) 13.6,
+// 14.8, 22, 32, 92 us; third (K = 800, N = 416) 9.5, 9.2, 10.7, 16, 34 us, where k_gemm took
+// 28.5, 12, 13, 21, 56 us; output layer (K = 416, N = 32) 6.8 us at all of them, 10 to 13 before.
+// The 64 x 16 tiles at 2003 cells took 30 us for the second layer, the 128 x 80 ones 22 us
+// at 64 cells.  The MFMA's sums do not depend on the tile: same bits.
+chem_status gemm_dma16_small(const GemmArgs &g, int epi, hipStream_t s) {
+  auto blocks = [&](int bm, int bn) { return (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+  if (g.N <= 32) return gemm_dma16_cfg<4, 1, 2, 6>(g, epi, s);
+  if (g.N % 208 == 0 && blocks(256, 208) >= 250) return gemm_dma16_cfg<8, 2, 13>(g, epi, s);
+  if (g.N % 160 == 0 && blocks(256, 160) >= 500) return gemm_dma16_cfg<8, 2, 10>(g, epi, s);
+  if (blocks(128, 80) >= 400) return gemm_dma16_cfg<4, 2, 5, 4>(g, epi, s);
+  if (blocks(64, 80) >= 256) return gemm_dma16_cfg<4, 1, 5, 5>(g, epi, s);
+  if (blocks(64, 32) >= 200) return gemm_dma16_cfg<4, 1, 2, 6>(g, epi, s);
+  return gemm_dma16_cfg<4, 1, 1, 6>(g, epi, s);
+}
+}  // namespace
+
+chem_status feat_l1(const FeatArgs &f, const u16 *W1, const float *b1, int nk, u16 *H, long ldh,
+                    hipStream_t s) {
+  if (f.n <= 0) return CHEM_OK;
+  chem::ProfScope prof("ann_features_l1", s);
+  const unsigned cb = nblk(f.n, FL1_CELLS);
+  // about two blocks per CU, each computing the inputs of its cells again: 64 cells
+  // one K-block per block (8 us), 2003 four (12 us; one 16, thirteen 16), 8000 thirteen
+  // (18 us; one 34, fifty 38)
+  const int kper = (int)(((long)nk * cb + 511) / 512);
+  FeatL1Args a{f, W1, b1, H, ldh, nk, kper};
+  hipLaunchKernelGGL(k_feat_l1, dim3(cb, (nk + kper - 1) / kper), dim3(256), 0, s, a);
+  CHEM_HIP(hipGetLastError());
+  return CHEM_OK;
+}
+
 bool gemm_fuses_next(const GemmArgs &g) {
   return dma16_ok(g) && g.N == 416 && (long)((g.M + 255) / 256) >= 512 && g.N2 == 32 &&
          g.N2 <= g.ldcf && g.N2 * (416 + 4) <= 2 * (128 + 416) * 32 && g.B2 &&
@@ -2324,8 +2448,7 @@ chem_status gemm(const GemmArgs &g, bool AK, bool BK, int epi, hipStream_t s,
     return gemm_dma16_cfg<4, 2, 26, 2>(g, epi, s);
   }
   if (g.tiled) {
-    // K-blocked operands exist only on the direct-to-LDS path, whose launch
-    // thresholds the caller has checked (ann_api: at least 2^17 cells)
+    // K-blocked operands exist only on the direct-to-LDS path
     const long mt = (g.M + 255) / 256;
     if (!AK || !BK || epi == EPI_GELUGRAD || !dma16_ok(g) || (g.tiled & ~7)) {
       chem::set_error("gemm: K-blocked operands need the direct-to-LDS tiling");
@@ -2335,20 +2458,20 @@ chem_status gemm(const GemmArgs &g, bool AK, bool BK, int epi, hipStream_t s,
     if (g.N % 400 == 0 && mt * (g.N / 400) >= 512) return gemm_dma16_cfg<8, 2, 25>(g, epi, s);
     if (g.N % 416 == 0 && mt * (g.N / 416) >= 512) return gemm_dma16_cfg<8, 2, 26>(g, epi, s);
     if (g.N <= 32 && mt >= 512) return gemm_dma16_cfg<4, 4, 2>(g, epi, s);
-    chem::set_error("gemm: no direct-to-LDS tiling for this K-blocked shape");
-    return CHEM_EUNSUPPORTED;
+    return gemm_dma16_small(g, epi, s);
   }
   if (AK && BK && epi != EPI_GELUGRAD && !g.tile && dma16_ok(g)) {
     // forward layers through the direct-to-LDS ring when the launch has at
     // least two blocks per CU of work: K = 32 (first layer) in 64 x 320
     // single-stage tiles; 256 x 400 (or x 416) tiles; 256 x 32 for the
-    // 32-wide output layer
+    // 32-wide output layer; smaller tiles below that
     const long mt = (g.M + 255) / 256;
     if (g.K == 32 && g.N % 320 == 0 && 4 * mt * (g.N / 320) >= 512)
       return gemm_dma16_cfg<4, 1, 20, 1>(g, epi, s);
     if (g.N % 400 == 0 && mt * (g.N / 400) >= 512) return gemm_dma16_cfg<8, 2, 25>(g, epi, s);
     if (g.N % 416 == 0 && mt * (g.N / 416) >= 512) return gemm_dma16_cfg<8, 2, 26>(g, epi, s);
     if (g.N <= 32 && mt >= 512) return gemm_dma16_cfg<4, 4, 2>(g, epi, s);
+    return gemm_dma16_small(g, epi, s);
   }
   return gemm_tiled(g, AK, BK, epi, s);
 }
