@@ -1738,13 +1738,20 @@ __global__ void k_take_col(int64_t n, const float *src, int lds, float *dst, int
   if (i < n) dst[i * ldd] = src[i * lds];
 }
 
+// 1/x by the hardware's approximation and two Newton steps (x normal).
+__device__ __forceinline__ double rcp_f64(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
 // Weight of species k in the element projection: the expected variance of
 // the network's error in its change, sd^2 (sd = the target's standard
 // deviation), tapered to zero as the species' own mass fraction vanishes:
 // sd^2 (Y+ + 1e-10) / (Y+ + sd), Y+ = max(Y', 0).
 __device__ __forceinline__ double proj_weight(double y, float sdf) {
   const double yp = fmax(y, 0.0), sd = (double)sdf;
-  return sd * sd * (yp + 1e-10) / (yp + sd);
+  return sd * sd * (yp + 1e-10) * rcp_f64(yp + sd);
 }
 
 // h_k(T) in J/kg from the folded h/RT polynomial of species k's range at T.
@@ -1938,267 +1945,387 @@ __global__ void k_tile(int R, int K, const T *src, T *dst) {
 
 // ----------------------------------------------------------------- post
 
-// c_p/R and h/RT of species k at T (Tp = T, T^2, T^3, T^4, 1/T): both
-// ranges' coefficients are wave-uniform loads, the range is chosen per lane;
-// h/RT uses the coefficients with the divisors folded in.
-__device__ __forceinline__ void species_h_cp(const chem::DevMech &M, int k, const double *Tp,
-                                             double &hRT, double &cpR) {
-  const bool low = Tp[0] <= M.Tmid[k];
-  double c[5], h[6];
-#pragma unroll
-  for (int q = 0; q < 5; ++q) {
-    const double a = M.nasa_lo[7 * k + q], b = M.nasa_hi[7 * k + q];
-    c[q] = low ? a : b;
-  }
-#pragma unroll
-  for (int q = 0; q < 6; ++q) {
-    const double a = M.nasa_h[7 * k + q], b = M.nasa_hh[7 * k + q];
-    h[q] = low ? a : b;
-  }
-  cpR = c[0] + c[1] * Tp[0] + c[2] * Tp[1] + c[3] * Tp[2] + c[4] * Tp[3];
-  hRT = h[0] + h[1] * Tp[0] + h[2] * Tp[1] + h[3] * Tp[2] + h[4] * Tp[3] + h[5] * Tp[4];
-}
-
-__device__ __forceinline__ void tpowers(double T, double *Tp) {
-  Tp[0] = T;
-  Tp[1] = T * T;
-  Tp[2] = Tp[1] * T;
-  Tp[3] = Tp[2] * T;
-  Tp[4] = 1.0 / T;
-}
-
 constexpr int EMAX = 8;
+constexpr int POST_WAVES = 4, POST_CELLS = 64;
 
-// One thread per cell.  One streaming pass over the species builds Y' =
-// Y0 + dY (kept in registers, KP >= K slots), the element sums of Y0 and of
-// Y0 - Y', the weighted normal matrix and h(T0, Y0); Y0 itself is not kept (it
-// is read again for RR).  Four waves per SIMD (a few spilled registers) beat
-// two spill-free ones: the kernel is latency-bound (FP64 Cholesky and Newton
-// chains per cell).
-template <int KP, int EP>
-__global__ __launch_bounds__(128, 4) void k_post(chem::DevMech M, PostArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n) return;
+// constants through the scalar cache: the index is wave-uniform and nothing
+// writes the tables while a kernel runs
+template <typename T>
+using cptr = const __attribute__((address_space(4))) T *;
+template <typename T>
+__device__ __forceinline__ cptr<T> uni(const T *p) {
+  return (cptr<T>)(uintptr_t)p;
+}
+
+// Post-processing of the network's output.  A block of four waves owns 64
+// consecutive cells, one per lane: wave w holds species J w .. J w + J - 1 of them in
+// registers (Y0 and the new state), so that every row moves as 512
+// contiguous bytes, Y0 is read once, and a small batch spreads over four times the
+// waves.  The waves' partial sums meet in LDS, where the first wave adds them in order:
+// the weighted normal matrix, residuals, density and enthalpy; after the
+// projection the residuals and the mixture's NASA sums, from which it finds T.
+//
+// What a species needs of the mechanism is three cache lines of wave-uniform
+// constants (PostPack): touched first, while the wave's loads of Y0 and U are in
+// flight, and then loaded into scalar registers one species ahead of their use.  The
+// species past K are null ones, so that no branch separates the loads from
+// the arithmetic.
+//
+// Bound by the latency of its phases (loads, sums, the first wave's solve, Newton) with
+// four blocks per CU: the arithmetic is a third of its time.  One cell per thread with
+// all of its species (spills, Y0 read twice, each constant its own load): 46 us
+// at 64 cells, 60 at 2003, 375 at 2^20; this 8.5, 9 and 207 (30 species), the 2^20
+// at 3.1 TB/s.  With the constants loaded where they are used: 16 and 298 us.
+template <int J, int EP>
+__global__ __launch_bounds__(POST_WAVES * 64, EP <= 4 ? 4 : 1) void k_post(chem::DevMech M,
+                                                                         PostArgs a) {
+  constexpr int NA = EP * (EP + 1) / 2;
+  constexpr int Q1 = 2 + EP + NA;  // S0, h0, r, A
+  constexpr int Q2 = EP + 8;       // residuals, hm, the bounds of the NASA ranges
+  constexpr int NQ = Q1 > Q2 ? Q1 : Q2;
+  __shared__ double part[POST_WAVES][NQ][POST_CELLS];
+  __shared__ double lam_s[EP][POST_CELLS];
+  __shared__ double T_s[POST_CELLS], sc_s[POST_CELLS];
+  __shared__ unsigned char go_s[POST_CELLS];  // 1: the network's state stands
   const int K = M.K, E = M.E;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const int64_t c0 = (int64_t)blockIdx.x * POST_CELLS;
+  const bool live = c0 + lane < a.n;
+  const int64_t i = live ? c0 + lane : a.n - 1;
+  const int kw = w * J;  // the wave's first species
+  double y0[J], y[J];
+  float u[J];
+  // all loads first
+#pragma unroll
+  for (int j = 0; j < J; ++j) y0[j] = kw + j < K ? a.Y[(int64_t)(kw + j) * a.ld + i] : 0.0;
+#pragma unroll
+  for (int j = 0; j < J; j += 4) {
+    // doutp is a multiple of 32, at least K
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (kw + j < K) v = *(const float4 *)(a.U + i * a.doutp + kw + j);
+    u[j] = v.x;
+    u[j + 1] = v.y;
+    u[j + 2] = v.z;
+    u[j + 3] = v.w;
+  }
   const double T0 = a.T[i], p = a.p[i];
   uint8_t flag = (uint8_t)a.force_flag;
   // out of distribution: any input feature outside the widened training range
   // (tested by k_features on the same cells)
   if (a.ood && a.ood[i]) flag |= 1;
-  double yn[KP];
-  double A[EP][EP], r[EP], z0[EP];
+  const cptr<chem::PostPack> pp = uni(M.pp) + kw;
+  {
+    int t = 0;
 #pragma unroll
-  for (int e = 0; e < EP; ++e) {
-    r[e] = 0.0;
-    z0[e] = 0.0;
-#pragma unroll
-    for (int f = 0; f < EP; ++f) A[e][f] = 0.0;
+    for (int j = 0; j < J; ++j) {
+      t |= (int)__builtin_bit_cast(uint64_t, pp[j].lo[0]);
+      t |= (int)__builtin_bit_cast(uint64_t, pp[j].hi[0]);
+      t |= (int)__builtin_bit_cast(uint64_t, pp[j].el[2]);
+    }
+    asm volatile("" : : "s"(t));
   }
-  double S0 = 0.0, h0 = 0.0, Tp[5];
-  tpowers(T0, Tp);
-  const bool vec = a.doutp % 4 == 0;
-  // Species in chunks of CH: the chunk's Y0 and U loads are issued together
-  // (indices past the last species are clamped into range and their values
-  // unused), ahead of the per-species branches that would otherwise hold
-  // each load back until the previous species is done.  All of a cell's U
-  // (one row of doutp floats) is then read while its lines are in cache.
-  constexpr int CH = 8;
+  // the de-normalisation of the wave's species (those past K: no change, any
+  // positive deviation)
+  float sd[J], mu[J];
 #pragma unroll
-  for (int k0 = 0; k0 < KP; k0 += CH) {
-    double y0c[CH];
-    float uc[CH];
-#pragma unroll
-    for (int t = 0; t < CH; ++t) y0c[t] = a.Y[(int64_t)min(k0 + t, K - 1) * a.ld + i];
-    if (vec) {
-#pragma unroll
-      for (int q = 0; q < CH; q += 4) {
-        const float4 v = *(const float4 *)(a.U + i * a.doutp + min(k0 + q, a.doutp - 4));
-        uc[q] = v.x;
-        uc[q + 1] = v.y;
-        uc[q + 2] = v.z;
-        uc[q + 3] = v.w;
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < CH; ++t) uc[t] = a.U[i * a.doutp + min(k0 + t, K - 1)];
-    }
-#pragma unroll
-    for (int t = 0; t < CH; ++t) {
-      const int k = k0 + t;
-      yn[k] = 0.0;
-      if (k < K) {
-        const double y0 = y0c[t];
-        const float du = uc[t] * a.nm.sd_out[k] + a.nm.mu_out[k];
-        const double y = y0 + (double)du;  // Y' = Y0 + sd u + mu
-        yn[k] = y;
-        const double d = proj_weight(y, a.nm.sd_out[k]);
-        S0 += y0 * M.invW[k];
-        double hRT, cpR;
-        species_h_cp(M, k, Tp, hRT, cpR);
-        h0 += y0 * RG * T0 * hRT * M.invW[k];
-        // weighted least-squares projection onto M Y = M Y0, D = diag(proj_weight)
-#pragma unroll
-        for (int e = 0; e < EP; ++e) {
-          if (e < E) {
-            const double me = M.Mel[e * K + k];
-            r[e] += me * (y0 - y);
-            z0[e] += me * y0;
-#pragma unroll
-            for (int f = 0; f <= e; ++f) A[e][f] += me * d * M.Mel[f * K + k];
-          }
-        }
-      }
-    }
-  }
-  double Lc[EP][EP], lam[EP];
-  bool ok = true;
-#pragma unroll
-  for (int e = 0; e < EP; ++e) {
-#pragma unroll
-    for (int f = 0; f <= e; ++f) {
-      if (e < E) {
-        double v = A[e][f];
-#pragma unroll
-        for (int q = 0; q < f; ++q) v -= Lc[e][q] * Lc[f][q];
-        if (e == f) {
-          if (!(v > 0.0)) ok = false;
-          Lc[e][e] = sqrt(fmax(v, 1e-300));
-        } else {
-          Lc[e][f] = v / Lc[f][f];
-        }
-      }
-    }
+  for (int j = 0; j < J; ++j) {
+    const int k = kw + j < K ? kw + j : K - 1;
+    sd[j] = uni(a.nm.sd_out)[k];
+    mu[j] = uni(a.nm.mu_out)[k];
   }
 #pragma unroll
-  for (int e = 0; e < EP; ++e) {
-    lam[e] = 0.0;
-    if (e < E) {
-      double v = r[e];
-#pragma unroll
-      for (int q = 0; q < e; ++q) v -= Lc[e][q] * lam[q];
-      lam[e] = v / Lc[e][e];
-    }
+  for (int j = 0; j < J; ++j) {
+    const bool real = kw + j < K;
+    sd[j] = real ? sd[j] : 1.0f;
+    const float du = u[j] * sd[j] + mu[j];
+    y[j] = y0[j] + (real ? (double)du : 0.0);  // Y' = Y0 + sd u + mu
   }
-#pragma unroll
-  for (int e = EP - 1; e >= 0; --e) {
-    if (e < E) {
-      double v = lam[e];
-#pragma unroll
-      for (int q = e + 1; q < EP; ++q)
-        if (q < E) v -= Lc[q][e] * lam[q];
-      lam[e] = v / Lc[e][e];
-    }
-  }
-  // projected and clipped state, and its element residual
-  double z1[EP];
-#pragma unroll
-  for (int e = 0; e < EP; ++e) z1[e] = 0.0;
-#pragma unroll
-  for (int k = 0; k < KP; ++k) {
-    if (k < K) {
-      double corr = 0.0;
-#pragma unroll
-      for (int e = 0; e < EP; ++e)
-        if (e < E) corr += M.Mel[e * K + k] * lam[e];
-      const double y = fmax(yn[k] + proj_weight(yn[k], a.nm.sd_out[k]) * corr, 0.0);
-      yn[k] = y;
-#pragma unroll
-      for (int e = 0; e < EP; ++e)
-        if (e < E) z1[e] += M.Mel[e * K + k] * y;
-    }
-  }
-  // residuals: of the network's own state Y' (r = M Y0 - M Y', which the
-  // projection removes), and of the projected, clipped state; either above
-  // the tolerance (or non-finite) flags the cell
-  const double rtol_e = (double)a.residual_tol;
-  bool bad = !ok;
-#pragma unroll
-  for (int e = 0; e < EP; ++e)
-    if (e < E) bad = bad || !(fabs(z1[e] - z0[e]) <= rtol_e) || !(fabs(r[e]) <= rtol_e);
-  if (bad) flag |= 2;
 
-  if (flag == 0) {
-    // temperature from h(T, Y) = h(T0, Y0) by Newton in FP64.  h and c_p of
-    // the mixture are linear in Y: with every species in the NASA range it
-    // takes at a reference temperature, they are polynomials in T whose
-    // coefficients are the Y / W-weighted sums of the species' (hm: h/RT
-    // terms with the divisors folded in, cm: c_p/R terms), exact for
-    // tlo < T <= thi; a Newton step then costs O(1), and the sums are built
-    // again only if an iterate leaves that interval.
-    double hm[6], cm[5], tlo = 0.0, thi = -1.0;
-    auto mixture = [&](double Tr) __attribute__((always_inline)) {
+  // the halves of a species' constants, each loaded while the half before it is in
+  // use: the address is made to depend on that one, and issued after the
+  // arithmetic of the half before that (else the scheduler loads them all first)
+  struct Lo { double h[6], invW, Tmid; };
+  struct Hi { double h[6], el[EP]; };
+  auto after = [](cptr<chem::PostPack> q, double c) __attribute__((always_inline)) {
+    asm volatile("" : "+s"(q) : "s"(c));
+    return q;
+  };
+  auto done = [](const double *v, int n) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < n; ++t) asm volatile("" : : "v"(v[t]));
+  };
+  auto load_lo = [](cptr<chem::PostPack> q) __attribute__((always_inline)) {
+    Lo c;
+#pragma unroll
+    for (int t = 0; t < 6; ++t) c.h[t] = q->lo[t];
+    c.invW = q->invW;
+    c.Tmid = q->Tmid;
+    return c;
+  };
+  auto load_hi = [](cptr<chem::PostPack> q) __attribute__((always_inline)) {
+    Hi c;
+#pragma unroll
+    for (int t = 0; t < 6; ++t) c.h[t] = q->hi[t];
+#pragma unroll
+    for (int e = 0; e < EP; ++e) c.el[e] = q->el[e];
+    return c;
+  };
+  auto add_h = [](const double *c, double x, double *hm) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q) hm[q] = fma(x, c[q], hm[q]);
+  };
+
+  // ---- partial sums over the wave's species
+  {
+    double S0 = 0.0, hm[6], r[EP], A[NA];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) hm[q] = 0.0;
+#pragma unroll
+    for (int e = 0; e < EP; ++e) r[e] = 0.0;
+#pragma unroll
+    for (int q = 0; q < NA; ++q) A[q] = 0.0;
+    Lo a0 = load_lo(pp);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const Hi c = load_hi(after(pp + j, a0.invW));
+      const double d = proj_weight(y[j], sd[j]);
+      const double x = y0[j] * a0.invW;
+      S0 += x;
+      // h(T0, Y0) from the sums of the polynomials of the range T0 selects
+      const bool low = T0 <= a0.Tmid;
+      add_h(a0.h, low ? x : 0.0, hm);
+      done(hm, 6);
+      if (j + 1 < J) a0 = load_lo(after(pp + j + 1, c.el[0]));
+      add_h(c.h, low ? 0.0 : x, hm);
+      // weighted least-squares projection onto M Y = M Y0, D = diag(d)
+      const double dy = y0[j] - y[j];
+      int q = 0;
+#pragma unroll
+      for (int e = 0; e < EP; ++e) {
+        if (EP == 4 || e < E) {
+          r[e] = fma(c.el[e], dy, r[e]);
+          const double md = c.el[e] * d;
+#pragma unroll
+          for (int f = 0; f <= e; ++f) A[q + f] = fma(md, c.el[f], A[q + f]);
+        }
+        q += e + 1;
+      }
+      done(hm, 6);
+      done(r, EP);
+      done(A, NA);
+    }
+    double(*const o)[POST_CELLS] = part[w];
+    o[0][lane] = S0;
+    o[1][lane] =
+        hm[5] + T0 * (hm[0] + T0 * (hm[1] + T0 * (hm[2] + T0 * (hm[3] + T0 * hm[4]))));
+#pragma unroll
+    for (int e = 0; e < EP; ++e)
+      if (e < E) o[2 + e][lane] = r[e];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) o[2 + EP + q][lane] = A[q];
+  }
+  __syncthreads();
+  auto total = [&](int q) __attribute__((always_inline)) {
+    return (part[0][q][lane] + part[1][q][lane]) + (part[2][q][lane] + part[3][q][lane]);
+  };
+  // first wave: the element multipliers by a Cholesky factorisation (L D L^T), and
+  // what the flags and the rates take later
+  double rho0 = 0.0, h0 = 0.0;
+  bool bad = false;
+  if (w == 0) {
+    double r[EP], A[EP][EP], L[EP][EP], inv[EP], lam[EP];
+    rho0 = p / (RG * T0 * total(0));
+    h0 = total(1);  // over R
+    bool ok = true;
+    int q = 2 + EP;
+#pragma unroll
+    for (int e = 0; e < EP; ++e) {
+      r[e] = lam[e] = inv[e] = 0.0;
+      if (e < E) {
+        r[e] = total(2 + e);
+#pragma unroll
+        for (int f = 0; f <= e; ++f) A[e][f] = total(q + f);
+      }
+      q += e + 1;
+    }
+    const double rtol_e = (double)a.residual_tol;
+    // the residual of the network's own state Y' (r = M Y0 - M Y', which the
+    // projection removes)
+#pragma unroll
+    for (int e = 0; e < EP; ++e)
+      if (e < E) bad = bad || !(fabs(r[e]) <= rtol_e);
+#pragma unroll
+    for (int e = 0; e < EP; ++e) {
+      if (e < E) {
+        double dd = A[e][e], v = r[e];
+#pragma unroll
+        for (int f = 0; f < e; ++f) {
+#pragma unroll
+          for (int g = 0; g < f; ++g) A[e][f] = fma(-A[e][g], L[f][g], A[e][f]);
+          L[e][f] = A[e][f] * inv[f];
+        }
+#pragma unroll
+        for (int f = 0; f < e; ++f) {
+          dd = fma(-A[e][f], L[e][f], dd);
+          v = fma(-L[e][f], lam[f], v);
+        }
+        if (!(dd > 0.0)) ok = false;
+        inv[e] = rcp_f64(fmax(dd, 1e-300));
+        lam[e] = v;
+      }
+    }
+#pragma unroll
+    for (int e = EP - 1; e >= 0; --e) {
+      if (e < E) {
+        double v = lam[e] * inv[e];
+#pragma unroll
+        for (int g = e + 1; g < EP; ++g)
+          if (g < E) v = fma(-L[g][e], lam[g], v);
+        lam[e] = v;
+        lam_s[e][lane] = v;
+      }
+    }
+    bad = bad || !ok;
+    T_s[lane] = T0;
+  }
+  __syncthreads();
+  // ---- projected and clipped state, what it changed of the elements
+  {
+    double lam[EP], z[EP], nx[EP];
+#pragma unroll
+    for (int e = 0; e < EP; ++e) {
+      lam[e] = e < E ? lam_s[e][lane] : 0.0;
+      z[e] = 0.0;
+      nx[e] = pp->el[e];
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      double corr = 0.0, el[EP];
+#pragma unroll
+      for (int e = 0; e < EP; ++e) el[e] = nx[e];
+      if (j + 1 < J) {
+        const cptr<chem::PostPack> q = after(pp + j + 1, el[0]);
+#pragma unroll
+        for (int e = 0; e < EP; ++e) nx[e] = q->el[e];
+      }
+#pragma unroll
+      for (int e = 0; e < EP; ++e)
+        if (EP == 4 || e < E) corr = fma(el[e], lam[e], corr);
+      y[j] = fmax(fma(proj_weight(y[j], sd[j]), corr, y[j]), 0.0);
+      const double dy = y[j] - y0[j];
+#pragma unroll
+      for (int e = 0; e < EP; ++e)
+        if (EP == 4 || e < E) z[e] = fma(el[e], dy, z[e]);
+      done(z, EP);
+    }
+#pragma unroll
+    for (int e = 0; e < EP; ++e)
+      if (e < E) part[w][e][lane] = z[e];
+  }
+  // temperature from h(T, Y) = h(T0, Y0) by Newton in FP64.  h and c_p of the
+  // mixture are linear in Y: with every species in the NASA range it takes at a
+  // reference temperature, they are polynomials in T whose coefficients are the
+  // Y / W-weighted sums of the species' (hm: h/RT; those of c_p/R are multiples),
+  // exact for tlo < T <= thi; a Newton step then costs O(1), and the sums are built
+  // again, by all waves, only where an iterate leaves that interval.
+  double T = T0;
+  int it = 0;
+  bool need = true;  // first wave: the cell's sums are to be built at T_s
+  for (;;) {
+    {
+      const double Tr = T_s[lane];
+      double hm[6], tlo = -INFINITY, thi = INFINITY;
 #pragma unroll
       for (int q = 0; q < 6; ++q) hm[q] = 0.0;
+      Lo a0 = load_lo(after(pp, 0.0));
 #pragma unroll
-      for (int q = 0; q < 5; ++q) cm[q] = 0.0;
-      tlo = -INFINITY;
-      thi = INFINITY;
+      for (int j = 0; j < J; ++j) {
+        double hi[6];
+        const cptr<chem::PostPack> q = after(pp + j, a0.invW);
 #pragma unroll
-      for (int k = 0; k < KP; ++k) {
-        if (k < K) {
-          const double w = yn[k] * M.invW[k];
-          const double tm = M.Tmid[k];
-          const bool low = Tr <= tm;
-          thi = low ? fmin(thi, tm) : thi;
-          tlo = low ? tlo : fmax(tlo, tm);
-#pragma unroll
-          for (int q = 0; q < 6; ++q) {
-            const double lo = M.nasa_h[7 * k + q], hi = M.nasa_hh[7 * k + q];
-            hm[q] += w * (low ? lo : hi);
-          }
-#pragma unroll
-          for (int q = 0; q < 5; ++q) {
-            const double lo = M.nasa_lo[7 * k + q], hi = M.nasa_hi[7 * k + q];
-            cm[q] += w * (low ? lo : hi);
-          }
-        }
+        for (int t = 0; t < 6; ++t) hi[t] = q->hi[t];
+        const double x = y[j] * a0.invW;
+        const bool low = Tr <= a0.Tmid;
+        thi = low ? fmin(thi, a0.Tmid) : thi;
+        tlo = low ? tlo : fmax(tlo, a0.Tmid);
+        add_h(a0.h, low ? x : 0.0, hm);
+        done(hm, 6);
+        if (j + 1 < J) a0 = load_lo(after(pp + j + 1, hi[0]));
+        add_h(hi, low ? 0.0 : x, hm);
+        done(hm, 6);
       }
-    };
-    double T = T0;
-    for (int it = 0; it < 20; ++it) {
-      if (!(T > tlo && T <= thi)) mixture(T);
-      tpowers(T, Tp);
-      const double hRT = hm[0] + hm[1] * Tp[0] + hm[2] * Tp[1] + hm[3] * Tp[2] +
-                         hm[4] * Tp[3] + hm[5] * Tp[4];
-      const double cpR = cm[0] + cm[1] * Tp[0] + cm[2] * Tp[1] + cm[3] * Tp[2] + cm[4] * Tp[3];
-      const double dT = (RG * T * hRT - h0) / (RG * cpR);
-      T -= dT;
-      if (!isfinite(T) || fabs(dT) < 1e-9 * T) break;
+      double(*const o)[POST_CELLS] = part[w] + EP;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) o[q][lane] = hm[q];
+      o[6][lane] = tlo;
+      o[7][lane] = thi;
     }
-    if (!isfinite(T) || !(T > 0.0)) flag |= 2;
-    if (flag == 0) {
-      const double rho0 = p / (RG * T0 * S0);
-      const double sc = rho0 / a.dt;
-      // Y0 is read again for the rates, eight species at a time before their
-      // stores (a load placed after a store that may alias it waits for it)
-      constexpr int WB = 8;
+    __syncthreads();
+    if (w == 0 && need) {
+      if (it == 0) {
+        // the residual of the projected, clipped state; either above the
+        // tolerance (or non-finite) flags the cell
+        const double rtol_e = (double)a.residual_tol;
 #pragma unroll
-      for (int k0 = 0; k0 < KP; k0 += WB) {
-        double y0[WB];
-#pragma unroll
-        for (int t = 0; t < WB; ++t)
-          y0[t] = (a.RR && k0 + t < K) ? a.Y[(int64_t)(k0 + t) * a.ld + i] : 0.0;
-#pragma unroll
-        for (int t = 0; t < WB; ++t) {
-          const int k = k0 + t;
-          if (k < K) {
-            if (a.RR) a.RR[(int64_t)k * a.ld + i] = sc * (yn[k] - y0[t]);
-            a.Y[(int64_t)k * a.ld + i] = yn[k];
-          }
-        }
+        for (int e = 0; e < EP; ++e)
+          if (e < E) bad = bad || !(fabs(total(e)) <= rtol_e);
+        if (bad) flag |= 2;
       }
-      a.T[i] = T;
+      need = false;
+      if (flag == 0) {
+        double hm[6], tlo = -INFINITY, thi = INFINITY;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) hm[q] = total(EP + q);
+#pragma unroll
+        for (int v = 0; v < POST_WAVES; ++v) {
+          tlo = fmax(tlo, part[v][EP + 6][lane]);
+          thi = fmin(thi, part[v][EP + 7][lane]);
+        }
+        const double c1 = 2.0 * hm[1], c2 = 3.0 * hm[2], c3 = 4.0 * hm[3], c4 = 5.0 * hm[4];
+        hm[5] -= h0;
+        for (; it < 20; ++it) {
+          if (!(T > tlo && T <= thi)) {
+            need = isfinite(T);
+            break;
+          }
+          const double dh =
+              hm[5] + T * (hm[0] + T * (hm[1] + T * (hm[2] + T * (hm[3] + T * hm[4]))));
+          const double cp = hm[0] + T * (c1 + T * (c2 + T * (c3 + T * c4)));
+          const double dT = dh * rcp_f64(cp);
+          T -= dT;
+          if (!isfinite(T) || fabs(dT) < 1e-9 * T) break;
+        }
+        T_s[lane] = T;
+      }
+    }
+    if (!__syncthreads_or(w == 0 && need)) break;
+  }
+  if (w == 0) {
+    if (flag == 0 && (!isfinite(T) || !(T > 0.0))) flag |= 2;
+    go_s[lane] = flag == 0;
+    sc_s[lane] = rho0 / a.dt;
+    if (live) {
+      if (flag == 0) a.T[i] = T;
+      if (a.flags) a.flags[i] = flag;
+      if (flag != 0) {
+        const unsigned long long slot = atomicAdd(a.fb_count, 1ull);
+        if (a.fb_index) a.fb_index[slot] = (int32_t)(a.index_base + i);
+      }
     }
   }
-  if (flag != 0 && a.RR) {
+  __syncthreads();
+  const bool go = go_s[lane];
+  const double sc = sc_s[lane];
+  if (!live) return;
+  int64_t ld = a.ld;  // the rows' addresses again, rather than kept from the loads
+  asm volatile("" : "+s"(ld));
 #pragma unroll
-    for (int k = 0; k < KP; ++k)
-      if (k < K) a.RR[(int64_t)k * a.ld + i] = 0.0;
-  }
-  if (a.flags) a.flags[i] = flag;
-  if (flag != 0) {
-    const unsigned long long slot = atomicAdd(a.fb_count, 1ull);
-    if (a.fb_index) a.fb_index[slot] = (int32_t)(a.index_base + i);
+  for (int j = 0; j < J; ++j) {
+    const int k = kw + j;
+    if (k >= K) continue;
+    if (a.RR) a.RR[(int64_t)k * ld + i] = go ? sc * (y[j] - y0[j]) : 0.0;
+    if (go) a.Y[(int64_t)k * ld + i] = y[j];
   }
 }
 
@@ -2708,15 +2835,15 @@ chem_status post(const chem::DevMech &M, const PostArgs &a, hipStream_t s) {
     return CHEM_EUNSUPPORTED;
   }
   chem::ProfScope prof("ann_post", s);
-  const dim3 grid(nblk(a.n, 128)), block(128);
+  const dim3 grid(nblk(a.n, POST_CELLS)), block(POST_WAVES * 64);
   if (M.K <= 16 && M.E <= 4)
-    hipLaunchKernelGGL((k_post<16, 4>), grid, block, 0, s, M, a);
+    hipLaunchKernelGGL((k_post<4, 4>), grid, block, 0, s, M, a);
   else if (M.K <= 32 && M.E <= 4)
-    hipLaunchKernelGGL((k_post<32, 4>), grid, block, 0, s, M, a);
+    hipLaunchKernelGGL((k_post<8, 4>), grid, block, 0, s, M, a);
   else if (M.K <= 32)
-    hipLaunchKernelGGL((k_post<32, EMAX>), grid, block, 0, s, M, a);
+    hipLaunchKernelGGL((k_post<8, EMAX>), grid, block, 0, s, M, a);
   else
-    hipLaunchKernelGGL((k_post<64, EMAX>), grid, block, 0, s, M, a);
+    hipLaunchKernelGGL((k_post<16, EMAX>), grid, block, 0, s, M, a);
   CHEM_HIP(hipGetLastError());
   return CHEM_OK;
 }

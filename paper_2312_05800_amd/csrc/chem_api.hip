@@ -314,6 +314,17 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
     tp[k].Tmid = Tmid[k];
     tp[k].invW = invW[k];
   }
+  std::vector<PostPack> pp(KMAX + 1);
+  for (int k = 0; k <= KMAX; ++k) {
+    pp[k] = PostPack{};
+    pp[k].Tmid = INFINITY;
+    if (k >= K) continue;
+    memcpy(pp[k].lo, nh.data() + 7 * k, 6 * 8);
+    memcpy(pp[k].hi, nhh.data() + 7 * k, 6 * 8);
+    pp[k].invW = invW[k];
+    pp[k].Tmid = Tmid[k];
+    for (int e = 0; e < E && e < 10; ++e) pp[k].el[e] = Mel[e * K + k];
+  }
   RxnPack null{{K, K, K, K}, {0, 0, 0, 0}, {0, 0, 0, 0}, -1e9, 0.0, 0.0, 0.0};
   std::vector<RxnPack> rx((R + RATES_PER_WAVE - 1) / RATES_PER_WAVE * RATES_PER_WAVE, null);
   for (int r = 0; r < R; ++r) {
@@ -374,8 +385,7 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
 
   Packer pk;
   size_t oW = pk.add(W.data(), K * 8), oiW = pk.add(invW.data(), K * 8),
-         oTm = pk.add(Tmid.data(), K * 8), olo = pk.add(lo.data(), 7 * K * 8),
-         ohi = pk.add(hi.data(), 7 * K * 8), oM = pk.add(Mel.data(), Mel.size() * 8),
+         oTm = pk.add(Tmid.data(), K * 8), oM = pk.add(Mel.data(), Mel.size() * 8),
          onh = pk.add(nh.data(), nh.size() * 8), onhh = pk.add(nhh.data(), nhh.size() * 8),
          ons = pk.add(ns.data(), ns.size() * 8), onsh = pk.add(nsh.data(), nsh.size() * 8),
          ocpT = pk.add(cpT.data(), cpT.size() * 8), ohT = pk.add(hT.data(), hT.size() * 8),
@@ -386,6 +396,7 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
                oxab = pk.add(xab.data(), xab.size() * sizeof(double2)),
                oxeb = pk.add(xeb.data(), xeb.size() * sizeof(double2));
   const size_t otp = pk.add(tp.data(), tp.size() * sizeof(SpPack));
+  const size_t opp = pk.add(pp.data(), pp.size() * sizeof(PostPack));
   const size_t orx = pk.add(rx.data(), rx.size() * sizeof(RxnPack));
   const size_t orst = pk.add(rs_start.data(), rs_start.size() * sizeof(int)),
                orsr = pk.add(rs_row.data(), rs_row.size() * sizeof(int)),
@@ -427,8 +438,6 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
   dm.W = (const double *)(base + oW);
   dm.invW = (const double *)(base + oiW);
   dm.Tmid = (const double *)(base + oTm);
-  dm.nasa_lo = (const double *)(base + olo);
-  dm.nasa_hi = (const double *)(base + ohi);
   dm.Mel = (const double *)(base + oM);
   dm.nasa_h = (const double *)(base + onh);
   dm.nasa_hh = (const double *)(base + onhh);
@@ -443,6 +452,7 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
   dm.xab = (const double2 *)(base + oxab);
   dm.xeb = (const double2 *)(base + oxeb);
   dm.tp = (const SpPack *)(base + otp);
+  dm.pp = (const PostPack *)(base + opp);
   dm.rx = (const RxnPack *)(base + orx);
   dm.rs_start = (const int *)(base + orst);
   dm.rs_row = (const int *)(base + orsr);

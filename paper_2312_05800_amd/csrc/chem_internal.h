@@ -16,13 +16,12 @@ constexpr int KMAX = 63;  // species limit: n = K + 1 <= 64 lanes per cell
 // Device-resident mechanism constants (one allocation, see chem_api.hip).
 struct RxnPack;
 struct SpPack;
+struct PostPack;
 struct DevMech {
   int K, R, E, n;
   const double *W;        // [K] kg/mol
   const double *invW;     // [K]
   const double *Tmid;     // [K]
-  const double *nasa_lo;  // [K][7]
-  const double *nasa_hi;  // [K][7]
   const double *Mel;      // [E][K] element mass per unit mass fraction, A_e a_ek / W_k
   const double *nasa_h;   // [K][7] low-range h/RT polynomial: a1, a2/2, a3/3, a4/4, a5/5, a6, 0
   const double *nasa_hh;  // [K][7] same for the high range
@@ -50,6 +49,7 @@ struct DevMech {
   const int *rs_start;
   const int *rs_row;
   const double *rs_coef;
+  const PostPack *pp;  // [KMAX + 1], the entries past K null species
 };
 constexpr int RATES_CHUNK = 32, RATES_PER_WAVE = 4;
 
@@ -68,6 +68,15 @@ struct RxnPack {
 struct SpPack {
   double c[2][17];
   double Tmid, invW;
+};
+
+// What the surrogate's post-processing reads of a species: h/RT of the low range, 1/W and the
+// range limit; h/RT of the high range and two elements' mass per unit mass
+// fraction; the other elements'.  Three cache lines; a null species is all zeros
+// with Tmid = infinity.
+struct PostPack {
+  double lo[6], invW, Tmid;
+  double hi[6], el[10];
 };
 
 // A constant kept in scalar registers: the FMA takes it as an operand
