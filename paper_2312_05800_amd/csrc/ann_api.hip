@@ -1423,11 +1423,14 @@ TrainProduct train_product(const ann_model *m, int64_t B, int p, int S) {
     g.ldz = P.doutp;
     g.Cb = m->tGb[l - 1];
     g.ldcb = P.doutp;
+    // in FP32 for colsum(), or already summed over its row tiles
     g.Cf = m->tGf[l - 1];
     g.ldcf = P.doutp;
+    g.colsum = (double *)m->tGf[l - 1];
     g.gA = (long)B * L.doutp;
     g.gB = (long)layer_elems(L);
     g.gz = g.gcb = g.gcf = (long)B * P.doutp;
+    g.gcol = (long)ann::gemm_col_parts(g) * P.doutp;
     t.AK = true;
     t.BK = false;
     t.epi = ann::EPI_GELUGRAD;
@@ -1443,12 +1446,17 @@ int train_split(const ann_model *m, int64_t B, int l) {
   return wgrad_splits(m->L[l].doutp, m->L[l].dinp, B, m->G);
 }
 
-chem_status run_product(const ann_model *m, int64_t B, int p, int S, hipStream_t s) {
+TrainProduct tuned_product(const ann_model *m, int64_t B, int p, int S) {
   TrainProduct t = train_product(m, B, p, S);
   if (m->tt_B == B) {
     t.g.tile = m->tt_tile[p];
     t.g.bk = m->tt_bk[p];
   }
+  return t;
+}
+
+chem_status run_product(const ann_model *m, int64_t B, int p, int S, hipStream_t s) {
+  const TrainProduct t = tuned_product(m, B, p, S);
   return ann::gemm(t.g, t.AK, t.BK, t.epi, s, t.label);
 }
 
@@ -1547,9 +1555,12 @@ extern "C" chem_status ann_train_step(ann_model *m, const chem_mech *mech, chem_
     if (S > 1 && (st = ann::sum_splits((long)G * wn, S, m->wg_part, (long)G * wn, m->gW[l], s)) !=
                      CHEM_OK)
       return st;
-    if ((st = ann::colsum(B, L.doutp, m->tGf[l], L.doutp, m->gb[l], m->col_part, s, G,
-                          (long)B * L.doutp, L.doutp)) != CHEM_OK)
-      return st;
+    // the bias gradient: the column sums that the data gradient left, or its own
+    const int P = l < 3 ? ann::gemm_col_parts(tuned_product(m, B, 8 + l, 1).g) : 0;
+    st = P > 0 ? ann::colsum_parts(L.doutp, P, (const double *)m->tGf[l], m->gb[l], s, G, L.doutp)
+               : ann::colsum(B, L.doutp, m->tGf[l], L.doutp, m->gb[l], m->col_part, s, G,
+                             (long)B * L.doutp, L.doutp);
+    if (st != CHEM_OK) return st;
     if (l > 0 && (st = run_product(m, B, 7 + l, 1, s)) != CHEM_OK) return st;
   }
   if (opts->lr > 0.0f) {

@@ -64,10 +64,14 @@ struct GemmArgs {
   // (E4M3), so the rows of one K-step are contiguous; ld is then the stride
   // between K-blocks.  Only the direct-to-LDS kernels accept it.
   int tiled;
+  // EPI_GELUGRAD on the direct-to-LDS path: FP64 sums of the output's columns over each row
+  // tile, [gemm_col_parts() row tiles][N] (group z at + z gcol)
+  double *colsum;
+  long gcol;
   // grouped product (the networks of a per-species ensemble, one per
   // blockIdx.z): group z reads A + z gA, B + z gB, bias + z gbias and writes
   // Cb + z gcb, Cf + z gcf, Z + z gz (element strides; 0 = shared operand).
-  // Only the generic tiling (training products) accepts groups > 1.
+  // The training products' tilings accept groups > 1.
   int groups;
   long gA, gB, gbias, gcb, gcf, gz;
   // tiling of the generic kernel chosen by the autotuner: tile 0 = the
@@ -84,6 +88,9 @@ enum { TILED_A = 1, TILED_B = 2, TILED_C = 4 };
 // row-major (else [K][N]).
 chem_status gemm(const GemmArgs &g, bool AK, bool BK, int epi, hipStream_t s,
                  const char *label);
+// Row tiles whose column sums gemm() writes to colsum for this data gradient (0: it writes
+// the FP32 output to Cf instead).
+int gemm_col_parts(const GemmArgs &g);
 // Whether gemm() can run this forward layer with EPI_GELU_NEXT (the output
 // layer fused into its epilogue).
 bool gemm_fuses_next(const GemmArgs &g);
@@ -184,6 +191,9 @@ chem_status phys_grad(const PhysArgs &a, const chem::DevMech &M, double *part, f
 // With groups > 1, group z sums X + z gx into out + z gout (part: groups
 // times as many doubles).
 constexpr int COLSUM_PARTS = 64;
+// its last step: out[j] = sum of part[q][j] over q < P (FP64, [groups][P][N])
+chem_status colsum_parts(int N, int P, const double *part, float *out, hipStream_t s,
+                         int groups = 1, long gout = 0);
 chem_status colsum(int64_t M, int N, const float *X, long ldx, float *out, double *part,
                    hipStream_t s, int groups = 1, long gx = 0, long gout = 0);
 // Per-species ensemble: member g's output is column 0 of U + g gu (row

@@ -349,30 +349,63 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 // valid row (their results are never stored).  K must be a multiple of 32.
 // Fragment: lane l holds row l % 16 and the 8 K values 8 (l / 16) ..; result:
 // lane l holds cell l % 16 and features 4 (l / 16) .. + 3 of its tile.
-template <int WM, int TM16, int TN16, int EPI, int STAGES>
-__global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
-  constexpr int BK = 32;
-  constexpr int BM = WM * TM16 * 16, BN = TN16 * 16, ROWS = BM + BN;
-  constexpr int NI = ROWS / 16;
-  constexpr int NPW = (NI + WM - 1) / WM;
-  constexpr int NMIN = NI / WM;
+//
+// The backward products read operands that lie the other way, A [K][M] (AT) or
+// B [K][N] (BT): their stage keeps the 32 K-rows as they are in memory, 16-byte
+// chunks padded to 2 mod 4 a row (so that the 32-byte pieces of the four rows that
+// 16 lanes read together are on distinct banks), and ds_read_b64_tr_b16 hands each
+// lane four K values of its column.  Same fragments, same bits.  The waves
+// split the tile WM x WN: with both sides split a wave reads fewer fragments per
+// MFMA (64 x 80 of a 128 x 160 tile: 9 per 20; 32 x 80 of a 128 x 80 one 7 per 10).
+// ksplit > 1 cuts the K-steps, blockIdx.z is the member of a grouped product.
+__host__ __device__ constexpr int ring_chunks(int cols) {  // of 16 bytes in a K-row
+  return cols / 8 + (cols / 8 % 4 == 2 ? 0 : 2);
+}
+template <int WM, int TM16, int TN16, int EPI, int STAGES, int WN = 1, bool AT = false,
+          bool BT = false>
+__global__ __launch_bounds__(WM * WN * 64) void k_gemm_dma16(GemmArgs g) {
+  if (g.groups > 1) {
+    const long z = blockIdx.z;  // this block's member of a grouped product
+    g.A += z * g.gA;
+    g.B += z * g.gB;
+    if (g.bias) g.bias += z * g.gbias;
+    if (g.Cb) g.Cb += z * g.gcb;
+    if (g.Cf) g.Cf += z * g.gcf;
+    if (g.Z) g.Z += z * g.gz;
+    if (g.colsum) g.colsum += z * g.gcol;
+  }
+  constexpr int BK = 32, NW = WM * WN;
+  constexpr int BM = WM * TM16 * 16, BN = WN * TN16 * 16;
+  constexpr int CA = ring_chunks(BM), CB = ring_chunks(BN);
+  static_assert((!AT || CA % 4 == 2) && (!BT || CB % 4 == 2), "conflict-free K-rows");
+  // direct loads per stage, of 64 chunks (16 rows of a K-contiguous operand) each
+  constexpr int NA = AT ? CA / 2 : BM / 16, NB = BT ? CB / 2 : BN / 16, NI = NA + NB;
+  constexpr int NPW = (NI + NW - 1) / NW;
+  constexpr int NMIN = NI / NW;
   static_assert(BM % 16 == 0 && BN % 16 == 0, "tile rows must be multiples of 16");
   static_assert(STAGES >= 1 && (STAGES - 1) * NPW < 64,
                 "a ring (or one stage for a single K-step) whose loads vmcnt can count");
-  __shared__ __attribute__((aligned(1024))) u16 S[STAGES * ROWS * BK];
+  __shared__ __attribute__((aligned(1024))) u16 S[STAGES * NI * 512];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % WM, wn = wave / WM;
   const int ntn = (g.N + BN - 1) / BN;
   const int ntm = (g.M + BM - 1) / BM;
-  const int total = ntn * ntm;
+  const int ns = g.ksplit > 1 ? g.ksplit : 1;
+  // an XCD takes consecutive tiles, and those of one range of K before the next: what
+  // its blocks share stays in its L2
+  const int total = ntn * ntm * ns;
   const int per_xcd = (total + 7) / 8;
-  const int logical = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  if (logical >= total) return;
+  const int item = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  if (item >= total) return;
+  // (quotients come in vector registers, the loads' bases are scalars)
+  const int split = ns > 1 ? __builtin_amdgcn_readfirstlane(item / (ntn * ntm)) : 0;
+  const int logical = item - split * (ntn * ntm);
   const long m0 = (long)(logical / ntn) * BM, n0 = (long)(logical % ntn) * BN;
   // the tile's bias in LDS (published by the barrier below) so that the
   // epilogue does not wait on global loads per feature tile
   __shared__ __attribute__((aligned(16))) float bias_s[BN];
-  for (int c = tid; c < BN / 4; c += WM * 64) {
+  for (int c = tid; c < BN / 4; c += NW * 64) {
     float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (g.bias && n0 + 4 * c < g.N) v = *(const float4 *)(g.bias + n0 + 4 * c);
     *(float4 *)&bias_s[4 * c] = v;
@@ -382,26 +415,39 @@ __global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
   // per-lane byte offsets of this wave's DMA rows within the tile (rows past
   // M or N clamped to the last valid one) and the wave-uniform tile bases;
   // a K-blocked operand keeps the tile's rows of one K-step contiguous
+  const int nk_all = g.K / BK;
+  const int kt0 = ns > 1 ? __builtin_amdgcn_readfirstlane(nk_all * split / ns) : 0;
+  const int nk =
+      ns > 1 ? __builtin_amdgcn_readfirstlane(nk_all * (split + 1) / ns) - kt0 : nk_all;
   const bool ta = g.tiled & TILED_A, tb = g.tiled & TILED_B;
-  const u16 *const sA = g.A + m0 * (ta ? BK : g.lda);
-  const u16 *const sB = g.B + n0 * (tb ? BK : g.ldb);
-  const long kA = ta ? g.lda : BK, kB = tb ? g.ldb : BK;  // step between K-blocks
+  // step between K-blocks
+  const long kA = AT ? BK * g.lda : ta ? g.lda : BK, kB = BT ? BK * g.ldb : tb ? g.ldb : BK;
+  const u16 *const sA = g.A + m0 * (AT ? 1 : ta ? BK : g.lda) + kt0 * kA;
+  const u16 *const sB = g.B + n0 * (BT ? 1 : tb ? BK : g.ldb) + kt0 * kB;
   unsigned voff[NPW];
 #pragma unroll
   for (int i = 0; i < NPW; ++i) {
-    const int gi = i * WM + wave;
-    const int row = gi * 16 + (lane >> 2);
-    const int chunk = (lane & 3) ^ swz(row);
+    const int gi = i * NW + wave;
     unsigned o = 0;
-    if (gi < NI) {
-      if (row < BM) {
-        const long m = m0 + row < g.M ? m0 + row : g.M - 1;
-        o = (unsigned)(((m - m0) * (ta ? BK : g.lda) + chunk * 8) * 2);
-      } else {
-        const long n = n0 + (row - BM) < g.N ? n0 + (row - BM) : g.N - 1;
-        o = (unsigned)(((n - n0) * (tb ? BK : g.ldb) + chunk * 8) * 2);
-      }
-    }
+    // K-rows: chunk q of the stage; a column past the operand's (or the padding)
+    // reads its last valid one
+    auto krows = [&](int q, int C, int cols, long c0, long n, long ld) {
+      const int r = q / C, c = (q % C) * 8;
+      const long col = c0 + c + 8 <= n ? c : n - 8 - c0;
+      return (unsigned)((r * ld + (c < cols ? col : 0)) * 2);
+    };
+    auto rows = [&](int q, long r0, long n, long ld) {
+      const int row = q * 16 + (lane >> 2);
+      const int chunk = (lane & 3) ^ swz(row);
+      const long r = r0 + row < n ? row : n - 1 - r0;
+      return (unsigned)((r * ld + chunk * 8) * 2);
+    };
+    if (gi < NA)
+      o = AT ? krows(gi * 64 + lane, CA, BM, m0, g.M, g.lda)
+             : rows(gi, m0, g.M, ta ? BK : g.lda);
+    else if (gi < NI)
+      o = BT ? krows((gi - NA) * 64 + lane, CB, BN, n0, g.N, g.ldb)
+             : rows(gi - NA, n0, g.N, tb ? BK : g.ldb);
     voff[i] = o;
   }
   const unsigned lds0 =
@@ -409,10 +455,10 @@ __global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
   auto issue = [&](int stage, int kt) {
 #pragma unroll
     for (int i = 0; i < NPW; ++i) {
-      const int gi = i * WM + wave;
+      const int gi = i * NW + wave;
       if (gi < NI)
-        lds_dma16s(gi * 16 < BM ? sA + kt * kA : sB + kt * kB, voff[i],
-                   lds0 + (unsigned)((stage * ROWS + gi * 16) * BK * 2));
+        lds_dma16s(gi < NA ? sA + kt * kA : sB + kt * kB, voff[i],
+                   lds0 + (unsigned)((stage * NI + gi) * 1024));
     }
   };
 
@@ -422,8 +468,22 @@ __global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < TN16; ++j) acc[i][j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
 
-  const int nk = g.K / BK;
   const int cc = lane >> 4;
+  // the 8 K values of row (column of a K-row operand) t 16 + lane % 16 of part P
+  // (C chunks a K-row) of a stage
+  auto frag = [&](const u16 *P, int t, bool T, int C) __attribute__((always_inline)) -> bf16x8 {
+    if (T) {
+      typedef __attribute__((address_space(3))) s16x4 ls16x4;
+      const u16 *const q = P + (8 * cc + ((lane & 15) >> 2)) * C * 8 + t * 16 + 4 * (lane & 3);
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ls16x4 *)q);
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ls16x4 *)(q + 4 * C * 8));
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5,
+                                                                       6, 7));
+    }
+    const int row = t * 16 + (lane & 15);
+    return *(const bf16x8 *)&P[row * BK + ((cc ^ swz(row)) * 8)];
+  };
   // STAGES - 1 K-steps in flight ahead of the one being multiplied (a single
   // stage serves layers with one K-step only; two stages leave the CU room
   // for a second block, whose work covers this one's waits)
@@ -445,17 +505,13 @@ __global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
     // which every wave finished before the barrier above
     if (STAGES > 1 && kt + STAGES - 1 < nk)
       issue((kt + STAGES - 1) % STAGES, kt + STAGES - 1);
-    const u16 *T = S + (kt % STAGES) * ROWS * BK;
+    const u16 *TA = S + (kt % STAGES) * NI * 512, *TB = TA + NA * 512;
     bf16x8 x[TM16];
 #pragma unroll
-    for (int i = 0; i < TM16; ++i) {
-      const int row = wave * TM16 * 16 + i * 16 + (lane & 15);
-      x[i] = *(const bf16x8 *)&T[row * BK + ((cc ^ swz(row)) * 8)];
-    }
+    for (int i = 0; i < TM16; ++i) x[i] = frag(TA, wm * TM16 + i, AT, CA);
 #pragma unroll
     for (int j = 0; j < TN16; ++j) {
-      const int row = BM + j * 16 + (lane & 15);
-      const bf16x8 w = *(const bf16x8 *)&T[row * BK + ((cc ^ swz(row)) * 8)];
+      const bf16x8 w = frag(TB, wn * TN16 + j, BT, CB);
 #pragma unroll
       for (int i = 0; i < TM16; ++i)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x[i], acc[i][j], 0, 0, 0);
@@ -532,15 +588,67 @@ __global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
   bool live[TM16];
 #pragma unroll
   for (int i = 0; i < TM16; ++i) {
-    const long row = m0 + wave * TM16 * 16 + i * 16 + (lane & 15);
+    const long row = m0 + wm * TM16 * 16 + i * 16 + (lane & 15);
     live[i] = row < g.M;
     rb[i] = row;
   }
+  if constexpr (EPI == EPI_GELUGRAD) {
+    // d = v GELU'(z), stored in BF16 and summed over the tile's cells (the bias
+    // gradient's partial sums): in FP64 over the lane's cells, then, through the
+    // idle ring, over the lanes'.
+    static_assert(WM * 16 * BN * 8 <= (int)sizeof(S), "the column sums fit the ring");
+    float4 z[TN16][TM16];
+#pragma unroll
+    for (int j = 0; j < TN16; ++j) {
+      const long cj = n0 + (wn * TN16 + j) * 16;
+#pragma unroll
+      for (int i = 0; i < TM16; ++i)
+        if (cj < g.N) z[j][i] = *(const float4 *)(g.Z + (live[i] ? rb[i] : m0) * g.ldz + hf + cj);
+    }
+    asm volatile("s_barrier" : : : "memory");  // every wave is done with the ring
+    double *const cs = (double *)S;            // [WM 16][BN]
+#pragma unroll
+    for (int j = 0; j < TN16; ++j) {
+      const int c = (wn * TN16 + j) * 16 + hf;
+      const long cj = n0 + (wn * TN16 + j) * 16;
+      double sum[4] = {0.0, 0.0, 0.0, 0.0};
+      if (cj < g.N) {
+#pragma unroll
+        for (int i = 0; i < TM16; ++i) {
+          if (!live[i]) continue;
+          const float4 d =
+              make_float4(acc[i][j][0] * gelu_grad(z[j][i].x), acc[i][j][1] * gelu_grad(z[j][i].y),
+                          acc[i][j][2] * gelu_grad(z[j][i].z), acc[i][j][3] * gelu_grad(z[j][i].w));
+          const bf16x2 lo = __builtin_convertvector((f32x2){d.x, d.y}, bf16x2);
+          const bf16x2 hi = __builtin_convertvector((f32x2){d.z, d.w}, bf16x2);
+          *(uint2 *)(g.Cb + (rb[i] * g.ldcb + hf) + cj) =
+              make_uint2(__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi));
+          sum[0] += (double)d.x;
+          sum[1] += (double)d.y;
+          sum[2] += (double)d.z;
+          sum[3] += (double)d.w;
+        }
+      }
+      double *const o = cs + (wm * 16 + (lane & 15)) * BN + c;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) o[t] = sum[t];
+    }
+    __syncthreads();
+    for (int c = tid; c < BN; c += NW * 64) {
+      if (n0 + c >= g.N) continue;
+      double t = 0.0;
+#pragma unroll
+      for (int r = 0; r < WM * 16; ++r) t += cs[r * BN + c];
+      g.colsum[(m0 / BM) * (long)g.N + n0 + c] = t;
+    }
+    return;
+  }
+  float *const Cf = EPI == EPI_F32 && g.ksplit > 1 ? g.Cf + split * g.split_stride : g.Cf;
 #pragma unroll
   for (int j = 0; j < TN16; ++j) {
-    const long cj = n0 + j * 16;  // uniform
+    const long cj = n0 + (wn * TN16 + j) * 16;  // uniform
     if (cj >= g.N) break;
-    const float4 b = *(const float4 *)&bias_s[j * 16 + hf];
+    const float4 b = *(const float4 *)&bias_s[(wn * TN16 + j) * 16 + hf];
 #pragma unroll
     for (int i = 0; i < TM16; ++i) {
       if (!live[i]) continue;
@@ -548,7 +656,7 @@ __global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
       const float4 v = make_float4(acc[i][j][0] + b.x, acc[i][j][1] + b.y, acc[i][j][2] + b.z,
                                    acc[i][j][3] + b.w);
       if (EPI == EPI_F32) {
-        *(float4 *)(g.Cf + row * g.ldcf + hf + cj) = v;
+        *(float4 *)(Cf + row * g.ldcf + hf + cj) = v;
       } else if (EPI == EPI_GELU) {
         if (g.Z) *(float4 *)(g.Z + row * g.ldz + hf + cj) = v;
         const float4 h = make_float4(gelu(v.x), gelu(v.y), gelu(v.z), gelu(v.w));
@@ -573,27 +681,27 @@ __global__ __launch_bounds__(WM * 64) void k_gemm_dma16(GemmArgs g) {
   }
 }
 
-template <int WM, int TM16, int TN16, int STAGES = 3>
+template <int WM, int TM16, int TN16, int STAGES = 3, int WN = 1>
 chem_status gemm_dma16_cfg(const GemmArgs &g, int epi, hipStream_t s) {
-  constexpr int BM = WM * TM16 * 16, BN = TN16 * 16;
+  constexpr int BM = WM * TM16 * 16, BN = WN * TN16 * 16;
   if (STAGES == 1 && g.K != 32) {
     chem::set_error("gemm: the single-stage tiling needs K = 32");
     return CHEM_EUNSUPPORTED;
   }
   const long total = (long)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  dim3 grid((unsigned)(((total + 7) / 8) * 8));
-  dim3 block(WM * 64);
+  dim3 grid((unsigned)(((total + 7) / 8) * 8), 1, g.groups > 1 ? g.groups : 1);
+  dim3 block(WM * WN * 64);
   if (epi == EPI_GELU)
-    hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_GELU, STAGES>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_GELU, STAGES, WN>), grid, block, 0, s, g);
   else if (epi == EPI_F32)
-    hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_F32, STAGES>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_F32, STAGES, WN>), grid, block, 0, s, g);
   else if (epi == EPI_GELU_Q8)
-    hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_GELU_Q8, STAGES>), grid, block, 0, s,
+    hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_GELU_Q8, STAGES, WN>), grid, block, 0, s,
                        g);
-  else if (TN16 == 26 && epi == EPI_GELU_NEXT && g.N <= BN && g.N2 == 32 &&
+  else if (TN16 == 26 && WN == 1 && epi == EPI_GELU_NEXT && g.N <= BN && g.N2 == 32 &&
            g.N2 * (BN + 4) <= STAGES * (BM + BN) * 32 && g.ldcf % 4 == 0) {
     // only the 416-feature tiles hold all features of their cells
-    if constexpr (TN16 == 26)
+    if constexpr (TN16 == 26 && WN == 1)
       hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_GELU_NEXT, STAGES>), grid, block, 0, s,
                          g);
   } else {
@@ -2503,26 +2611,98 @@ bool dma16_ok(const GemmArgs &g) {
 }  // namespace
 
 namespace {
-// Forward layers below the large tiles' launch sizes (K-contiguous or K-blocked
-// operands).  These launches are bound by the latency of their K-steps, so the
-// ring is deep (up to five K-steps in flight, where the register-staged k_gemm
-// prefetches one), and the tile is the largest that still gives the CUs blocks:
-// measured at 64, 500, 2003, 8000, 32000 cells, second layer (K = 1600, N = 800) 13.6,
-// 14.8, 22, 32, 92 us; third (K = 800, N = 416) 9.5, 9.2, 10.7, 16, 34 us, where k_gemm took
-// 28.5, 12, 13, 21, 56 us; output layer (K = 416, N = 32) 6.8 us at all of them, 10 to 13 before.
-// The 64 x 16 tiles at 2003 cells took 30 us for the second layer, the 128 x 80 ones 22 us
-// at 64 cells.  The MFMA's sums do not depend on the tile: same bits.
+long tiles(const GemmArgs &g, int bm, int bn) {
+  return (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * (g.groups > 1 ? g.groups : 1);
+}
+
+// Products below the large tiles' launch sizes are bound by the latency of their
+// K-steps and by what their blocks read of each other's rows: 64 x 64 tiles as long as
+// all of them are resident (about four to a CU), larger ones above; below 200
+// tiles the rings are deep (five K-steps in flight) and the tiles narrower.  The
+// MFMA's sums do not depend on the tile.  Second layer (K = 1600, N = 800, K-blocked)
+// at 64, 512, 2048, 4096, 8192, 24576 cells in 64 x 16, 64 x 64, 96 x 160, 256 x 160 tiles:
+// 10.8, 12.5, -, - | 11.7, 12.8, -, - | 29.6, 15.8, 25.8, - | -, 24.4, 27.7, - |
+// -, 40.8, 34.7, - | -, -, 91, 84 us.
+enum RingTile { RT_64x16, RT_64x32, RT_64x64, RT_96x160 };
+RingTile ring_tile(const GemmArgs &g) {
+  const long t = tiles(g, 64, 64);
+  if (t >= 200) return t <= 1000 ? RT_64x64 : RT_96x160;
+  return tiles(g, 64, 32) >= 200 ? RT_64x32 : RT_64x16;
+}
+
+// Forward layers (K-contiguous or K-blocked operands).  One K-step (the first layer):
+// a store of its pre-activations, 64 x 80 tiles; an output layer has one column of tiles
+// (6.8 us at 64 to 8000 cells, 10 to 13 in k_gemm's).
 chem_status gemm_dma16_small(const GemmArgs &g, int epi, hipStream_t s) {
-  auto blocks = [&](int bm, int bn) { return (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
   if (g.N <= 32) return gemm_dma16_cfg<4, 1, 2, 6>(g, epi, s);
-  if (g.N % 208 == 0 && blocks(256, 208) >= 250) return gemm_dma16_cfg<8, 2, 13>(g, epi, s);
-  if (g.N % 160 == 0 && blocks(256, 160) >= 500) return gemm_dma16_cfg<8, 2, 10>(g, epi, s);
-  if (blocks(128, 80) >= 400) return gemm_dma16_cfg<4, 2, 5, 4>(g, epi, s);
-  if (blocks(64, 80) >= 256) return gemm_dma16_cfg<4, 1, 5, 5>(g, epi, s);
-  if (blocks(64, 32) >= 200) return gemm_dma16_cfg<4, 1, 2, 6>(g, epi, s);
-  return gemm_dma16_cfg<4, 1, 1, 6>(g, epi, s);
+  if (g.K == 32 && tiles(g, 64, 80) >= 256) return gemm_dma16_cfg<4, 1, 5, 5>(g, epi, s);
+  if (g.N % 208 == 0 && tiles(g, 256, 208) >= 250) return gemm_dma16_cfg<8, 2, 13>(g, epi, s);
+  if (g.N % 160 == 0 && tiles(g, 256, 160) >= 480) return gemm_dma16_cfg<8, 2, 10>(g, epi, s);
+  switch (ring_tile(g)) {
+    case RT_96x160: return gemm_dma16_cfg<2, 3, 5, 3, 2>(g, epi, s);
+    case RT_64x64: return gemm_dma16_cfg<2, 2, 2, 4, 2>(g, epi, s);
+    case RT_64x32: return gemm_dma16_cfg<4, 1, 2, 6>(g, epi, s);
+    default: return gemm_dma16_cfg<4, 1, 1, 6>(g, epi, s);
+  }
+}
+
+// Data gradients through GELU': A [M][K], B [K][N].  Second layer's (N = 1600, K = 800) and
+// third's (N = 800, K = 416) at batch 2048: 20, 9 us (k_gemm 39, 30); 8192: 55, 23 (88, 37).
+template <int WM, int TM16, int TN16, int STAGES, int WN>
+chem_status ring_dgrad_cfg(const GemmArgs &g, hipStream_t s) {
+  const long t = (long)((g.M + WM * TM16 * 16 - 1) / (WM * TM16 * 16)) *
+                 ((g.N + WN * TN16 * 16 - 1) / (WN * TN16 * 16));
+  hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_GELUGRAD, STAGES, WN, false, true>),
+                     dim3((unsigned)((t + 7) / 8 * 8), 1, g.groups > 1 ? g.groups : 1),
+                     dim3(WM * WN * 64), 0, s, g);
+  CHEM_HIP(hipGetLastError());
+  return CHEM_OK;
+}
+chem_status ring_dgrad(const GemmArgs &g, hipStream_t s) {
+  switch (ring_tile(g)) {
+    case RT_96x160: return ring_dgrad_cfg<2, 3, 5, 3, 2>(g, s);
+    case RT_64x64: return ring_dgrad_cfg<2, 2, 2, 4, 2>(g, s);
+    case RT_64x32: return ring_dgrad_cfg<4, 1, 2, 6, 1>(g, s);
+    default: return ring_dgrad_cfg<4, 1, 1, 6, 1>(g, s);
+  }
+}
+bool ring_dgrad_ok(const GemmArgs &g) {
+  return !g.tile && !g.tiled && g.colsum && g.Cb && dma16_ok(g);
+}
+
+// Weight gradients: A [K][M], B [K][N], K the batch in ksplit ranges (whose partial products
+// sum_splits adds in order, so that the ranges are part of the result).  160 x 160 tiles on
+// two stages (two or three blocks to a CU) stream the fewest bytes per product; where they
+// are too few, or a side is 32, 64 x 64 ones.  M = 800, N = 1600 in 16 ranges of batch 2048, 8192:
+// 24.5, 40 us (k_gemm 36.7, 75.7); 416 x 800 10.3, 16.3 (16.8, 28.8); 1600 x 32 4.7, 7.4 (6.3,
+// 14.1); 32 x 416 3.9, 6.1 (8.9, 16.3).
+template <int WM, int TM16, int TN16, int STAGES, int WN>
+chem_status ring_wgrad_cfg(const GemmArgs &g, hipStream_t s) {
+  const long t = (long)((g.M + WM * TM16 * 16 - 1) / (WM * TM16 * 16)) *
+                 ((g.N + WN * TN16 * 16 - 1) / (WN * TN16 * 16)) * (g.ksplit > 1 ? g.ksplit : 1);
+  hipLaunchKernelGGL((k_gemm_dma16<WM, TM16, TN16, EPI_F32, STAGES, WN, true, true>),
+                     dim3((unsigned)((t + 7) / 8 * 8), 1, g.groups > 1 ? g.groups : 1),
+                     dim3(WM * WN * 64), 0, s, g);
+  CHEM_HIP(hipGetLastError());
+  return CHEM_OK;
+}
+chem_status ring_wgrad(const GemmArgs &g, hipStream_t s) {
+  if (g.M > 64 && g.N > 64 && tiles(g, 160, 160) * (g.ksplit > 1 ? g.ksplit : 1) >= 192)
+    return ring_wgrad_cfg<2, 5, 5, 2, 2>(g, s);
+  return ring_wgrad_cfg<2, 2, 2, 4, 2>(g, s);
+}
+bool ring_wgrad_ok(const GemmArgs &g) {
+  return !g.tile && !g.tiled && !g.bias && g.M % 16 == 0 && g.N % 16 == 0 && g.K % 32 == 0 &&
+         g.lda % 8 == 0 && g.ldb % 8 == 0 && g.ldcf % 4 == 0 && ((uintptr_t)g.A & 15) == 0 &&
+         ((uintptr_t)g.B & 15) == 0 && ((uintptr_t)g.Cf & 15) == 0;
 }
 }  // namespace
+
+int gemm_col_parts(const GemmArgs &g) {
+  if (!ring_dgrad_ok(g)) return 0;
+  const int bm = ring_tile(g) == RT_96x160 ? 96 : 64;
+  return (g.M + bm - 1) / bm;
+}
 
 chem_status feat_l1(const FeatArgs &f, const u16 *W1, const float *b1, int nk, u16 *H, long ldh,
                     hipStream_t s) {
@@ -2557,11 +2737,17 @@ chem_status gemm(const GemmArgs &g, bool AK, bool BK, int epi, hipStream_t s,
     chem::set_error("gemm: split-K needs K a multiple of 32 ksplit, FP32 output, no bias");
     return CHEM_EINVAL;
   }
+  if (!AK && !BK && epi == EPI_F32 && g.groups <= 65535 && ring_wgrad_ok(g))
+    return ring_wgrad(g, s);
+  if (AK && !BK && epi == EPI_GELUGRAD && g.groups <= 65535 && ring_dgrad_ok(g))
+    return ring_dgrad(g, s);
   if (g.groups > 1) {
     if (g.tiled || epi == EPI_GELU_NEXT || epi == EPI_GELU_Q8 || g.groups > 65535) {
-      chem::set_error("gemm: grouped products take the generic tiling only");
+      chem::set_error("gemm: grouped products take the training products' tilings only");
       return CHEM_EUNSUPPORTED;
     }
+    if (AK && BK && epi != EPI_GELUGRAD && !g.tile && dma16_ok(g))
+      return gemm_dma16_small(g, epi, s);
     return gemm_tiled(g, AK, BK, epi, s);
   }
   if (epi == EPI_GELU_NEXT) {
@@ -2795,7 +2981,14 @@ chem_status colsum(int64_t M, int N, const float *X, long ldx, float *out, doubl
   const unsigned G = groups > 1 ? (unsigned)groups : 1u;
   hipLaunchKernelGGL(k_colsum_part, dim3(nblk(N, 64), P, G), dim3(64), 0, s, M, N, X, ldx, part,
                      gx);
-  hipLaunchKernelGGL(k_colsum_fin, dim3(nblk(N, 256), 1, G), dim3(256), 0, s, N, P, part, out,
+  CHEM_HIP(hipGetLastError());
+  return colsum_parts(N, P, part, out, s, groups, gout);
+}
+
+chem_status colsum_parts(int N, int P, const double *part, float *out, hipStream_t s, int groups,
+                         long gout) {
+  const unsigned G = groups > 1 ? (unsigned)groups : 1u;
+  hipLaunchKernelGGL(k_colsum_fin, dim3(nblk(N, 64), 1, G), dim3(64), 0, s, N, P, part, out,
                      gout);
   CHEM_HIP(hipGetLastError());
   return CHEM_OK;
