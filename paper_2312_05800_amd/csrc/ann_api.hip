@@ -76,9 +76,10 @@ struct ann_model {
   float *tZ[3] = {}, *tU = nullptr, *tUt = nullptr, *tGf[ann::NLAYER] = {};
   double *loss_part = nullptr;
   double *phys_part = nullptr;  // [PHYS_PARTS][3] partial sums of the physics terms
-  double *col_part = nullptr;  // [COLSUM_PARTS][max dout] bias-gradient partials
-  float *wg_part = nullptr;    // split-K partial weight gradients
-  size_t wg_cap = 0;           // floats in wg_part
+  double *col_part[ann::NLAYER] = {};  // [G][COLSUM_PARTS][dout] bias-gradient partials
+  // split-K partial weight gradients of each layer, and the most ranges they have room for
+  float *wg_part[ann::NLAYER] = {};
+  int wg_most[ann::NLAYER] = {};
   // FP8 inference of the hidden-to-hidden layers (L2, L3)
   bool fp8_ready = false, use_fp8 = false;
   float sa[3] = {1, 1, 1}, sw[3] = {1, 1, 1};  // per-tensor scales of layers 1, 2
@@ -267,16 +268,21 @@ chem_status grow_train(ann_model *m, int64_t B) {
   }
   const size_t oL = sect(LOSS_PARTS * 8);
   const size_t oP = sect(ann::PHYS_PARTS * 3 * 8);
-  size_t col_n = 0, wg_n = 0;
+  size_t wg_n = 0, oC[ann::NLAYER], wg_off[ann::NLAYER];
+  int wg_most[ann::NLAYER];
   for (int l = 0; l < 4; ++l) {
     const ann::Layer &L = m->L[l];
-    col_n = std::max(col_n, G * ann::COLSUM_PARTS * L.doutp);
+    oC[l] = sect(G * ann::COLSUM_PARTS * L.doutp * 8);
     // the largest split any batch size can select (K = 2^30 divides by all)
     const int S = wgrad_splits(L.doutp, L.dinp, 1L << 30, m->G);
     if (S > 1) wg_n = std::max(wg_n, (size_t)S * G * L.doutp * L.dinp);
   }
-  const size_t oC = sect(col_n * 8);
-  const size_t oW = sect(wg_n * 4);
+  // every layer keeps its partial weight gradients until the step's end
+  for (int l = 0; l < 4; ++l) {
+    const size_t wn = G * layer_elems(m->L[l]);
+    wg_most[l] = (int)std::min<size_t>(16, std::max<size_t>(1, wg_n / wn));
+    wg_off[l] = sect(wg_most[l] > 1 ? wg_most[l] * wn * 4 : 0);
+  }
   if (m->wt.base) (void)hipFree(m->wt.base);
   m->wt.base = nullptr;
   m->wt.cap = 0;
@@ -298,9 +304,11 @@ chem_status grow_train(ann_model *m, int64_t B) {
     m->tGf[l] = (float *)(b + oGf[l]);
   }
   m->loss_part = (double *)(b + oL);
-  m->col_part = (double *)(b + oC);
-  m->wg_part = (float *)(b + oW);
-  m->wg_cap = wg_n;
+  for (int l = 0; l < 4; ++l) {
+    m->col_part[l] = (double *)(b + oC[l]);
+    m->wg_part[l] = (float *)(b + wg_off[l]);
+    m->wg_most[l] = wg_most[l];
+  }
   m->wt.cap = B;
   m->wt.bytes = off;
   return CHEM_OK;
@@ -1400,7 +1408,7 @@ TrainProduct train_product(const ann_model *m, int64_t B, int p, int S) {
     g.B = l > 0 ? m->tH[l - 1] : m->tX;
     g.ldb = L.dinp;
     g.ldcf = L.dinp;
-    g.Cf = S > 1 ? m->wg_part : m->gW[l];
+    g.Cf = S > 1 ? m->wg_part[l] : m->gW[l];
     g.ksplit = S;
     g.split_stride = (long)G * wn;
     g.gA = (long)B * L.doutp;
@@ -1546,55 +1554,46 @@ extern "C" chem_status ann_train_step(ann_model *m, const chem_mech *mech, chem_
     pa.w[2] = opts->w_hrr;
     if ((st = ann::phys_grad(pa, mech->d, m->phys_part, loss, terms, s)) != CHEM_OK) return st;
   }
-  // backward: wgrad, bias grad, dgrad (through GELU') per layer
+  // backward: wgrad and dgrad (through GELU') per layer; the column sums of the
+  // output gradients (the bias gradients) come with the data gradients, or, for
+  // the output layer and the generic tilings, from their own pass
+  ann::FinishTable f{};
   for (int l = 3; l >= 0; --l) {
     const ann::Layer &L = m->L[l];
     const int S = train_split(m, B, l);
-    const long wn = (long)L.doutp * L.dinp;
     if ((st = run_product(m, B, 4 + l, S, s)) != CHEM_OK) return st;
-    if (S > 1 && (st = ann::sum_splits((long)G * wn, S, m->wg_part, (long)G * wn, m->gW[l], s)) !=
-                     CHEM_OK)
-      return st;
-    // the bias gradient: the column sums that the data gradient left, or its own
-    const int P = l < 3 ? ann::gemm_col_parts(tuned_product(m, B, 8 + l, 1).g) : 0;
-    st = P > 0 ? ann::colsum_parts(L.doutp, P, (const double *)m->tGf[l], m->gb[l], s, G, L.doutp)
-               : ann::colsum(B, L.doutp, m->tGf[l], L.doutp, m->gb[l], m->col_part, s, G,
-                             (long)B * L.doutp, L.doutp);
-    if (st != CHEM_OK) return st;
     if (l > 0 && (st = run_product(m, B, 7 + l, 1, s)) != CHEM_OK) return st;
+    f.cpart[l] = (const double *)m->tGf[l];
+    f.P[l] = l < 3 ? ann::gemm_col_parts(tuned_product(m, B, 8 + l, 1).g) : 0;
+    if (f.P[l] == 0) {
+      f.cpart[l] = m->col_part[l];
+      st = ann::colsum(B, L.doutp, m->tGf[l], L.doutp, m->col_part[l], &f.P[l], s, G,
+                       (long)B * L.doutp);
+      if (st != CHEM_OK) return st;
+    }
+    f.S[l] = S;
+    f.part[l] = S > 1 ? m->wg_part[l] : m->gW[l];
+    f.wn[l] = (int64_t)G * layer_elems(L);
+    f.gW[l] = m->gW[l];
+    f.W[l] = m->Wm[l];
+    f.mW[l] = m->mW[l];
+    f.vW[l] = m->vW[l];
+    f.Wb[l] = m->Wb[l];
+    f.N[l] = L.doutp;
+    f.gb[l] = m->gb[l];
+    f.bW[l] = m->bm[l];
+    f.bm[l] = m->mb[l];
+    f.bv[l] = m->vb[l];
   }
-  if (opts->lr > 0.0f) {
+  f.adam = opts->lr > 0.0f;
+  if (f.adam) {
     m->step += 1;
     m->wt_stale = true;
-    const double bc1 = 1.0 - pow((double)opts->beta1, (double)m->step);
-    const double bc2 = 1.0 - pow((double)opts->beta2, (double)m->step);
-    // the four weight tensors and the four biases in one launch
-    ann::AdamTable at{};
-    at.count = 8;
-    int64_t o = 0;
-    for (int l = 0; l < 4; ++l) {
-      const ann::Layer &L = m->L[l];
-      at.start[2 * l] = o;
-      at.W[2 * l] = m->Wm[l];
-      at.g[2 * l] = m->gW[l];
-      at.m[2 * l] = m->mW[l];
-      at.v[2 * l] = m->vW[l];
-      at.Wb[2 * l] = m->Wb[l];
-      o += (int64_t)G * layer_elems(L);
-      at.start[2 * l + 1] = o;
-      at.W[2 * l + 1] = m->bm[l];
-      at.g[2 * l + 1] = m->gb[l];
-      at.m[2 * l + 1] = m->mb[l];
-      at.v[2 * l + 1] = m->vb[l];
-      at.Wb[2 * l + 1] = nullptr;
-      o += (int64_t)G * L.doutp;
-    }
-    at.start[8] = o;
-    st = ann::adam_multi(at, opts->lr, opts->beta1, opts->beta2, opts->eps, (float)bc1,
-                         (float)bc2, s);
-    if (st != CHEM_OK) return st;
+    f.o = {opts->lr, opts->beta1, opts->beta2, opts->eps,
+           (float)(1.0 - pow((double)opts->beta1, (double)m->step)),
+           (float)(1.0 - pow((double)opts->beta2, (double)m->step))};
   }
-  return CHEM_OK;
+  return ann::finish(f, G, s);
 }
 
 extern "C" int64_t ann_num_steps(const ann_model *m) { return m ? m->step : -1; }
@@ -1625,9 +1624,8 @@ extern "C" chem_status ann_autotune_train(ann_model *m, int64_t B, double *ms_de
     for (int p = 0; p < 11 && ok; ++p)
       ok = tl[p] >= 0 && tl[p] <= ann::GEMM_TILES && (bk[p] == 0 || bk[p] == 32 || bk[p] == 64);
     for (int l = 0; l < 4 && ok; ++l) {
-      const long wn = (long)m->L[l].doutp * m->L[l].dinp;
       ok = sp[l] >= 1 && sp[l] <= 16 && B % (32L * sp[l]) == 0 &&
-           (sp[l] == 1 || (size_t)sp[l] * m->G * wn <= m->wg_cap);
+           sp[l] <= m->wg_most[l];
     }
     if (ok) {
       std::copy(tl, tl + 11, m->tt_tile);
@@ -1661,7 +1659,7 @@ extern "C" chem_status ann_autotune_train(ann_model *m, int64_t B, double *ms_de
     auto once = [&]() -> chem_status {
       chem_status r = ann::gemm(t.g, t.AK, t.BK, t.epi, s, "autotune");
       if (r == CHEM_OK && S > 1)
-        r = ann::sum_splits((long)G * wn, S, m->wg_part, (long)G * wn, m->gW[l], s);
+        r = ann::sum_splits((long)G * wn, S, m->wg_part[l], (long)G * wn, m->gW[l], s);
       return r;
     };
     if (once() != CHEM_OK) return INFINITY;
@@ -1691,8 +1689,7 @@ extern "C" chem_status ann_autotune_train(ann_model *m, int64_t B, double *ms_de
     int bt = 0, bb = 0, bs = S0;
     for (int S = 1; S <= (wg ? 16 : 1); S *= 2) {
       if (wg) {
-        const long wn = (long)m->L[l].doutp * m->L[l].dinp;
-        if (B % (32L * S) != 0 || (S > 1 && (size_t)S * G * wn > m->wg_cap)) continue;
+        if (B % (32L * S) != 0 || S > m->wg_most[l]) continue;
       }
       for (int tile = 1; tile <= ann::GEMM_TILES; ++tile)
         for (int bkv : {32, 64}) {

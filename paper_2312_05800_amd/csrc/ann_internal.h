@@ -187,15 +187,11 @@ struct PhysArgs {
 constexpr int PHYS_PARTS = 64;
 chem_status phys_grad(const PhysArgs &a, const chem::DevMech &M, double *part, float *loss,
                       float *terms, hipStream_t s);
-// out[j] = sum over the M rows of X[:, j]; part: COLSUM_PARTS * N doubles.
-// With groups > 1, group z sums X + z gx into out + z gout (part: groups
-// times as many doubles).
+// part[q][j], q < *P <= COLSUM_PARTS: sums over consecutive ranges of the M rows of X[:, j].
+// With groups > 1, group z sums X + z gx into part + z *P N.
 constexpr int COLSUM_PARTS = 64;
-// its last step: out[j] = sum of part[q][j] over q < P (FP64, [groups][P][N])
-chem_status colsum_parts(int N, int P, const double *part, float *out, hipStream_t s,
-                         int groups = 1, long gout = 0);
-chem_status colsum(int64_t M, int N, const float *X, long ldx, float *out, double *part,
-                   hipStream_t s, int groups = 1, long gx = 0, long gout = 0);
+chem_status colsum(int64_t M, int N, const float *X, long ldx, double *part, int *P,
+                   hipStream_t s, int groups = 1, long gx = 0);
 // Per-species ensemble: member g's output is column 0 of U + g gu (row
 // stride ldu) and its target column g of Ut (row stride ldt); the gradient
 // sign(u - u*) / (n G) goes to column 0 of Gb/Gf + g gu (every other column
@@ -209,20 +205,25 @@ chem_status take_col(int64_t n, const float *src, int lds, float *dst, int ldd, 
 // out[i] = sum_{s < S} part[s * stride + i], in order of s
 chem_status sum_splits(int64_t n, int S, const float *part, long stride, float *out,
                        hipStream_t s);
-// Adam over several tensors in one launch: tensor k holds elements
-// start[k] .. start[k + 1] - 1 of the concatenation (start[0] = 0).
-constexpr int ADAM_MAX = 8;
-struct AdamTable {
-  int count;
-  int64_t start[ADAM_MAX + 1];
-  float *W[ADAM_MAX];
-  const float *g[ADAM_MAX];
-  float *m[ADAM_MAX];
-  float *v[ADAM_MAX];
-  u16 *Wb[ADAM_MAX];  // BF16 copy of W, or null
+// The end of a training step (see k_finish), layer by layer; G networks.
+struct AdamOpts {
+  float lr, b1, b2, eps, bc1, bc2;
 };
-chem_status adam_multi(const AdamTable &t, float lr, float b1, float b2, float eps, float bc1,
-                       float bc2, hipStream_t s);
+struct FinishTable {
+  bool adam;  // update weights and biases too
+  AdamOpts o;
+  int64_t wn[NLAYER];         // weights
+  int S[NLAYER];              // ranges of the weight gradient
+  const float *part[NLAYER];  // [S][wn]; S = 1: gW itself
+  float *gW[NLAYER], *W[NLAYER], *mW[NLAYER], *vW[NLAYER];
+  u16 *Wb[NLAYER];  // BF16 copy of W
+  int N[NLAYER];    // biases of one network, a multiple of 32
+  int P[NLAYER];    // partial column sums
+  const double *cpart[NLAYER];  // [G][P][N]
+  float *gb[NLAYER], *bW[NLAYER], *bm[NLAYER], *bv[NLAYER];
+  int wblk[NLAYER + 1], bblk[NLAYER];  // first blocks (filled in by finish)
+};
+chem_status finish(const FinishTable &f, int G, hipStream_t s);
 chem_status to_bf16(int64_t n, const float *src, u16 *dst, hipStream_t s);
 // dst [K/32][N][32] from src [N][K] (BF16, K a multiple of 32); with permute,
 // element k % 32 of each block goes to position mlp12_slot(k % 32) (the K
