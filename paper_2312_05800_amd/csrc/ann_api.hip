@@ -75,7 +75,7 @@ struct ann_model {
   u16 *tX = nullptr, *tH[3] = {}, *tGb[ann::NLAYER] = {};
   float *tZ[3] = {}, *tU = nullptr, *tUt = nullptr, *tGf[ann::NLAYER] = {};
   double *loss_part = nullptr;
-  double *phys_part = nullptr;  // [PHYS_PARTS][3] partial sums of the physics terms
+  double *phys_part = nullptr;  // [blocks][3] partial sums of the physics terms
   double *col_part[ann::NLAYER] = {};  // [G][COLSUM_PARTS][dout] bias-gradient partials
   // split-K partial weight gradients of each layer, and the most ranges they have room for
   float *wg_part[ann::NLAYER] = {};
@@ -233,6 +233,9 @@ chem_status grow_infer(ann_model *m, int64_t n) {
   return CHEM_OK;
 }
 
+// Blocks of ann::out_grad.
+int out_blocks(int64_t B) { return (int)((B + ann::OUT_SAMPLES - 1) / ann::OUT_SAMPLES); }
+
 // Split-K factor of a weight-gradient GEMM (M x N output, K = batch rows): a
 // power of two that brings the launch to about 1024 blocks of 128 x 128, while
 // every split keeps a multiple of 32 rows.
@@ -266,8 +269,9 @@ chem_status grow_train(ann_model *m, int64_t B) {
     oGb[l] = sect(G * B * m->L[l].doutp * 2);
     oGf[l] = sect(G * B * m->L[l].doutp * 4);
   }
-  const size_t oL = sect(LOSS_PARTS * 8);
-  const size_t oP = sect(ann::PHYS_PARTS * 3 * 8);
+  const size_t parts = (size_t)std::max(LOSS_PARTS, out_blocks(B));
+  const size_t oL = sect(parts * 8);
+  const size_t oP = sect(parts * 3 * 8);
   size_t wg_n = 0, oC[ann::NLAYER], wg_off[ann::NLAYER];
   int wg_most[ann::NLAYER];
   for (int l = 0; l < 4; ++l) {
@@ -868,7 +872,7 @@ chem_status forward_small(ann_model *m, const InferWs &w, int64_t n, const ann::
 chem_status forward_chunk(ann_model *m, const InferWs &w, int64_t n, int64_t ld, const double *T,
                           const double *p, const double *Y, float *U, int ldu, uint8_t *ood,
                           float ood_margin, hipStream_t s, bool keep_h1 = false) {
-  ann::FeatArgs fa{n, ld, T, p, Y, nullptr, m->n_out, m->L[0].dinp, m->nm.mu_in, m->nm.sd_in,
+  ann::FeatArgs fa{n, ld, T, p, Y, m->n_out, m->L[0].dinp, m->nm.mu_in, m->nm.sd_in,
                    m->nm.lambda, w.X, ood, m->nm.lo, m->nm.hi, ood_margin};
   chem_status st;
   if (!keep_h1 && small_path(m, w, n)) return forward_small(m, w, n, fa, U, ldu, s);
@@ -1516,55 +1520,51 @@ extern "C" chem_status ann_train_step(ann_model *m, const chem_mech *mech, chem_
     m->fp8_ready = false;
     m->use_fp8 = false;
   }
-  ann::FeatArgs fa{B, batch.ld, T, p, Y0, index, K, m->L[0].dinp, m->nm.mu_in, m->nm.sd_in,
-                   m->nm.lambda, m->tX, nullptr, nullptr, nullptr, 0.0f};
-  if ((st = ann::features(fa, s)) != CHEM_OK) return st;
-  ann::TargetArgs ta{B, batch.ld, Y0, Y1, index, K, uw(m), m->nm.mu_out, m->nm.sd_out,
-                     m->nm.lambda, m->tUt};
-  if ((st = ann::targets(ta, s)) != CHEM_OK) return st;
+  const ann::TrainInArgs ta{B, batch.ld, T, p, Y0, Y1, index, K, m->L[0].dinp, uw(m),
+                            m->nm.mu_in, m->nm.sd_in, m->nm.mu_out, m->nm.sd_out, m->nm.lambda,
+                            m->tX, m->tUt};
+  if ((st = ann::train_inputs(ta, s)) != CHEM_OK) return st;
   // forward, keeping pre-activations (FP32) and activations (BF16); an
   // ensemble's members are the groups of each product (the first layer reads
   // the shared input rows)
   const int G = m->G;
   for (int l = 0; l < 4; ++l)
     if ((st = run_product(m, B, l, 1, s)) != CHEM_OK) return st;
-  if (G > 1)
-    st = ann::l1_grad_members(B, G, m->L[3].doutp, (long)B * m->L[3].doutp, m->tU, m->tUt, uw(m),
-                              m->tGb[3], m->tGf[3], m->loss_part, LOSS_PARTS, loss, s);
-  else
-    st = ann::l1_grad(B, K, m->L[3].doutp, m->tU, m->tUt, m->tGb[3], m->tGf[3], m->loss_part,
-                      LOSS_PARTS, loss, s);
-  if (st != CHEM_OK) return st;
-  if (phys) {
-    ann::PhysArgs pa{};
-    pa.n = B;
-    pa.ld = batch.ld;
-    pa.K = K;
-    pa.doutp = m->L[3].doutp;
-    pa.U = m->tU;
-    pa.Ut = m->tUt;
-    pa.Gf = m->tGf[3];
-    pa.Gb = m->tGb[3];
-    pa.mu = m->nm.mu_out;
-    pa.sd = m->nm.sd_out;
-    pa.T1 = T1;
-    pa.index = index;
-    pa.w[0] = opts->w_mass;
-    pa.w[1] = opts->w_energy;
-    pa.w[2] = opts->w_hrr;
-    if ((st = ann::phys_grad(pa, mech->d, m->phys_part, loss, terms, s)) != CHEM_OK) return st;
-  }
-  // backward: wgrad and dgrad (through GELU') per layer; the column sums of the
-  // output gradients (the bias gradients) come with the data gradients, or, for
-  // the output layer and the generic tilings, from their own pass
   ann::FinishTable f{};
+  f.lpart = m->loss_part;
+  f.loss = loss;
+  if (G > 1) {
+    st = ann::l1_grad_members(B, G, m->L[3].doutp, (long)B * m->L[3].doutp, m->tU, m->tUt, uw(m),
+                              m->tGb[3], m->tGf[3], m->loss_part, LOSS_PARTS, s);
+    f.nparts = LOSS_PARTS;
+    f.lscale = 1.0 / ((double)B * G);
+  } else {
+    ann::OutGradArgs oa{B, K, m->L[3].doutp, m->tU, m->tUt, m->tGb[3], m->loss_part, m->phys_part,
+                        (double *)m->tGf[3], m->nm.mu_out, m->nm.sd_out, T1, index,
+                        {opts->w_mass, opts->w_energy, opts->w_hrr}};
+    st = ann::out_grad(oa, phys ? &mech->d : nullptr, s);
+    f.nparts = out_blocks(B);
+    f.lscale = 1.0 / ((double)B * K);
+    if (phys) {
+      f.ppart = m->phys_part;
+      f.inv_n = 1.0 / (double)B;
+      for (int q = 0; q < 3; ++q) f.w[q] = oa.w[q];
+      f.terms = terms;
+    }
+  }
+  if (st != CHEM_OK) return st;
+  // backward: wgrad and dgrad (through GELU') per layer; the column sums of the
+  // output gradients (the bias gradients) come with those, or, for an
+  // ensemble's output layer and the generic tilings, from their own pass
   for (int l = 3; l >= 0; --l) {
     const ann::Layer &L = m->L[l];
     const int S = train_split(m, B, l);
     if ((st = run_product(m, B, 4 + l, S, s)) != CHEM_OK) return st;
     if (l > 0 && (st = run_product(m, B, 7 + l, 1, s)) != CHEM_OK) return st;
     f.cpart[l] = (const double *)m->tGf[l];
-    f.P[l] = l < 3 ? ann::gemm_col_parts(tuned_product(m, B, 8 + l, 1).g) : 0;
+    f.P[l] = l < 3     ? ann::gemm_col_parts(tuned_product(m, B, 8 + l, 1).g)
+             : G == 1 ? out_blocks(B)
+                      : 0;
     if (f.P[l] == 0) {
       f.cpart[l] = m->col_part[l];
       st = ann::colsum(B, L.doutp, m->tGf[l], L.doutp, m->col_part[l], &f.P[l], s, G,

@@ -137,7 +137,6 @@ chem_status tile_e4m3(int rows_p, int cols_p, const uint8_t *src, uint8_t *dst, 
 struct FeatArgs {
   int64_t n, ld;
   const double *T, *p, *Y;
-  const int64_t *index;  // optional gather list
   int K, dinp;
   const float *mu, *sd;
   float lambda;
@@ -155,38 +154,36 @@ chem_status features(const FeatArgs &a, hipStream_t s);
 chem_status feat_l1(const FeatArgs &f, const u16 *W1, const float *b1, int nk, u16 *H, long ldh,
                     hipStream_t s);
 
-struct TargetArgs {
+// Inputs X [n][dinp] and targets Ut [n][doutp] of a training batch (dinp, doutp multiples of 32).
+struct TrainInArgs {
   int64_t n, ld;
-  const double *Y0, *Y1;
+  const double *T, *p, *Y0, *Y1;
   const int64_t *index;
-  int K, doutp;
-  const float *mu, *sd;
+  int K, dinp, doutp;
+  const float *mu_in, *sd_in, *mu_out, *sd_out;
   float lambda;
-  float *U;  // [n][doutp] fp32
+  u16 *X;
+  float *Ut;
 };
-chem_status targets(const TargetArgs &a, hipStream_t s);
+chem_status train_inputs(const TrainInArgs &a, hipStream_t s);
 
-chem_status l1_grad(int64_t n, int K, int doutp, const float *U, const float *Ut, u16 *Gb,
-                    float *Gf, double *loss_part, int nparts, float *loss, hipStream_t s);
-
-// Physics terms of the training loss (mass-fraction sum, energy at the
-// reference final temperature T1, heat release at 298.15 K): their gradient
-// is added to Gf (and Gb refreshed from it), w-weighted batch means are
-// added to *loss, the unweighted means written to terms[3] (nullable).
-struct PhysArgs {
-  int64_t n, ld;
+// Output gradient Gb [n][doutp] (see k_out_grad) and, per block of OUT_SAMPLES samples,
+// the sums of |u - u*| (lpart), of the three terms (ppart [3], with a mechanism) and of the
+// gradient's columns (cpart [doutp]).
+constexpr int OUT_SAMPLES = 64;
+struct OutGradArgs {
+  int64_t n;
   int K, doutp;
   const float *U, *Ut;  // network output and targets, z-space [n][doutp]
-  float *Gf;
   u16 *Gb;
+  double *lpart, *ppart, *cpart;
+  // the physics terms
   const float *mu, *sd;  // output statistics
   const double *T1;      // [ld] reference final temperature, gathered through index
   const int64_t *index;
   float w[3];
 };
-constexpr int PHYS_PARTS = 64;
-chem_status phys_grad(const PhysArgs &a, const chem::DevMech &M, double *part, float *loss,
-                      float *terms, hipStream_t s);
+chem_status out_grad(const OutGradArgs &a, const chem::DevMech *M, hipStream_t s);
 // part[q][j], q < *P <= COLSUM_PARTS: sums over consecutive ranges of the M rows of X[:, j].
 // With groups > 1, group z sums X + z gx into part + z *P N.
 constexpr int COLSUM_PARTS = 64;
@@ -195,10 +192,10 @@ chem_status colsum(int64_t M, int N, const float *X, long ldx, double *part, int
 // Per-species ensemble: member g's output is column 0 of U + g gu (row
 // stride ldu) and its target column g of Ut (row stride ldt); the gradient
 // sign(u - u*) / (n G) goes to column 0 of Gb/Gf + g gu (every other column
-// 0), and *loss is the mean of |u - u*| over samples and members.
+// 0); loss_part: nparts partial sums of |u - u*| over samples and members.
 chem_status l1_grad_members(int64_t n, int G, int ldu, long gu, const float *U, const float *Ut,
                             int ldt, u16 *Gb, float *Gf, double *loss_part, int nparts,
-                            float *loss, hipStream_t s);
+                            hipStream_t s);
 // dst[i * ldd] = src[i * lds] for i < n (one output column of an ensemble
 // member into the ensemble's output)
 chem_status take_col(int64_t n, const float *src, int lds, float *dst, int ldd, hipStream_t s);
@@ -221,6 +218,12 @@ struct FinishTable {
   int P[NLAYER];    // partial column sums
   const double *cpart[NLAYER];  // [G][P][N]
   float *gb[NLAYER], *bW[NLAYER], *bm[NLAYER], *bv[NLAYER];
+  // loss = lscale sum lpart + w . terms, the terms inv_n sum ppart (null: none)
+  int nparts;
+  const double *lpart, *ppart;
+  double lscale, inv_n;
+  float w[3];
+  float *loss, *terms;
   int wblk[NLAYER + 1], bblk[NLAYER];  // first blocks (filled in by finish)
 };
 chem_status finish(const FinishTable &f, int G, hipStream_t s);

@@ -1620,7 +1620,6 @@ __global__ __launch_bounds__(BLK) void k_features(FeatArgs a) {
   if (DINP == 0 && !live) return;
   const int dinp = DINP > 0 ? DINP : a.dinp;
   if (live) {
-    const int64_t c = a.index ? a.index[i] : i;
     u16 *out = a.X + i * dinp;
     bool outside = false;
     constexpr int UNROLL = DINP > 0 ? DINP / 8 : 1;
@@ -1634,9 +1633,9 @@ __global__ __launch_bounds__(BLK) void k_features(FeatArgs a) {
         z[t] = 0.0f;
         if (j < a.K + 2) {
           float x;
-          if (j == 0) x = (float)a.T[c];
-          else if (j == 1) x = (float)a.p[c];
-          else x = boxcox_fast((float)a.Y[(int64_t)(j - 2) * a.ld + c], a.lambda);
+          if (j == 0) x = (float)a.T[i];
+          else if (j == 1) x = (float)a.p[i];
+          else x = boxcox_fast((float)a.Y[(int64_t)(j - 2) * a.ld + i], a.lambda);
           if (a.ood && ood_feature(a, j, x)) outside = true;
           z[t] = (x - a.mu[j]) / a.sd[j];
         }
@@ -1663,39 +1662,57 @@ __global__ __launch_bounds__(BLK) void k_features(FeatArgs a) {
   }
 }
 
-// One cell per thread.  The loads of a batch of TGT_BATCH outputs are all
-// issued before the first store (the output rows may not alias the inputs, but
-// the compiler cannot know that), and a padded width that is a multiple of 4
-// is written with 16-byte stores.
-constexpr int TGT_BATCH = 16;
-
-__global__ void k_targets(TargetArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The network inputs (z-scored features, BF16) and targets (z-scored change of the
+// mass fractions, FP64 difference) of a training batch, gathered through index.  A block
+// takes 64 samples, one per lane; its four waves share the columns, eight
+// at a time, with all of their loads in flight: the time is that of one gather.  8192
+// samples of 30 species: 16 us, 2048 10 (one sample per thread, features and targets in a
+// launch each: 23 and 15, 17 and 10).
+__global__ __launch_bounds__(256) void k_train_inputs(TrainInArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
   if (i >= a.n) return;
   const int64_t c = a.index ? a.index[i] : i;
-  float *out = a.U + i * a.doutp;
-  const bool vec = (a.doutp & 3) == 0 && ((uintptr_t)a.U & 15) == 0;
-  for (int k0 = 0; k0 < a.doutp; k0 += TGT_BATCH) {
-    double y1[TGT_BATCH], y0[TGT_BATCH];
+  for (int j0 = 8 * wave; j0 < a.dinp || j0 < a.doutp; j0 += 32) {
+    // Y0 of the species of the columns j0 .. j0 + 7 and of their features (j - 2)
+    double y0[10], y1[8];
 #pragma unroll
-    for (int j = 0; j < TGT_BATCH; ++j) {
-      const int k = k0 + j;
-      y1[j] = k < a.K ? a.Y1[(int64_t)k * a.ld + c] : 0.0;
-      y0[j] = k < a.K ? a.Y0[(int64_t)k * a.ld + c] : 0.0;
+    for (int t = 0; t < 10; ++t) {
+      const int k = j0 - 2 + t;
+      y0[t] = k >= 0 && k < a.K ? a.Y0[(int64_t)k * a.ld + c] : 0.0;
     }
-    float v[TGT_BATCH];
 #pragma unroll
-    for (int j = 0; j < TGT_BATCH; ++j) {
-      const int k = k0 + j;
-      // the change of the mass fraction over the step (FP64 difference)
-      v[j] = k < a.K ? (float)((y1[j] - y0[j] - a.mu[k]) / a.sd[k]) : 0.0f;
+    for (int t = 0; t < 8; ++t) y1[t] = j0 + t < a.K ? a.Y1[(int64_t)(j0 + t) * a.ld + c] : 0.0;
+    double T = 0.0, p = 0.0;
+    if (j0 == 0) {
+      T = a.T[c];
+      p = a.p[c];
     }
-    if (vec && k0 + TGT_BATCH <= a.doutp) {
+    float z[8], v[8];
 #pragma unroll
-      for (int j = 0; j < TGT_BATCH; j += 4)
-        *(float4 *)(out + k0 + j) = make_float4(v[j], v[j + 1], v[j + 2], v[j + 3]);
-    } else {
-      for (int j = 0; j < TGT_BATCH && k0 + j < a.doutp; ++j) out[k0 + j] = v[j];
+    for (int t = 0; t < 8; ++t) {
+      const int j = j0 + t;
+      z[t] = v[t] = 0.0f;
+      if (j < a.K + 2) {
+        const float x =
+            j == 0 ? (float)T : (j == 1 ? (float)p : boxcox_fast((float)y0[t], a.lambda));
+        z[t] = (x - a.mu_in[j]) / a.sd_in[j];
+      }
+      if (j < a.K) v[t] = (float)((y1[t] - y0[t + 2] - a.mu_out[j]) / a.sd_out[j]);
+    }
+    if (j0 < a.dinp) {
+      uint4 o;
+      o.x = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){z[0], z[1]}, bf16x2));
+      o.y = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){z[2], z[3]}, bf16x2));
+      o.z = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){z[4], z[5]}, bf16x2));
+      o.w = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){z[6], z[7]}, bf16x2));
+      *(uint4 *)(a.X + i * a.dinp + j0) = o;
+    }
+    if (j0 < a.doutp) {
+      float *const u = a.Ut + i * a.doutp + j0;
+      *(float4 *)u = make_float4(v[0], v[1], v[2], v[3]);
+      *(float4 *)(u + 4) = make_float4(v[4], v[5], v[6], v[7]);
     }
   }
 }
@@ -1781,35 +1798,6 @@ __global__ __launch_bounds__(256) void k_feat_l1(FeatL1Args a) {
 
 // ------------------------------------------------------------ training
 
-// g = sign(u - u*) / (n K) (sign(0) = 0) on the K real outputs, 0 on padding;
-// per-block partial sums of |u - u*| for the loss.
-__global__ void k_l1(int64_t n, int K, int doutp, const float *U, const float *Ut, u16 *Gb,
-                     float *Gf, double *part) {
-  __shared__ double red[256];
-  const double scale = 1.0 / ((double)n * K);
-  double s = 0.0;
-  const int64_t total = n * doutp;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int k = (int)(e % doutp);
-    float gv = 0.0f;
-    if (k < K) {
-      const float d = U[e] - Ut[e];
-      s += fabs((double)d);
-      gv = (float)(((d > 0.0f) - (d < 0.0f)) * scale);
-    }
-    Gb[e] = f2bf(gv);
-    Gf[e] = gv;
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
 // Per-species ensemble: member g's single output is column 0 of its [n][ldu]
 // block; g = sign(u - u*) / (n G) there, 0 on the padding columns.
 __global__ void k_l1_members(int64_t n, int G, int ldu, long gu, const float *U, const float *Ut,
@@ -1869,89 +1857,137 @@ __device__ __forceinline__ double species_h(const chem::DevMech &M, int k, doubl
   return 8.314462618 * T * hRT * M.invW[k];
 }
 
-// One sample per thread.  With dY = sd u + mu the predicted change and
-// e = (u - u*) sd its error (FP64 from the FP32 u), each term is an L1
-// penalty |s_t| / D_t on a linear functional s_t: the sum of dY (weights 1),
-// sum_k h_k(T1) e_k and sum_k h_k(298.15 K) e_k; D_t = sum_k |a_tk| sd_k is
-// the functional's size for errors of one standard deviation.  d/du_k of
-// w_t |s_t| / (D_t n) is w_t sign(s_t) a_tk sd_k / (D_t n).
-__global__ void k_phys(PhysArgs a, chem::DevMech M, double *part) {
-  __shared__ double red[3][256];
+// Gradient of the loss in the network's output: sign(u - u*) / (n K) (sign(0) = 0) on the K
+// real outputs, 0 on the padding, plus, with KP > 0, that of the physics terms.  With
+// dY = sd u + mu the predicted change and e = (u - u*) sd its error (FP64 from the FP32
+// u), each term is an L1 penalty |s_t| / D_t on a linear functional s_t: the sum of dY
+// (weights 1), sum_k h_k(T1) e_k and sum_k h_k(298.15 K) e_k; D_t = sum_k |a_tk| sd_k is
+// the functional's size for errors of one standard deviation.  d/du_k of w_t |s_t| /
+// (D_t n) is w_t sign(s_t) a_tk sd_k / (D_t n).
+//
+// A block takes 64 samples, one per lane, its four waves eight of every 32 outputs each;
+// the summands of the functionals go through LDS and one wave adds up one functional in
+// the order of the species.  The block leaves partial sums of the loss, the terms and
+// the gradient's columns (the output layer's bias gradient).  Bound by the latency of
+// these phases: 8192 samples, 30 species: 13.5 us, without the terms 5 (one sample per
+// thread: 39, after 6 for the L1 part, and 20 of adding up the partial sums serially).
+template <int KP>
+__global__ __launch_bounds__(256) void k_out_grad(OutGradArgs a, chem::DevMech M) {
   constexpr double TREF = 298.15;
-  double acc[3] = {0.0, 0.0, 0.0};
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t c = a.index ? a.index[i] : i;
+  constexpr int KS = KP > 0 ? KP : 1, LANES = KP > 0 ? 64 : 1;
+  __shared__ double dY_s[KS][LANES], e_s[KS][LANES], h1_s[KS][LANES], h0_s[KS];
+  __shared__ double gt_s[3][LANES];
+  __shared__ float tile[64][33];
+  __shared__ double red[256];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const bool live = i < a.n;
+  const int64_t row = (live ? i : a.n - 1) * a.doutp;
+  double acc = 0.0;  // wave t < 3: the sample's term t
+  if constexpr (KP > 0) {
+    const int64_t c = a.index ? a.index[live ? i : a.n - 1] : (live ? i : a.n - 1);
     const double T1 = a.T1 ? a.T1[c] : TREF;
-    const float *u = a.U + i * a.doutp, *ut = a.Ut + i * a.doutp;
-    double sm = 0.0, se = 0.0, sh = 0.0, dm = 0.0, de = 0.0, dh = 0.0;
-    for (int k = 0; k < a.K; ++k) {
-      const double sd = a.sd[k], mu = a.mu[k];
-      const double dY = sd * (double)u[k] + mu;
-      const double e = ((double)u[k] - (double)ut[k]) * sd;
-      const double h1 = species_h(M, k, T1), h0 = species_h(M, k, TREF);
-      sm += dY;
-      dm += sd;
-      se += h1 * e;
-      de += fabs(h1) * sd;
-      sh += h0 * e;
-      dh += fabs(h0) * sd;
+    if (tid < a.K) h0_s[tid] = species_h(M, tid, TREF);
+    for (int j0 = 8 * wave; j0 < a.K; j0 += 32) {
+      const float4 ua = *(const float4 *)(a.U + row + j0), ub = *(const float4 *)(a.U + row + j0 + 4);
+      const float4 ta = *(const float4 *)(a.Ut + row + j0),
+                   tb = *(const float4 *)(a.Ut + row + j0 + 4);
+      const float u[8] = {ua.x, ua.y, ua.z, ua.w, ub.x, ub.y, ub.z, ub.w};
+      const float ut[8] = {ta.x, ta.y, ta.z, ta.w, tb.x, tb.y, tb.z, tb.w};
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int k = j0 + t;
+        if (k >= a.K) break;
+        const double sd = a.sd[k], mu = a.mu[k];
+        dY_s[k][lane] = sd * (double)u[t] + mu;
+        e_s[k][lane] = ((double)u[t] - (double)ut[t]) * sd;
+        h1_s[k][lane] = species_h(M, k, T1);
+      }
     }
-    acc[0] += fabs(sm) / dm;
-    acc[1] += fabs(se) / de;
-    acc[2] += fabs(sh) / dh;
-    const double inv_n = 1.0 / (double)a.n;
-    const double gm = a.w[0] * ((sm > 0.0) - (sm < 0.0)) / dm * inv_n;
-    const double ge = a.w[1] * ((se > 0.0) - (se < 0.0)) / de * inv_n;
-    const double gh = a.w[2] * ((sh > 0.0) - (sh < 0.0)) / dh * inv_n;
-    float *gf = a.Gf + i * a.doutp;
-    u16 *gb = a.Gb + i * a.doutp;
-    for (int k = 0; k < a.K; ++k) {
-      const double sd = a.sd[k];
-      const double g = (gm + ge * species_h(M, k, T1) + gh * species_h(M, k, TREF)) * sd;
-      const float v = gf[k] + (float)g;
-      gf[k] = v;
-      gb[k] = f2bf(v);
+    __syncthreads();
+    if (wave < 3) {
+      double s = 0.0, d = 0.0;
+      for (int k = 0; k < a.K; ++k) {
+        const double sd = a.sd[k];
+        if (wave == 0) {
+          s += dY_s[k][lane];
+          d += sd;
+        } else {
+          const double h = wave == 1 ? h1_s[k][lane] : h0_s[k];
+          s += h * e_s[k][lane];
+          d += fabs(h) * sd;
+        }
+      }
+      acc = live ? fabs(s) / d : 0.0;
+      gt_s[wave][lane] = a.w[wave] * ((s > 0.0) - (s < 0.0)) / d * (1.0 / (double)a.n);
     }
-  }
-  for (int t = 0; t < 3; ++t) red[t][threadIdx.x] = acc[t];
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off)
-      for (int t = 0; t < 3; ++t) red[t][threadIdx.x] += red[t][threadIdx.x + off];
     __syncthreads();
   }
-  if (threadIdx.x < 3) part[blockIdx.x * 3 + threadIdx.x] = red[threadIdx.x][0];
-}
-
-// Batch means of the three terms (partials added in block order); the
-// weighted sum joins the L1 loss.
-__global__ void k_phys_final(const double *part, int nparts, double inv_n, float w0, float w1,
-                             float w2, float *loss, float *terms) {
-  if (threadIdx.x != 0) return;
-  double t[3] = {0.0, 0.0, 0.0};
-  for (int b = 0; b < nparts; ++b)
-    for (int q = 0; q < 3; ++q) t[q] += part[b * 3 + q];
-  for (int q = 0; q < 3; ++q) t[q] *= inv_n;
-  if (terms)
-    for (int q = 0; q < 3; ++q) terms[q] = (float)t[q];
-  *loss = (float)((double)*loss + w0 * t[0] + w1 * t[1] + w2 * t[2]);
-}
-
-__global__ void k_loss_final(const double *part, int nparts, double scale, float *loss) {
-  if (threadIdx.x != 0) return;
-  // partials added in order, loaded eight at a time
-  double s = 0.0;
-  int i = 0;
-  for (; i + 8 <= nparts; i += 8) {
-    double x[8];
+  const double scale = 1.0 / ((double)a.n * a.K);
+  double loss = 0.0;
+  for (int c0 = 0; c0 < a.doutp; c0 += 32) {
+    const int j0 = c0 + 8 * wave;
+    const float4 ua = *(const float4 *)(a.U + row + j0), ub = *(const float4 *)(a.U + row + j0 + 4);
+    const float4 ta = *(const float4 *)(a.Ut + row + j0),
+                 tb = *(const float4 *)(a.Ut + row + j0 + 4);
+    const float u[8] = {ua.x, ua.y, ua.z, ua.w, ub.x, ub.y, ub.z, ub.w};
+    const float ut[8] = {ta.x, ta.y, ta.z, ta.w, tb.x, tb.y, tb.z, tb.w};
+    u16 h[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) x[r] = part[i + r];
+    for (int t = 0; t < 8; ++t) {
+      const int k = j0 + t;
+      float v = 0.0f;
+      if (live && k < a.K) {
+        const float d = u[t] - ut[t];
+        loss += fabs((double)d);
+        v = (float)(((d > 0.0f) - (d < 0.0f)) * scale);
+        if constexpr (KP > 0) {
+          const double sd = a.sd[k];
+          const double g =
+              (gt_s[0][lane] + gt_s[1][lane] * h1_s[k][lane] + gt_s[2][lane] * h0_s[k]) * sd;
+          v = v + (float)g;
+        }
+      }
+      h[t] = f2bf(v);
+      tile[lane][8 * wave + t] = v;
+    }
+    if (live)
+      *(uint4 *)(a.Gb + row + j0) =
+          make_uint4(h[0] | (unsigned)h[1] << 16, h[2] | (unsigned)h[3] << 16,
+                     h[4] | (unsigned)h[5] << 16, h[6] | (unsigned)h[7] << 16);
+    __syncthreads();
+    // the 32 columns over the block's samples, eight to a thread
+    double s = 0.0;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) s += x[r];
+    for (int r = 0; r < 8; ++r) s += tile[8 * (tid >> 5) + r][tid & 31];
+    red[tid] = s;
+    __syncthreads();
+    if (tid < 32) {
+      s = 0.0;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) s += red[32 * r + tid];
+      a.cpart[(int64_t)blockIdx.x * a.doutp + c0 + tid] = s;
+    }
+    __syncthreads();
   }
-  for (; i < nparts; ++i) s += part[i];
-  *loss = (float)(s * scale);
+  red[tid] = loss;
+  __syncthreads();
+  for (int off = 128; off > 0; off >>= 1) {
+    if (tid < off) red[tid] += red[tid + off];
+    __syncthreads();
+  }
+  if (tid == 0) a.lpart[blockIdx.x] = red[0];
+  if constexpr (KP > 0) {
+    __syncthreads();
+    red[tid] = acc;
+    __syncthreads();
+    for (int off = 32; off > 0; off >>= 1) {
+      if (lane < off) red[tid] += red[tid + off];
+      __syncthreads();
+    }
+    if (lane == 0 && wave < 3) a.ppart[(int64_t)blockIdx.x * 3 + wave] = red[tid];
+  }
 }
 
 // Column sums in two fixed-order passes (FP64 accumulation): block row q
@@ -2002,8 +2038,8 @@ __device__ __forceinline__ u16 adam_elem(float gi, float *W, float *m, float *v,
 }
 
 // The end of a training step in one launch: the weight gradients from their ranges
-// (added in order), the bias gradients from the column sums, and, with adam set,
-// the update of weights and biases.  A weight block takes 1024 elements of one layer, a
+// (added in order), the bias gradients from the column sums, the loss from its partial
+// sums, and, with adam set, the update of weights and biases.  A weight block takes 1024 elements of one layer, a
 // thread four with the loads of all ranges in flight; a bias block FIN_COLS columns, the
 // partial sums over its 16 rows of threads.
 //
@@ -2013,6 +2049,33 @@ constexpr int FIN_COLS = 16;
 __global__ __launch_bounds__(256) void k_finish(FinishTable t) {
   __shared__ double red[16][FIN_COLS];
   const int b = blockIdx.x, tid = threadIdx.x;
+  if (b == (int)gridDim.x - 1) {  // the loss, with the weighted means of the physics terms
+    __shared__ double sums[4][256];
+    const int nq = t.ppart ? 4 : 1;
+    for (int q = 0; q < nq; ++q) {
+      double s = 0.0;
+      for (int r = tid; r < t.nparts; r += 256)
+        s += q == 0 ? t.lpart[r] : t.ppart[3 * (int64_t)r + q - 1];
+      sums[q][tid] = s;
+    }
+    __syncthreads();
+    for (int off = 128; off > 0; off >>= 1) {
+      if (tid < off)
+        for (int q = 0; q < nq; ++q) sums[q][tid] += sums[q][tid + off];
+      __syncthreads();
+    }
+    if (tid != 0) return;
+    float loss = (float)(sums[0][0] * t.lscale);
+    if (t.ppart) {
+      double x[3];
+      for (int q = 0; q < 3; ++q) x[q] = sums[1 + q][0] * t.inv_n;
+      if (t.terms)
+        for (int q = 0; q < 3; ++q) t.terms[q] = (float)x[q];
+      loss = (float)((double)loss + t.w[0] * x[0] + t.w[1] * x[1] + t.w[2] * x[2]);
+    }
+    *t.loss = loss;
+    return;
+  }
   if (b < t.wblk[NLAYER]) {
     int l = 0;
 #pragma unroll
@@ -2951,39 +3014,32 @@ chem_status features(const FeatArgs &a, hipStream_t s) {
   return CHEM_OK;
 }
 
-chem_status targets(const TargetArgs &a, hipStream_t s) {
+chem_status train_inputs(const TrainInArgs &a, hipStream_t s) {
   if (a.n <= 0) return CHEM_OK;
-  hipLaunchKernelGGL(k_targets, dim3(nblk(a.n, 64)), dim3(64), 0, s, a);
+  chem::ProfScope prof("ann_train_inputs", s);
+  hipLaunchKernelGGL(k_train_inputs, dim3(nblk(a.n, 64)), dim3(256), 0, s, a);
   CHEM_HIP(hipGetLastError());
   return CHEM_OK;
 }
 
-chem_status phys_grad(const PhysArgs &a, const chem::DevMech &M, double *part, float *loss,
-                      float *terms, hipStream_t s) {
+chem_status out_grad(const OutGradArgs &a, const chem::DevMech *M, hipStream_t s) {
   if (a.n <= 0) return CHEM_OK;
-  hipLaunchKernelGGL(k_phys, dim3(PHYS_PARTS), dim3(256), 0, s, a, M, part);
-  hipLaunchKernelGGL(k_phys_final, dim3(1), dim3(64), 0, s, part, PHYS_PARTS, 1.0 / (double)a.n,
-                     a.w[0], a.w[1], a.w[2], loss, terms);
-  CHEM_HIP(hipGetLastError());
-  return CHEM_OK;
-}
-
-chem_status l1_grad(int64_t n, int K, int doutp, const float *U, const float *Ut, u16 *Gb,
-                    float *Gf, double *loss_part, int nparts, float *loss, hipStream_t s) {
-  hipLaunchKernelGGL(k_l1, dim3(nparts), dim3(256), 0, s, n, K, doutp, U, Ut, Gb, Gf, loss_part);
-  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, s, loss_part, nparts,
-                     1.0 / ((double)n * K), loss);
+  const dim3 grid(nblk(a.n, OUT_SAMPLES)), block(256);
+  if (!M)
+    hipLaunchKernelGGL(k_out_grad<0>, grid, block, 0, s, a, chem::DevMech{});
+  else if (a.K <= 32)
+    hipLaunchKernelGGL(k_out_grad<32>, grid, block, 0, s, a, *M);
+  else
+    hipLaunchKernelGGL(k_out_grad<64>, grid, block, 0, s, a, *M);
   CHEM_HIP(hipGetLastError());
   return CHEM_OK;
 }
 
 chem_status l1_grad_members(int64_t n, int G, int ldu, long gu, const float *U, const float *Ut,
                             int ldt, u16 *Gb, float *Gf, double *loss_part, int nparts,
-                            float *loss, hipStream_t s) {
+                            hipStream_t s) {
   hipLaunchKernelGGL(k_l1_members, dim3(nparts), dim3(256), 0, s, n, G, ldu, gu, U, Ut, ldt, Gb,
                      Gf, loss_part);
-  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, s, loss_part, nparts,
-                     1.0 / ((double)n * G), loss);
   CHEM_HIP(hipGetLastError());
   return CHEM_OK;
 }
@@ -3050,7 +3106,7 @@ chem_status finish(const FinishTable &f, int G, hipStream_t s) {
     b += G * (t.N[l] / FIN_COLS);
   }
   t.wblk[NLAYER] = w;
-  hipLaunchKernelGGL(k_finish, dim3((unsigned)(w + b)), dim3(256), 0, s, t);
+  hipLaunchKernelGGL(k_finish, dim3((unsigned)(w + b + 1)), dim3(256), 0, s, t);
   CHEM_HIP(hipGetLastError());
   return CHEM_OK;
 }
