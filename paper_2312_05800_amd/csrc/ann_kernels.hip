@@ -1352,12 +1352,13 @@ __global__ __launch_bounds__(WM *WN * 64) void k_gemm8(GemmArgs g) {
 // E4M3 x E4M3 forward GEMM on the direct-to-LDS ring: 16x16 output tiles with
 // v_mfma_scale_f32_16x16x128_f8f6f4 (block scales 2^0), one MFMA K-step per
 // 128-byte stage row.  A DMA instruction covers 8 rows of 128 bytes; chunk c
-// of row r sits at c ^ swz8(r), which keeps the 16-lane phases of the
-// fragment reads (rows r..r+15, one chunk each) on distinct banks.  K must be
+// of row r sits at c ^ swz8(r), which keeps the phases of the fragment reads
+// on distinct banks (see swz: the even rows of a phase are 0, 2, 12, 14 with chunk c and
+// 4 .. 10 with c ^ 2, the odd ones likewise in the other half of the banks).  K must be
 // a multiple of 128 (operands zero-padded by the caller).  Fragment: lane l
 // holds row l % 16 and the 32 K bytes 32 (l / 16) ..; the per-tensor scales
 // multiply the accumulator in the epilogue.
-__device__ __forceinline__ int swz8(int r) { return (r >> 1) & 7; }
+__device__ __forceinline__ int swz8(int r) { return ((r >> 1) & 1) | (r & 8 ? 6 : 0); }
 
 template <int WM, int TM16, int TN16, int EPI, int STAGES = 3>
 __global__ __launch_bounds__(WM * 64) void k_gemm8_dma16(GemmArgs g) {
@@ -2970,9 +2971,12 @@ chem_status gemm8(const GemmArgs &g, int epi, hipStream_t s, const char *label) 
   }
   if (g.K % 128 == 0 && g.N % 16 == 0 && ((uintptr_t)g.A8 & 15) == 0 &&
       ((uintptr_t)g.B8 & 15) == 0 && g.ldcb % 4 == 0 && g.ldcq % 4 == 0) {
-    // 256 x 160 tiles (N a multiple of 160), else 128 x 208 (N of 208)
+    // 128 x 160 tiles (N a multiple of 160), else 128 x 208 (N of 208): two
+    // blocks of eight waves per CU, so that one's GELUs run beside the other's
+    // products (second layer at 200003 cells 372 us; 256 x 160 tiles on three stages, one
+    // block per CU, 417; 256 x 272 on two 389; four waves 380)
     const long mt = (g.M + 255) / 256;
-    if (g.N % 160 == 0 && mt * (g.N / 160) >= 512) return gemm8_dma16_cfg<8, 2, 10>(g, epi, s);
+    if (g.N % 160 == 0 && mt * (g.N / 160) >= 512) return gemm8_dma16_cfg<8, 1, 10, 2>(g, epi, s);
     if (g.N % 208 == 0 && mt * 2 * (g.N / 208) >= 512) return gemm8_dma16_cfg<8, 1, 13>(g, epi, s);
   }
   if (g.tiled) {
