@@ -871,9 +871,10 @@ chem_status forward_small(ann_model *m, const InferWs &w, int64_t n, const ann::
 // that reads their first n rows
 chem_status forward_chunk(ann_model *m, const InferWs &w, int64_t n, int64_t ld, const double *T,
                           const double *p, const double *Y, float *U, int ldu, uint8_t *ood,
-                          float ood_margin, hipStream_t s, bool keep_h1 = false) {
+                          float ood_margin, hipStream_t s, bool keep_h1 = false,
+                          unsigned long long *zero = nullptr) {
   ann::FeatArgs fa{n, ld, T, p, Y, m->n_out, m->L[0].dinp, m->nm.mu_in, m->nm.sd_in,
-                   m->nm.lambda, w.X, ood, m->nm.lo, m->nm.hi, ood_margin};
+                   m->nm.lambda, w.X, ood, m->nm.lo, m->nm.hi, ood_margin, zero};
   chem_status st;
   if (!keep_h1 && small_path(m, w, n)) return forward_small(m, w, n, fa, U, ldu, s);
   if ((st = ann::features(fa, s)) != CHEM_OK) return st;
@@ -1089,9 +1090,6 @@ chem_status step_prepare(ann_model *m, int64_t n, bool fallback) {
 
 void release_graph(void *owner) { ((ann_model *)owner)->graph_refs--; }
 
-__global__ void k_zero_counter(unsigned long long *c) {
-  if (threadIdx.x == 0) *c = 0ull;
-}
 __global__ void k_add_counter(const unsigned long long *c, int64_t *total, int first) {
   if (threadIdx.x == 0) *total = (first ? 0 : *total) + (int64_t)*c;
 }
@@ -1185,13 +1183,13 @@ chem_status audit_prepare(ann_model *m, int64_t cap, float f) {
 }
 
 // The step over batch.n cells in chunks of w.cap, with the fallback list
-// fb_index (n entries, or null without fallback) and count w.fb_count.
+// fb_index (n entries, or null without fallback), its count w.fb_count[0] and the
+// fallback's queue w.fb_count[1] (both cleared by the first chunk's prologue).
 chem_status step_impl(ann_model *m, const chem_mech *mech, chem_batch batch, double dt, double *T,
                       const double *p, double *Y, double *RR, uint8_t *flags,
                       int64_t *n_fallback, const ann_step_opts &o, const StepOpts &fo,
                       const InferWs &w, int32_t *fb_index, hipStream_t s) {
   chem_status st;
-  hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(64), 0, s, w.fb_count);
   // a step other than the one the network was trained for: every cell falls back
   const bool dt_mismatch = fabs(dt - m->nm.dt_model) > 1e-6 * m->nm.dt_model;
   const bool audit = o.audit_fraction > 0.0f;
@@ -1212,7 +1210,7 @@ chem_status step_impl(ann_model *m, const chem_mech *mech, chem_batch batch, dou
       if ((st = ann::audit_gather(aa, s)) != CHEM_OK) return st;
     }
     st = forward_chunk(m, w, nc, batch.ld, T + c0, p + c0, Y + c0, w.U, uw(m), w.ood,
-                       o.ood_margin, s);
+                       o.ood_margin, s, false, c0 == 0 ? w.fb_count : nullptr);
     if (st != CHEM_OK) return st;
     ann::PostArgs pa{};
     pa.n = nc;
@@ -1248,7 +1246,7 @@ chem_status step_impl(ann_model *m, const chem_mech *mech, chem_batch batch, dou
   }
   if (o.fallback) {
     st = launch_step(mech, batch.n, batch.ld, dt, nullptr, T, p, Y, RR, nullptr, nullptr, fo,
-                     fb_index, s, w.fb_count, flags);
+                     fb_index, s, w.fb_count, flags, nullptr, nullptr, 0, w.fb_count + 1);
     if (st != CHEM_OK) return st;
   }
   if (n_fallback) hipLaunchKernelGGL(k_add_counter, dim3(1), dim3(64), 0, s, w.fb_count,

@@ -146,7 +146,9 @@ struct FeatArgs {
   uint8_t *ood;
   const float *lo, *hi;
   float ood_margin;
+  unsigned long long *zero;  // optional: ZERO_COUNTERS counters to clear
 };
+constexpr int ZERO_COUNTERS = 2;
 chem_status features(const FeatArgs &a, hipStream_t s);
 
 // Prologue and first layer of a small batch (see k_feat_l1): n_in <= 32 inputs, nk

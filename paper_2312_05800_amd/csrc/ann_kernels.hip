@@ -1623,6 +1623,7 @@ __device__ __forceinline__ bool ood_feature(const FeatArgs &a, int j, float x) {
 // batch of 8192 cells fills 128 blocks instead of 32).
 template <int DINP, int BLK>
 __global__ __launch_bounds__(BLK) void k_features(FeatArgs a) {
+  if (a.zero && blockIdx.x == 0 && threadIdx.x < ZERO_COUNTERS) a.zero[threadIdx.x] = 0;
   constexpr int CH = DINP > 0 ? DINP / 8 : 1;  // 16-byte chunks per row
   __shared__ uint4 stage[DINP > 0 ? BLK * (CH + 1) : 1];
   const int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x;
@@ -1747,6 +1748,8 @@ __global__ __launch_bounds__(256) void k_feat_l1(FeatL1Args a) {
   __shared__ __attribute__((aligned(16))) u16 xs[FL1_CELLS * LW];
   __shared__ unsigned char out_s[4][FL1_CELLS];
   const FeatArgs &f = a.f;
+  if (f.zero && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < ZERO_COUNTERS)
+    f.zero[threadIdx.x] = 0;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t c0 = (int64_t)blockIdx.x * FL1_CELLS;

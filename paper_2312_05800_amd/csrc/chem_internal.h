@@ -274,13 +274,15 @@ int group_size(int n);
 size_t step_lds_bytes(const chem_mech *m, int G);
 // resident integrator wavefronts per CU that the LDS allows (1..32)
 int max_waves_per_cu(size_t sh);
+// queue: the cell queue's counter, cleared by the caller; null: the mechanism's own, cleared
+// by a launch before the integrator's.
 chem_status launch_step(const chem_mech *m, int64_t n, int64_t ld, double dt,
                         const double *dt_cell, double *T, const double *p, double *Y,
                         double *RR, double *h_hint, int32_t *stats, const StepOpts &o,
                         const int32_t *index, hipStream_t s,
                         const unsigned long long *n_dev = nullptr, uint8_t *flags = nullptr,
                         const chem_set *sets = nullptr, const int64_t *set_off = nullptr,
-                        int n_sets = 0);
+                        int n_sets = 0, unsigned long long *queue = nullptr);
 // Offsets and total cell count of a device set table (see k_set_offsets).
 chem_status launch_set_offsets(const chem_set *sets, int n_sets, int64_t *off,
                                unsigned long long *total, int32_t *n_bad, hipStream_t s);

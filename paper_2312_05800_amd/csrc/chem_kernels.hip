@@ -1290,9 +1290,11 @@ chem_status launch_step(const chem_mech *m, int64_t N, int64_t ld, double dt,
                         const double *dt_cell, double *T, const double *p, double *Y, double *RR,
                         double *h_hint, int32_t *stats, const StepOpts &o, const int32_t *index,
                         hipStream_t s, const unsigned long long *n_dev, uint8_t *flags,
-                        const chem_set *sets, const int64_t *set_off, int n_sets) {
-  StepArgs A{N,       ld,    dt,          dt_cell, T,     p,    Y,       RR,     h_hint,
-             stats,   index, o,           m->counters, n_dev, flags, sets, set_off, n_sets};
+                        const chem_set *sets, const int64_t *set_off, int n_sets,
+                        unsigned long long *queue) {
+  StepArgs A{N,     ld,    dt,    dt_cell, T,    p,       Y,      RR,
+             h_hint, stats, index, o,       queue ? queue : m->counters, n_dev, flags, sets,
+             set_off, n_sets};
   const int G = m->tune_G ? m->tune_G : group_size(m->d.n);
   const int cpw = 64 / G;
   const size_t sh = step_lds_bytes(m, G);
@@ -1307,7 +1309,7 @@ chem_status launch_step(const chem_mech *m, int64_t N, int64_t ld, double dt,
   int64_t blocks = (int64_t)cus * per_cu;
   if (blocks > want) blocks = want;
   if (blocks < 1) return CHEM_OK;
-  hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, m->counters);
+  if (!queue) hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, m->counters);
   ProfScope prof(index ? "chem_step_fallback" : (sets ? "chem_step_sets" : "chem_step"), s);
   switch (G) {
     case 16:
