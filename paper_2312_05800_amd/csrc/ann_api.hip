@@ -1462,6 +1462,16 @@ TrainProduct tuned_product(const ann_model *m, int64_t B, int p, int S) {
     t.g.tile = m->tt_tile[p];
     t.g.bk = m->tt_bk[p];
   }
+  // the first layer's pre-activations are not kept where its data gradient computes them again
+  if (p == 8 && m->L[0].dinp == 32 && ann::gemm_col_parts(t.g) > 0) {
+    t.g.Z = nullptr;
+    t.g.X1 = m->tX;
+    t.g.W1 = m->Wb[0];
+    t.g.b1 = m->bm[0];
+    t.g.gW1 = (long)layer_elems(m->L[0]);
+    t.g.gb1 = m->L[0].doutp;
+  }
+  if (p == 0 && tuned_product(m, B, 8, 1).g.X1) t.g.Z = nullptr;
   return t;
 }
 

@@ -68,6 +68,11 @@ struct GemmArgs {
   // tile, [gemm_col_parts() row tiles][N] (group z at + z gcol)
   double *colsum;
   long gcol;
+  // and, into the first layer (Z null): its pre-activations are computed again, W1 X + b1, from
+  // the inputs X1 [M][32] (shared by the groups), W1 [N][32] and b1 (group z at + z gW1, + z gb1)
+  const u16 *X1, *W1;
+  const float *b1;
+  long gW1, gb1;
   // grouped product (the networks of a per-species ensemble, one per
   // blockIdx.z): group z reads A + z gA, B + z gB, bias + z gbias and writes
   // Cb + z gcb, Cf + z gcf, Z + z gz (element strides; 0 = shared operand).

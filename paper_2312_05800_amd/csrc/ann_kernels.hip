@@ -376,6 +376,8 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_dma16(GemmArgs g) {
     if (g.Cf) g.Cf += z * g.gcf;
     if (g.Z) g.Z += z * g.gz;
     if (g.colsum) g.colsum += z * g.gcol;
+    if (g.W1) g.W1 += z * g.gW1;
+    if (g.b1) g.b1 += z * g.gb1;
   }
   constexpr int BK = 32, NW = WM * WN;
   constexpr int BM = WM * TM16 * 16, BN = WN * TN16 * 16;
@@ -598,15 +600,38 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_dma16(GemmArgs g) {
   if constexpr (EPI == EPI_GELUGRAD) {
     // d = v GELU'(z), stored in BF16 and summed over the tile's cells (the bias
     // gradient's partial sums): in FP64 over the lane's cells, then, through the
-    // idle ring, over the lanes'.
+    // idle ring, over the lanes'.  z is read, or, into the first layer, computed
+    // again by the forward pass's one MFMA a tile: 16 bytes a lane for the inputs of
+    // a row of tiles and for the weights of a column instead of 16 for every tile.
     static_assert(WM * 16 * BN * 8 <= (int)sizeof(S), "the column sums fit the ring");
     float4 z[TN16][TM16];
-#pragma unroll
-    for (int j = 0; j < TN16; ++j) {
-      const long cj = n0 + (wn * TN16 + j) * 16;
+    if (g.X1) {
+      bf16x8 xf[TM16];
 #pragma unroll
       for (int i = 0; i < TM16; ++i)
-        if (cj < g.N) z[j][i] = *(const float4 *)(g.Z + (live[i] ? rb[i] : m0) * g.ldz + hf + cj);
+        xf[i] = *(const bf16x8 *)(g.X1 + (live[i] ? rb[i] : m0) * 32 + 2 * hf);
+#pragma unroll
+      for (int j = 0; j < TN16; ++j) {
+        const long cj = n0 + (wn * TN16 + j) * 16;
+        if (cj >= g.N) break;
+        const bf16x8 wf = *(const bf16x8 *)(g.W1 + (cj + (lane & 15)) * 32 + 2 * hf);
+        const float4 b = *(const float4 *)(g.b1 + cj + hf);
+#pragma unroll
+        for (int i = 0; i < TM16; ++i) {
+          const f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              wf, xf[i], (f32x4){0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+          z[j][i] = make_float4(a[0] + b.x, a[1] + b.y, a[2] + b.z, a[3] + b.w);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < TN16; ++j) {
+        const long cj = n0 + (wn * TN16 + j) * 16;
+#pragma unroll
+        for (int i = 0; i < TM16; ++i)
+          if (cj < g.N)
+            z[j][i] = *(const float4 *)(g.Z + (live[i] ? rb[i] : m0) * g.ldz + hf + cj);
+      }
     }
     asm volatile("s_barrier" : : : "memory");  // every wave is done with the ring
     double *const cs = (double *)S;            // [WM 16][BN]
