@@ -210,6 +210,9 @@ def sampled_labels(P, mech, gm, dev, args):
     Yed = torch.from_numpy(Ye[:, None].copy()).to(dev)
     st = torch.zeros((3, 1), dtype=torch.int32, device=dev)
     P.chem_step(gm, 1e-2, Ted, ped, Yed, stats=st)
+    # traces that started from exactly zero end within rounding of it (1e-34), of
+    # either sign; one negative would have the filter drop the whole mixing line
+    Yed.clamp_(min=0.0)
     Ta, pa, Ya = chemgen.air_state(mech)
     end_eq = torch.cat([Ted, ped, Yed[:, 0]])
     end_air = torch.from_numpy(np.concatenate([[Ta, pa], Ya])).to(dev)
