@@ -52,6 +52,9 @@ struct DevMech {
   const PostPack *pp;  // [KMAX + 1], the entries past K null species
 };
 constexpr int RATES_CHUNK = 32, RATES_PER_WAVE = 4;
+constexpr int RATES_THREADS = 64 * (RATES_CHUNK / RATES_PER_WAVE);  // for 64 cells
+// threads a launch may have in the x direction of its grid
+constexpr int64_t GRID_THREADS = ((int64_t)1 << 32) - 1;
 
 // What k_rates_cells reads of a reaction, contiguous for the scalar cache.
 struct RxnPack {

@@ -1193,8 +1193,8 @@ chem_status launch_rates(const chem_mech *m, int64_t N, int64_t ld, const double
   // one cell per lane from 128 blocks of 64 cells on (16 000 CH4/air cells: 22
   // against 34 us with a lane group per cell, 2^20: 0.68 against 1.60 ms);
   // below, the groups spread a batch over more waves (1000 cells: 18 against
-  // 20 us, 8000: 20 against 21).  2^30: the grid's limit.
-  if (N >= 8192 && N < ((int64_t)1 << 30))
+  // 20 us, 8000: 20 against 21), and beyond the grid's limit they walk it in strides.
+  if (N >= 8192 && (N + 63) / 64 * RATES_THREADS <= GRID_THREADS)
     return launch_rates_cells(m, N, ld, T, p, Y, wdot, dTdt, kfkr, s);
   const int G = group_size(m->d.n);
   const int cpw = 64 / G;

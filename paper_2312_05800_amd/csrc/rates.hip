@@ -24,8 +24,7 @@ namespace {
 
 constexpr double RG = 8.314462618;
 constexpr double PREF = 101325.0;
-constexpr int RC_WAVES = 8;
-constexpr int RC_THREADS = 64 * RC_WAVES;
+constexpr int RC_WAVES = RATES_THREADS / 64;
 
 // constants through the scalar cache: the index is wave-uniform and nothing
 // writes the tables while a kernel runs
@@ -44,9 +43,8 @@ struct RatesArgs {
 
 // J: species per wave (species w J + j of wave w)
 template <int J>
-__global__ __launch_bounds__(RC_THREADS) void k_rates_cells(DevMech M, RatesArgs a) {
+__global__ __launch_bounds__(RATES_THREADS) void k_rates_cells(DevMech M, RatesArgs a) {
   constexpr int KP = J * RC_WAVES, CH = RATES_CHUNK, PW = RATES_PER_WAVE;
-  static_assert(CH == PW * RC_WAVES, "each wave takes RATES_PER_WAVE reactions of a chunk");
   __shared__ double2 cg[KP + 1][64];   // (C, g/RT) of the species, then the empty slots' dummy
   __shared__ double q[2][CH + 1][64];  // rates of progress; row CH is zero
   __shared__ double red[3][RC_WAVES][64];
@@ -186,7 +184,7 @@ chem_status launch_rates_cells(const chem_mech *m, int64_t N, int64_t ld, const 
                                const double *p, const double *Y, double *wdot, double *dTdt,
                                double *kfkr, hipStream_t s) {
   RatesArgs a{N, ld, T, p, Y, wdot, dTdt, kfkr};
-  const dim3 grid((unsigned)((N + 63) / 64)), block(RC_THREADS);
+  const dim3 grid((unsigned)((N + 63) / 64)), block(RATES_THREADS);
   ProfScope prof("chem_rates", s);
   const int K = m->d.K;
   if (K <= 2 * RC_WAVES)
