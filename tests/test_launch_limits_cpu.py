@@ -39,7 +39,7 @@ SIZES = [1, 64, 8191, 8192, 8193, 1 << 20, (1 << 29) - 65, (1 << 29) - 64, (1 <<
          (1 << 30) - 1, 1 << 30, (1 << 32) - 256, (1 << 32) - 255, 1 << 32, 1 << 40]
 
 
-@pytest.mark.parametrize("call", ["rates", "step"])
+@pytest.mark.parametrize("call", ["rates", "step", "sample"])
 def test_grids_within_a_launch(probe, call):
     for n, status, launches in probe(call, SIZES):
         assert status == 0 and launches
