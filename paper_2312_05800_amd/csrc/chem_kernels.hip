@@ -19,6 +19,8 @@
 #include <math.h>
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "chem_internal.h"
 
 namespace chem {
@@ -1156,6 +1158,15 @@ size_t lds_bytes(int R, int n, int cpw) {
   return (size_t)cpw * GLds<G>::doubles(R, n) * sizeof(double);
 }
 
+// LDS of one wave of k_rates, whose slices take the rate constants of all reactions.  A
+// mechanism that has too many for it is refused by chem_rates whatever the batch (the
+// cell-per-lane kernel could take it) and by chem_step, which a caller pairs with it.
+size_t rates_lds_bytes(const chem_mech *m, int G) {
+  const int cpw = 64 / G;
+  return G == 16 ? lds_bytes<16>(m->R, m->d.n, cpw)
+                 : (G == 32 ? lds_bytes<32>(m->R, m->d.n, cpw) : lds_bytes<64>(m->R, m->d.n, cpw));
+}
+
 chem_status check_lds(size_t sh, int *cus) {
   int dev = 0, maxsh = 0;
   CHEM_HIP(hipGetDevice(&dev));
@@ -1190,20 +1201,19 @@ int max_waves_per_cu(size_t sh) {
 chem_status launch_rates(const chem_mech *m, int64_t N, int64_t ld, const double *T,
                          const double *p, const double *Y, double *wdot, double *dTdt,
                          double *kfkr, hipStream_t s) {
+  const int G = group_size(m->d.n);
+  const size_t sh = rates_lds_bytes(m, G);
+  chem_status st = check_lds(sh, nullptr);
+  if (st != CHEM_OK) return st;
   // one cell per lane from 128 blocks of 64 cells on (16 000 CH4/air cells: 22
   // against 34 us with a lane group per cell, 2^20: 0.68 against 1.60 ms);
   // below, the groups spread a batch over more waves (1000 cells: 18 against
   // 20 us, 8000: 20 against 21), and beyond the grid's limit they walk it in strides.
   if (N >= 8192 && (N + 63) / 64 * RATES_THREADS <= GRID_THREADS)
     return launch_rates_cells(m, N, ld, T, p, Y, wdot, dTdt, kfkr, s);
-  const int G = group_size(m->d.n);
   const int cpw = 64 / G;
   int64_t blocks = (N + cpw - 1) / cpw;
   if (blocks > 65536) blocks = 65536;
-  size_t sh = G == 16 ? lds_bytes<16>(m->R, m->d.n, cpw)
-                      : (G == 32 ? lds_bytes<32>(m->R, m->d.n, cpw) : lds_bytes<64>(m->R, m->d.n, cpw));
-  chem_status st = check_lds(sh, nullptr);
-  if (st != CHEM_OK) return st;
   ProfScope prof("chem_rates", s);
   switch (G) {
     case 16:
@@ -1299,7 +1309,7 @@ chem_status launch_step(const chem_mech *m, int64_t N, int64_t ld, double dt,
   const int cpw = 64 / G;
   const size_t sh = step_lds_bytes(m, G);
   int cus = 0;
-  chem_status st = check_lds(sh, &cus);
+  chem_status st = check_lds(std::max(sh, rates_lds_bytes(m, G)), &cus);
   if (st != CHEM_OK) return st;
   // persistent grid: enough single-wave blocks to fill every CU's LDS, or
   // the tuned number of waves per CU

@@ -46,3 +46,13 @@ def test_grids_within_a_launch(probe, call):
         for name, grid, block in launches:
             assert grid[0] * block[0] < 1 << 32, (n, name, grid, block)
             assert grid[1] * block[1] < 1 << 32 and grid[2] * block[2] < 1 << 32
+
+
+# 4 cells a wave, each with 16 bytes a reaction: 1024 reactions fill 64 KB, 2560 160 KB
+@pytest.mark.parametrize("call", ["rates", "step"])
+@pytest.mark.parametrize("lds,most", [(65536, 1024 - 32), (163840, 2560 - 32)])
+def test_too_many_reactions_refused_at_every_size(probe, call, lds, most):
+    sizes = [1, 8191, 8192, 1 << 20]
+    assert all(st == 0 for _, st, _ in probe(call, sizes, reactions=most, lds=lds))
+    for n, st, launches in probe(call, sizes, reactions=most + 33, lds=lds):
+        assert st == 6 and not launches, (n, st, launches)  # CHEM_EUNSUPPORTED
