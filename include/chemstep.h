@@ -334,11 +334,15 @@ int64_t ann_num_steps(const ann_model *m);
  * step is launch- and latency-bound at training batches, so the best tiling
  * differs from the inference rule): each of the eleven products of a step at
  * batch B (forward, weight gradient and data gradient of every layer; an
- * ensemble's members grouped) is timed with every generic tiling (128 x 128,
- * 128 x 32, 64 x 64, 128 x 64 blocks; 32- or 64-wide K-steps) and, for the
- * weight gradients, every split along the batch the workspace holds (1..16),
- * on the model's training workspace; the fastest stays in the model for later
- * ann_train_step calls at batch B (other batches keep the built-in rules).
+ * ensemble's members grouped) is timed as the step runs it with its built-in
+ * tiling and with every generic one (128 x 128, 128 x 32, 64 x 64, 128 x 64
+ * blocks; 32- or 64-wide K-steps) and, for the weight gradients, every split
+ * along the batch the workspace holds (1..16), on the model's training
+ * workspace, with what the choice adds elsewhere: adding the ranges of a
+ * split, and, for a data gradient in a generic tiling, the bias gradient's
+ * pass over its output and the pre-activations it reads.  The fastest stays
+ * in the model for later ann_train_step calls at batch B (other batches keep
+ * the built-in rules).
  * ms_default / ms_tuned (host, nullable) receive the summed product times
  * with the built-in rules and the chosen tilings.  With CHEM_AUTOTUNE_CACHE
  * naming a file, a result stored there for this device, network and batch

@@ -1456,21 +1456,32 @@ int train_split(const ann_model *m, int64_t B, int l) {
   return wgrad_splits(m->L[l].doutp, m->L[l].dinp, B, m->G);
 }
 
-TrainProduct tuned_product(const ann_model *m, int64_t B, int p, int S) {
+// The products as a step runs them.  The first layer's pre-activations are not kept where
+// its data gradient (product 8) is in a form that computes them again.
+void recompute_z1(const ann_model *m, TrainProduct *t) {
+  t->g.Z = nullptr;
+  t->g.X1 = m->tX;
+  t->g.W1 = m->Wb[0];
+  t->g.b1 = m->bm[0];
+  t->g.gW1 = (long)layer_elems(m->L[0]);
+  t->g.gb1 = m->L[0].doutp;
+}
+bool recomputes_z1(const ann_model *m, const TrainProduct &p8) {
+  return m->L[0].dinp == 32 && ann::gemm_col_parts(p8.g) > 0;
+}
+
+TrainProduct tiled_product(const ann_model *m, int64_t B, int p, int S, int tile, int bk) {
   TrainProduct t = train_product(m, B, p, S);
-  if (m->tt_B == B) {
-    t.g.tile = m->tt_tile[p];
-    t.g.bk = m->tt_bk[p];
-  }
-  // the first layer's pre-activations are not kept where its data gradient computes them again
-  if (p == 8 && m->L[0].dinp == 32 && ann::gemm_col_parts(t.g) > 0) {
-    t.g.Z = nullptr;
-    t.g.X1 = m->tX;
-    t.g.W1 = m->Wb[0];
-    t.g.b1 = m->bm[0];
-    t.g.gW1 = (long)layer_elems(m->L[0]);
-    t.g.gb1 = m->L[0].doutp;
-  }
+  t.g.tile = tile;
+  t.g.bk = bk;
+  if (p == 8 && recomputes_z1(m, t)) recompute_z1(m, &t);
+  return t;
+}
+
+TrainProduct tuned_product(const ann_model *m, int64_t B, int p, int S) {
+  const bool tuned = m->tt_B == B;
+  TrainProduct t =
+      tiled_product(m, B, p, S, tuned ? m->tt_tile[p] : 0, tuned ? m->tt_bk[p] : 0);
   if (p == 0 && tuned_product(m, B, 8, 1).g.X1) t.g.Z = nullptr;
   return t;
 }
@@ -1656,20 +1667,8 @@ extern "C" chem_status ann_autotune_train(ann_model *m, int64_t B, double *ms_de
   }
   const int G = m->G;
   constexpr int REPS = 4;
-  // one product (and its split-K reduction) with the given tiling: its
-  // average over REPS launches after a warm-up, or infinity if it cannot run
-  auto timed = [&](int p, int tile, int bkv, int S) -> float {
-    TrainProduct t = train_product(m, B, p, S);
-    t.g.tile = tile;
-    t.g.bk = bkv;
-    const int l = p - 4;
-    const long wn = p >= 4 && p < 8 ? (long)m->L[l].doutp * m->L[l].dinp : 0;
-    auto once = [&]() -> chem_status {
-      chem_status r = ann::gemm(t.g, t.AK, t.BK, t.epi, s, "autotune");
-      if (r == CHEM_OK && S > 1)
-        r = ann::sum_splits((long)G * wn, S, m->wg_part[l], (long)G * wn, m->gW[l], s);
-      return r;
-    };
+  // average of REPS calls after a warm-up, or infinity if one fails
+  auto average = [&](auto once) -> float {
     if (once() != CHEM_OK) return INFINITY;
     if (hipEventRecord(ea, s) != hipSuccess) return INFINITY;
     for (int r = 0; r < REPS; ++r)
@@ -1680,41 +1679,105 @@ extern "C" chem_status ann_autotune_train(ann_model *m, int64_t B, double *ms_de
       return INFINITY;
     return ms / REPS;
   };
+  // a product with, for a data gradient whose tiling does not leave them, the pass
+  // over its output for the bias gradient
+  auto timed = [&](int p, const TrainProduct &t) -> float {
+    const int l = p - 8;
+    const bool sums = p >= 8 && ann::gemm_col_parts(t.g) == 0;
+    return average([&]() -> chem_status {
+      chem_status r = ann::gemm(t.g, t.AK, t.BK, t.epi, s, "autotune");
+      int P = 0;
+      if (r == CHEM_OK && sums)
+        r = ann::colsum(B, m->L[l].doutp, m->tGf[l], m->L[l].doutp, m->col_part[l], &P, s, G,
+                        (long)B * m->L[l].doutp);
+      return r;
+    });
+  };
+  // the step's last launch with the S ranges of layer l alone
+  auto finish_ms = [&](int l, int S) -> float {
+    ann::FinishTable f{};
+    f.lpart = m->loss_part;
+    f.loss = (float *)m->loss_part;
+    for (int q = 0; q < 4; ++q) f.S[q] = 1;
+    f.S[l] = S;
+    f.part[l] = S > 1 ? m->wg_part[l] : m->gW[l];
+    f.gW[l] = m->gW[l];
+    f.wn[l] = (int64_t)G * layer_elems(m->L[l]);
+    return average([&]() { return ann::finish(f, G, s); });
+  };
+  struct Choice {
+    float ms = INFINITY;
+    int tile = 0, bk = 0, S = 1;
+  };
+  // the fastest generic tiling of product p, its pre-activations kept or not
+  auto generic = [&](int p, int S, bool z, float extra, Choice *best) {
+    for (int tile = 1; tile <= ann::GEMM_TILES; ++tile)
+      for (int bkv : {32, 64}) {
+        TrainProduct t = tiled_product(m, B, p, S, tile, bkv);
+        if (!z) t.g.Z = nullptr;
+        const float ms = timed(p, t) + extra;
+        if (ms < best->ms) *best = {ms, tile, bkv, S};
+      }
+  };
   double tot0 = 0.0, tot1 = 0.0;
-  int tl[11], bk[11], sp[4];
-  for (int p = 0; p < 11; ++p) {
+  Choice c[11];
+  int bad = -1;
+  // products 0 and 8 belong together: with the built-in product 8, product 0 does not
+  // store what a generic one reads
+  const TrainProduct p8 = tiled_product(m, B, 8, 1, 0, 0);
+  const bool again = recomputes_z1(m, p8);
+  Choice keep;  // product 0 with its pre-activations stored
+  for (int p = 0; p < 11 && bad < 0; ++p) {
     const bool wg = p >= 4 && p < 8;
     const int l = wg ? p - 4 : 0;
     const int S0 = wg ? wgrad_splits(m->L[l].doutp, m->L[l].dinp, B, G) : 1;
-    const float t0 = timed(p, 0, 0, S0);
+    TrainProduct t = tiled_product(m, B, p, S0, 0, 0);
+    if (p == 0) {
+      keep = {timed(0, t), 0, 0, 1};
+      generic(0, 1, true, 0.0f, &keep);
+      if (again) t.g.Z = nullptr;
+    }
+    const float fin1 = wg ? finish_ms(l, 1) : 0.0f;
+    auto fin = [&](int S) { return S > 1 ? std::max(0.0f, finish_ms(l, S) - fin1) : 0.0f; };
+    const float t0 = timed(p, t) + fin(S0);
     if (!(t0 < INFINITY)) {
-      (void)hipEventDestroy(ea);
-      (void)hipEventDestroy(eb);
-      set_error("ann_autotune_train: the built-in tiling of product %d failed to run", p);
-      return CHEM_EHIP;
+      bad = p;
+      break;
     }
-    float best = t0;
-    int bt = 0, bb = 0, bs = S0;
+    c[p] = {t0, 0, 0, S0};
     for (int S = 1; S <= (wg ? 16 : 1); S *= 2) {
-      if (wg) {
-        if (B % (32L * S) != 0 || S > m->wg_most[l]) continue;
+      if (wg && (B % (32L * S) != 0 || S > m->wg_most[l])) continue;
+      const float extra = wg ? fin(S) : 0.0f;
+      if (wg && S != S0) {  // the built-in tiling with other ranges
+        const float ms = timed(p, tiled_product(m, B, p, S, 0, 0)) + extra;
+        if (ms < c[p].ms) c[p] = {ms, 0, 0, S};
       }
-      for (int tile = 1; tile <= ann::GEMM_TILES; ++tile)
-        for (int bkv : {32, 64}) {
-          const float t = timed(p, tile, bkv, S);
-          if (t < best) {
-            best = t;
-            bt = tile;
-            bb = bkv;
-            bs = S;
-          }
+      if (p == 8 && again) {
+        Choice g;
+        generic(8, 1, true, 0.0f, &g);
+        if (g.ms + keep.ms < c[8].ms + c[0].ms) {
+          tot1 += (double)keep.ms - c[0].ms;
+          c[0] = keep;
+          c[8] = g;
         }
+      } else {
+        generic(p, S, !(p == 0 && again), extra, &c[p]);
+      }
     }
-    tl[p] = bt;
-    bk[p] = bb;
-    if (wg) sp[l] = bs;
     tot0 += t0;
-    tot1 += best;
+    tot1 += c[p].ms;
+  }
+  if (bad >= 0) {
+    (void)hipEventDestroy(ea);
+    (void)hipEventDestroy(eb);
+    set_error("ann_autotune_train: the built-in tiling of product %d failed to run", bad);
+    return CHEM_EHIP;
+  }
+  int tl[11], bk[11], sp[4];
+  for (int p = 0; p < 11; ++p) {
+    tl[p] = c[p].tile;
+    bk[p] = c[p].bk;
+    if (p >= 4 && p < 8) sp[p - 4] = c[p].S;
   }
   (void)hipEventDestroy(ea);
   (void)hipEventDestroy(eb);

@@ -206,9 +206,6 @@ chem_status l1_grad_members(int64_t n, int G, int ldu, long gu, const float *U, 
 // dst[i * ldd] = src[i * lds] for i < n (one output column of an ensemble
 // member into the ensemble's output)
 chem_status take_col(int64_t n, const float *src, int lds, float *dst, int ldd, hipStream_t s);
-// out[i] = sum_{s < S} part[s * stride + i], in order of s
-chem_status sum_splits(int64_t n, int S, const float *part, long stride, float *out,
-                       hipStream_t s);
 // The end of a training step (see k_finish), layer by layer; G networks.
 struct AdamOpts {
   float lr, b1, b2, eps, bc1, bc2;

@@ -2059,14 +2059,6 @@ __global__ void k_colsum_part(int64_t M, int N, const float *X, long ldx, double
   part[(int64_t)q * N + j] = s;
 }
 
-__global__ void k_sum_splits(int64_t n, int S, const float *part, long stride, float *out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = part[i];
-  for (int q = 1; q < S; ++q) s += part[(int64_t)q * stride + i];
-  out[i] = s;
-}
-
 __device__ __forceinline__ u16 adam_elem(float gi, float *W, float *m, float *v, const AdamOpts &o) {
   // the roundings are spelled out: left to the compiler, which product joins the
   // sum's FMA would differ from kernel to kernel, and a training run amplifies it
@@ -2822,7 +2814,7 @@ bool ring_dgrad_ok(const GemmArgs &g) {
 }
 
 // Weight gradients: A [K][M], B [K][N], K the batch in ksplit ranges (whose partial products
-// sum_splits adds in order, so that the ranges are part of the result).  160 x 160 tiles on
+// k_finish adds in order, so that the ranges are part of the result).  160 x 160 tiles on
 // two stages (two or three blocks to a CU) stream the fewest bytes per product; where they
 // are too few, or a side is 32, 64 x 64 ones.  M = 800, N = 1600 in 16 ranges of batch 2048, 8192:
 // 24.5, 40 us (k_gemm 36.7, 75.7); 416 x 800 10.3, 16.3 (16.8, 28.8); 1600 x 32 4.7, 7.4 (6.3,
@@ -3128,13 +3120,6 @@ chem_status colsum(int64_t M, int N, const float *X, long ldx, double *part, int
   const unsigned G = groups > 1 ? (unsigned)groups : 1u;
   hipLaunchKernelGGL(k_colsum_part, dim3(nblk(N, 64), *P, G), dim3(64), 0, s, M, N, X, ldx, part,
                      gx);
-  CHEM_HIP(hipGetLastError());
-  return CHEM_OK;
-}
-
-chem_status sum_splits(int64_t n, int S, const float *part, long stride, float *out,
-                       hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_splits, dim3(nblk(n, 256)), dim3(256), 0, s, n, S, part, stride, out);
   CHEM_HIP(hipGetLastError());
   return CHEM_OK;
 }

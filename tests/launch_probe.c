@@ -1,7 +1,9 @@
 /* Calls the library with a HIP runtime of its own that only records the launches, so that the
  * launch shapes of batches no host could hold can be checked without a GPU.  Test code only.
- *   launch_probe LIB LDS_BYTES REACTIONS {rates|sample|step} N...
+ *   launch_probe LIB LDS_BYTES REACTIONS {rates|sample|step|autotune_train} N...
  * prints per N a line "call N STATUS" after its launches, "KERNEL gx gy gz bx by bz" each.
+ * Time, as events see it, passes by launches: LAUNCH_COSTS names parts of kernels' names and the
+ * milliseconds of each ("k_a=1.5,k_b=2", 0 for the others).
  * Built with -rdynamic: the functions below stand in for the runtime's of the same names. */
 #include <dlfcn.h>
 #include <stdio.h>
@@ -17,6 +19,20 @@ static long lds_bytes;
 static dim3 cfg_grid, cfg_block;
 static struct { const void *host; const char *name; } kernels[1024];
 static int n_kernels;
+static float now_ms;
+
+static float cost_of(const char *kernel) {
+  const char *c = getenv("LAUNCH_COSTS");
+  while (c && *c) {
+    const char *eq = strchr(c, '='), *end = strchr(c, ',');
+    char part[128] = "";
+    if (!eq || eq - c >= (long)sizeof(part)) break;
+    memcpy(part, c, eq - c);
+    if (strstr(kernel, part)) return strtof(eq + 1, NULL);
+    c = end ? end + 1 : NULL;
+  }
+  return 0.0f;
+}
 
 void **__hipRegisterFatBinary(const void *data) { static void *h; (void)data; return &h; }
 void __hipUnregisterFatBinary(void **m) { (void)m; }
@@ -49,6 +65,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
   const char *name = "?";
   for (int i = 0; i < n_kernels; ++i)
     if (kernels[i].host == f) name = kernels[i].name;
+  now_ms += cost_of(name);
   printf("%s %u %u %u %u %u %u\n", name, g.x, g.y, g.z, b.x, b.y, b.z);
   return 0;
 }
@@ -67,6 +84,15 @@ hipError_t hipMalloc(void **p, size_t n) { *p = malloc(n); return *p ? 0 : 2; }
 hipError_t hipFree(void *p) { free(p); return 0; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, int k) { (void)k; memcpy(d, s, n); return 0; }
 hipError_t hipMemset(void *d, int v, size_t n) { memset(d, v, n); return 0; }
+hipError_t hipMemsetAsync(void *d, int v, size_t n, void *s) { (void)s; return hipMemset(d, v, n); }
+hipError_t hipEventCreate(void **e) { *e = calloc(1, sizeof(float)); return *e ? 0 : 2; }
+hipError_t hipEventDestroy(void *e) { free(e); return 0; }
+hipError_t hipEventRecord(void *e, void *s) { (void)s; *(float *)e = now_ms; return 0; }
+hipError_t hipEventSynchronize(void *e) { (void)e; return 0; }
+hipError_t hipEventElapsedTime(float *ms, void *a, void *b) { *ms = *(float *)b - *(float *)a; return 0; }
+hipError_t hipStreamSynchronize(void *s) { (void)s; return 0; }
+hipError_t hipDeviceSynchronize(void) { return 0; }
+hipError_t hipGetDevicePropertiesR0600(void *p, int d) { (void)p, (void)d; return 1; }
 
 int main(int argc, char **argv) {
   if (argc < 6) return 2;
@@ -112,6 +138,15 @@ int main(int argc, char **argv) {
     chem_status st = CHEM_EINVAL;
     if (!strcmp(argv[4], "rates")) st = rates(m, n, x, x, x, x, x, NULL, NULL);
     if (!strcmp(argv[4], "step")) st = step(m, n, 1e-6, NULL, x, x, x, NULL, NULL, NULL, NULL, NULL);
+    if (!strcmp(argv[4], "autotune_train")) {
+      chem_status (*make)(const ann_arch *, uint64_t, ann_model **) = dlsym(lib, "ann_create");
+      chem_status (*tune)(ann_model *, int64_t, double *, double *, void *) =
+          dlsym(lib, "ann_autotune_train");
+      const ann_arch arch = {4, 2, {160, 96, 64}, 0, 1};
+      ann_model *net = NULL;
+      st = make(&arch, 1, &net);
+      if (st == CHEM_OK) st = tune(net, n.n, NULL, NULL, NULL);
+    }
     if (!strcmp(argv[4], "sample")) st = sample(m, n, x, x, x, x, NULL, NULL, NULL, &o, x, x, x, (uint8_t *)x, NULL);
     printf("call %lld %d\n", (long long)n.n, (int)st);
   }
