@@ -1628,8 +1628,8 @@ extern "C" chem_status ann_autotune_train(ann_model *m, int64_t B, double *ms_de
   if ((st = grow_train(m, B)) != CHEM_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   char kb[256];
-  snprintf(kb, sizeof(kb), "ann_train %s in=%d hidden=%d,%d,%d out=%d members=%d B=%lld",
-           tune_device_key().c_str(), m->n_in, m->L[0].dout, m->L[1].dout, m->L[2].dout,
+  snprintf(kb, sizeof(kb), "ann_train v%d %s in=%d hidden=%d,%d,%d out=%d members=%d B=%lld",
+           TUNE_VERSION, tune_device_key().c_str(), m->n_in, m->L[0].dout, m->L[1].dout, m->L[2].dout,
            m->n_out, m->G, (long long)B);
   std::string cached;
   if (tune_cache_get(kb, &cached)) {

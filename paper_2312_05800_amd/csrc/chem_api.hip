@@ -679,9 +679,9 @@ extern "C" chem_status chem_autotune(chem_mech *m, chem_batch sample, double dt,
   // a shape measured before for this device, mechanism, step and controls
   // (CHEM_AUTOTUNE_CACHE) is taken without timing
   char kb[256];
-  snprintf(kb, sizeof(kb), "chem_step %s K=%d R=%d mech=%016llx dt=%.6g rtol=%.3g atol=%.3g",
-           tune_device_key().c_str(), K, m->R, (unsigned long long)m->digest, dt, o.rtol,
-           o.atol_Y);
+  snprintf(kb, sizeof(kb), "chem_step v%d %s K=%d R=%d mech=%016llx dt=%.6g rtol=%.3g atol=%.3g",
+           TUNE_VERSION, tune_device_key().c_str(), K, m->R, (unsigned long long)m->digest, dt,
+           o.rtol, o.atol_Y);
   std::string cached;
   if (tune_cache_get(kb, &cached)) {
     int cg = 0, cw = 0;

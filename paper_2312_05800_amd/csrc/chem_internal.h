@@ -202,6 +202,9 @@ void set_error(const char *fmt, ...);
 // Tuning results kept between runs in the text file named by the environment
 // variable CHEM_AUTOTUNE_CACHE (no file: nothing is kept): one line
 // "key = value" per tuned problem, the last write of a key winning.
+// The version in the keys is that of the kernels the results were measured on: raised with a
+// change of k_step or of the training products, so that older results are measured again.
+constexpr int TUNE_VERSION = 2;
 bool tune_cache_get(const std::string &key, std::string *value);
 void tune_cache_put(const std::string &key, const std::string &value);
 // The current device's architecture name and compute-unit count, for keys.

@@ -1,6 +1,6 @@
 /* Calls the library with a HIP runtime of its own that only records the launches, so that the
  * launch shapes of batches no host could hold can be checked without a GPU.  Test code only.
- *   launch_probe LIB LDS_BYTES REACTIONS {rates|sample|step|autotune_train} N...
+ *   launch_probe LIB LDS_BYTES REACTIONS {rates|sample|step|autotune|autotune_train} N...
  * prints per N a line "call N STATUS" after its launches, "KERNEL gx gy gz bx by bz" each.
  * Time, as events see it, passes by launches: LAUNCH_COSTS names parts of kernels' names and the
  * milliseconds of each ("k_a=1.5,k_b=2", 0 for the others).
@@ -85,6 +85,14 @@ hipError_t hipFree(void *p) { free(p); return 0; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, int k) { (void)k; memcpy(d, s, n); return 0; }
 hipError_t hipMemset(void *d, int v, size_t n) { memset(d, v, n); return 0; }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, void *s) { (void)s; return hipMemset(d, v, n); }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) {
+  (void)d, (void)s, (void)n, (void)k, (void)st;
+  return 0;
+}
+hipError_t hipMemcpy2DAsync(void *d, size_t dp, const void *s, size_t sp, size_t w, size_t h, int k, void *st) {
+  (void)d, (void)dp, (void)s, (void)sp, (void)w, (void)h, (void)k, (void)st;
+  return 0;
+}
 hipError_t hipEventCreate(void **e) { *e = calloc(1, sizeof(float)); return *e ? 0 : 2; }
 hipError_t hipEventDestroy(void *e) { free(e); return 0; }
 hipError_t hipEventRecord(void *e, void *s) { (void)s; *(float *)e = now_ms; return 0; }
@@ -138,6 +146,12 @@ int main(int argc, char **argv) {
     chem_status st = CHEM_EINVAL;
     if (!strcmp(argv[4], "rates")) st = rates(m, n, x, x, x, x, x, NULL, NULL);
     if (!strcmp(argv[4], "step")) st = step(m, n, 1e-6, NULL, x, x, x, NULL, NULL, NULL, NULL, NULL);
+    if (!strcmp(argv[4], "autotune")) {
+      chem_status (*tune)(chem_mech *, chem_batch, double, const double *, const double *,
+                          const double *, const chem_step_opts *, void *, chem_tuning *) =
+          dlsym(lib, "chem_autotune");
+      st = tune(m, n, 1e-6, x, x, x, NULL, NULL, NULL);
+    }
     if (!strcmp(argv[4], "autotune_train")) {
       chem_status (*make)(const ann_arch *, uint64_t, ann_model **) = dlsym(lib, "ann_create");
       chem_status (*tune)(ann_model *, int64_t, double *, double *, void *) =
