@@ -371,12 +371,12 @@ chem_status ann_load(const char *path, ann_model **out);
 /* ------------------------------------------------------ launch autotuning
  * The persistent integrator's launch shape: lanes per cell (a power of two
  * >= K + 1, at most 64; a wavefront carries 64 / lanes cells) and resident
- * wavefronts per CU (each holds its cells' LDS slices; 0 = as many as the LDS
- * allows).  Per-cell results do not depend on the shape beyond the rounding
+ * wavefronts per CU (each holds its cells' LDS slices; 0 = as many as LDS and
+ * registers allow, and a larger number counts as that).  Per-cell results do not depend on the shape beyond the rounding
  * of wave-level reductions (well inside the step's error control). */
 typedef struct {
   int32_t lanes_per_cell; /* 0 = the smallest power of two >= K + 1 */
-  int32_t waves_per_cu;   /* 0 = LDS-limited maximum */
+  int32_t waves_per_cu;   /* 0 = as many as can be resident */
   double cells_per_s;     /* measured by chem_autotune (output only) */
 } chem_tuning;
 

@@ -701,7 +701,7 @@ extern "C" chem_status chem_autotune(chem_mech *m, chem_batch sample, double dt,
     }
   }
   // candidates: every usable lane group, and 1/4 .. 4/4 of the waves per CU
-  // its LDS allows
+  // that can be resident
   struct Cand {
     int G, w;
   };

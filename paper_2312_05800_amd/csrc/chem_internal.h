@@ -278,7 +278,9 @@ chem_status launch_rates_cells(const chem_mech *m, int64_t n, int64_t ld, const 
 int group_size(int n);
 // LDS bytes of one integrator wavefront with G lanes per cell
 size_t step_lds_bytes(const chem_mech *m, int G);
-// resident integrator wavefronts per CU that the LDS allows (1..32)
+// resident integrator wavefronts per CU: what the LDS allows, at most two a SIMD (k_step is
+// compiled for that many, and takes all of their registers)
+constexpr int STEP_WAVES_EU = 2;
 int max_waves_per_cu(size_t sh);
 // queue: the cell queue's counter, cleared by the caller; null: the mechanism's own, cleared
 // by a launch before the integrator's.

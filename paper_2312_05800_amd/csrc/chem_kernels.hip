@@ -1110,7 +1110,8 @@ __global__ __launch_bounds__(64) void k_rates(DevMech M, int64_t N, int64_t ld, 
 }
 
 template <int G>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step(DevMech M, StepArgs A) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(STEP_WAVES_EU, STEP_WAVES_EU)))
+void k_step(DevMech M, StepArgs A) {
   extern __shared__ double lds[];
   const int lane = threadIdx.x;
   const int g = lane / G, l = lane % G, lane_in_group = l;
@@ -1359,7 +1360,7 @@ size_t step_lds_bytes(const chem_mech *m, int G) {
 
 int max_waves_per_cu(size_t sh) {
   const int w = (int)((160 * 1024) / (sh > 0 ? sh : 1));
-  return w < 1 ? 1 : (w > 32 ? 32 : w);
+  return std::clamp(w, 1, 4 * STEP_WAVES_EU);
 }
 
 chem_status launch_rates(const chem_mech *m, int64_t N, int64_t ld, const double *T,
@@ -1475,8 +1476,8 @@ chem_status launch_step(const chem_mech *m, int64_t N, int64_t ld, double dt,
   int cus = 0;
   chem_status st = check_lds(std::max(sh, rates_lds_bytes(m, G)), &cus);
   if (st != CHEM_OK) return st;
-  // persistent grid: enough single-wave blocks to fill every CU's LDS, or
-  // the tuned number of waves per CU
+  // persistent grid: the single-wave blocks that a CU's LDS and registers hold, or the tuned
+  // number of waves per CU
   int per_cu = max_waves_per_cu(sh);
   if (m->tune_waves > 0 && m->tune_waves < per_cu) per_cu = m->tune_waves;
   int64_t want = (N + cpw - 1) / cpw;  // with n_dev, N is an upper bound

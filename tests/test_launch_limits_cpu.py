@@ -56,3 +56,11 @@ def test_too_many_reactions_refused_at_every_size(probe, call, lds, most):
     assert all(st == 0 for _, st, _ in probe(call, sizes, reactions=most, lds=lds))
     for n, st, launches in probe(call, sizes, reactions=most + 33, lds=lds):
         assert st == 6 and not launches, (n, st, launches)  # CHEM_EUNSUPPORTED
+
+
+def test_step_grid_can_be_resident(probe):
+    """The persistent grid: what the registers allow (two waves on each of a CU's four SIMDs), however
+    little LDS a mechanism needs."""
+    (_, status, launches), = probe("step", [1 << 20])
+    grid = [g for name, g, _ in launches if "k_step" in name]
+    assert status == 0 and grid == [(256 * 8, 1, 1)]
