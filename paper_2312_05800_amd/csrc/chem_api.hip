@@ -360,34 +360,10 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
     }
   rs_start.push_back((int)rs_row.size());
 
-  // what the digest that keys the tuning cache covers: the mechanism as described
-  Packer named;
-  named.add(W.data(), K * 8);
-  named.add(invW.data(), K * 8);
-  named.add(Tmid.data(), K * 8);
-  named.add(lo.data(), 7 * K * 8);
-  named.add(hi.data(), 7 * K * 8);
-  named.add(lnA.data(), R * 8);
-  named.add(bb.data(), R * 8);
-  named.add(EaR.data(), R * 8);
-  named.add(dn.data(), R * 8);
-  named.add(sp4.data(), R * sizeof(int4));
-  named.add(nu4.data(), R * sizeof(int4));
-  named.add(Mel.data(), Mel.size() * 8);
-  named.add(nh.data(), nh.size() * 8);
-  named.add(nhh.data(), nhh.size() * 8);
-  named.add(ns.data(), ns.size() * 8);
-  named.add(nsh.data(), nsh.size() * 8);
-  named.add(cpT.data(), cpT.size() * 8);
-  named.add(hT.data(), hT.size() * 8);
-  named.add(sT.data(), sT.size() * 8);
-  named.add(compd.data(), compd.size() * 8);
-
   Packer pk;
   size_t oW = pk.add(W.data(), K * 8), oiW = pk.add(invW.data(), K * 8),
-         oTm = pk.add(Tmid.data(), K * 8), oM = pk.add(Mel.data(), Mel.size() * 8),
-         onh = pk.add(nh.data(), nh.size() * 8), onhh = pk.add(nhh.data(), nhh.size() * 8),
-         ons = pk.add(ns.data(), ns.size() * 8), onsh = pk.add(nsh.data(), nsh.size() * 8),
+         oTm = pk.add(Tmid.data(), K * 8), onh = pk.add(nh.data(), nh.size() * 8),
+         onhh = pk.add(nhh.data(), nhh.size() * 8),
          ocpT = pk.add(cpT.data(), cpT.size() * 8), ohT = pk.add(hT.data(), hT.size() * 8),
          osT = pk.add(sT.data(), sT.size() * 8), ocd = pk.add(compd.data(), compd.size() * 8);
 
@@ -420,7 +396,18 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
     set_error("chem_mech_create: device allocation: %s", hipGetErrorString(e));
     return CHEM_ENOMEM;
   }
-  m->digest = fnv1a(named.buf.data(), named.buf.size());
+  // the mechanism as described, for the keys of stored launch shapes
+  const int32_t sizes[3] = {K, R, E};
+  uint64_t dg = fnv1a(sizes, sizeof(sizes));
+  dg = fnv1a(d->W, K * 8, dg);
+  dg = fnv1a(d->comp, (size_t)K * E * 4, dg);
+  dg = fnv1a(d->awt, E * 8, dg);
+  dg = fnv1a(d->nasa, 17 * K * 8, dg);
+  dg = fnv1a(sp4.data(), R * sizeof(int4), dg);
+  dg = fnv1a(nu4.data(), R * sizeof(int4), dg);
+  dg = fnv1a(lnA.data(), R * 8, dg);
+  dg = fnv1a(bb.data(), R * 8, dg);
+  m->digest = fnv1a(EaR.data(), R * 8, dg);
   e = hipMemcpy(m->blob, pk.buf.data(), pk.buf.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemset(m->counters, 0, 64 * sizeof(unsigned long long));
   if (e != hipSuccess) {
@@ -438,11 +425,8 @@ extern "C" chem_status chem_mech_create(const chem_mech_desc *d, chem_mech **out
   dm.W = (const double *)(base + oW);
   dm.invW = (const double *)(base + oiW);
   dm.Tmid = (const double *)(base + oTm);
-  dm.Mel = (const double *)(base + oM);
   dm.nasa_h = (const double *)(base + onh);
   dm.nasa_hh = (const double *)(base + onhh);
-  dm.nasa_s = (const double *)(base + ons);
-  dm.nasa_sh = (const double *)(base + onsh);
   dm.cpT = (const double *)(base + ocpT);
   dm.hT = (const double *)(base + ohT);
   dm.sT = (const double *)(base + osT);

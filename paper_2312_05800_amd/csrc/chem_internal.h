@@ -22,14 +22,11 @@ struct DevMech {
   const double *W;        // [K] kg/mol
   const double *invW;     // [K]
   const double *Tmid;     // [K]
-  const double *Mel;      // [E][K] element mass per unit mass fraction, A_e a_ek / W_k
   const double *nasa_h;   // [K][7] low-range h/RT polynomial: a1, a2/2, a3/3, a4/4, a5/5, a6, 0
   const double *nasa_hh;  // [K][7] same for the high range
-  const double *nasa_s;   // [K][7] low-range s/R: a1, a2, a3/2, a4/3, a5/4, a7, 0
-  const double *nasa_sh;  // [K][7] same for the high range
   const double *compd;    // [E][K] atoms of element e in species k
-  const double *cpT;      // [2][7][K] the c_p/R, h/RT and s/R polynomials above,
-  const double *hT;       //   low range then high range, coefficient-major
+  const double *cpT;      // [2][7][K] the c_p/R, h/RT and s/R polynomials (divisors folded
+  const double *hT;       //   in), low range then high range, coefficient-major
   const double *sT;
   // the integrator's lane groups: component c >= 1 is species order[c - 1] (see
   // species_order); the reactions in the order of their passes (see pass_order),
