@@ -122,7 +122,7 @@ __host__ __device__ inline int mlp12_slot(int f) {
   return 8 * ((f & 15) >> 2) + 4 * (f >> 4) + (f & 3);
 }
 // Whether mlp12() takes this shape (32 inputs, K a multiple of 32 up to
-// 2048, N a multiple of 400, aligned operands).
+// 2048, N a multiple of 800, aligned operands).
 bool mlp12_ok(const Mlp12Args &g);
 chem_status mlp12(const Mlp12Args &g, hipStream_t s, const char *label);
 // Whether gemm8() can run this layer with EPI_GELU_NEXT (the BF16 output

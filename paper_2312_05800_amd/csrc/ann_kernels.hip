@@ -754,243 +754,33 @@ chem_status gemm_dma16_cfg(const GemmArgs &g, int epi, hipStream_t s) {
 // and 16+4g..16+4g+3 (g = l / 16) of the K-step; the second layer's MFMA
 // takes K positions 8g..8g+7 from lane group g, so the step's features enter
 // in that permuted order and the second layer's weights are stored with the
-// same permutation within each 32-wide K-block (mlp12_slot).  The tile is
-// the second layer's 256 cells x 400 features: the block's two feature
-// tiles each recompute the first layer for their cells (8 % more MFMA work,
-// twice the GELUs of the first layer).  The ring stage of K-step kt carries
-// the second layer's weights of step kt and the first layer's of step kt + 1,
-// whose GELUs then overlap the multiplications of step kt.
+// same permutation within each 32-wide K-block (mlp12_slot).  The ring stage of
+// K-step kt carries the second layer's weights of step kt and the first layer's of
+// step kt + 1, whose GELUs then overlap the multiplications of step kt.
 constexpr int MLP12_KMAX = 2048;
-// waves per block and 16-cell tiles per wave (block: MLP12_WM MLP12_TM16 16
-// cells x 400 features)
-constexpr int MLP12_WM = 8, MLP12_TM16 = 2;
 // second-layer weight fragments in flight ahead of their MFMAs
 constexpr int MLP12_PF = 2;
-// k_mlp12p: the first tile, and the spacing in tiles, of the first layer's
+// the first tile, and the spacing in tiles, of the first layer's
 // GELUs among the second layer's MFMAs (8 GELUs over 25 tiles)
 constexpr int MLP12P_GSTART = 2, MLP12P_GSTEP = 3;
 // and of a wave's loads of the next stage (7 over 25 tiles)
 constexpr int MLP12P_DSTART = 1, MLP12P_DSTEP = 2;
-constexpr int PHASE = 4;
 
-template <int TN16>
-struct Mlp12Tile {
-  static constexpr int WM = MLP12_WM, TM16 = MLP12_TM16, BK = 32, STAGES = 3;
-  static constexpr int BM = WM * TM16 * 16, BN = TN16 * 16;
-  static constexpr int R1 = 32;  // first-layer weight rows of one K-step
-  static constexpr int ROWS = R1 + BN;
-};
-
-// One block's tile; MULFIRST: this wave multiplies before it produces (the
-// whole body is instantiated per order, so that no accumulator crosses a
-// branch).
-template <int TN16, bool MULFIRST>
-__device__ __forceinline__ void mlp12_tile(const Mlp12Args &g, u16 *S, float *b1_s,
-                                           float *bias_s, int wave) {
-  using TL = Mlp12Tile<TN16>;
-  constexpr int WM = TL::WM, TM16 = TL::TM16, BK = TL::BK, STAGES = TL::STAGES;
-  constexpr int BM = TL::BM, BN = TL::BN, R1 = TL::R1, ROWS = TL::ROWS;
-  constexpr int NI = ROWS / 16;
-  constexpr int NPW = (NI + WM - 1) / WM;
-  constexpr int NMIN = NI / WM;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int ntn = (g.N + BN - 1) / BN;
-  const int ntm = (g.M + BM - 1) / BM;
-  const int total = ntn * ntm;
-  const int per_xcd = (total + 7) / 8;
-  const int logical = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  if (logical >= total) return;
-  const long m0 = (long)(logical / ntn) * BM, n0 = (long)(logical % ntn) * BN;
-  for (int c = tid; c < BN / 4; c += WM * 64) {
-    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (n0 + 4 * c < g.N) v = *(const float4 *)(g.b2 + n0 + 4 * c);
-    *(float4 *)&bias_s[4 * c] = v;
-  }
-  for (int c = tid; c < g.K / 4; c += WM * 64) *(float4 *)&b1_s[4 * c] = *(const float4 *)(g.b1 + 4 * c);
-
-  // the wave's 32 cells as the first layer's B operand (lane: cell l % 16 of
-  // tile i, inputs 8g..8g+7); rows past M clamped (never stored)
-  const int cc = lane >> 4, hf = 4 * cc;
-  bf16x8 xin[TM16];
-#pragma unroll
-  for (int i = 0; i < TM16; ++i) {
-    long row = m0 + wave * TM16 * 16 + i * 16 + (lane & 15);
-    if (row >= g.M) row = g.M - 1;
-    xin[i] = *(const bf16x8 *)(g.X + row * 32 + cc * 8);
-  }
-  __syncthreads();  // b1_s, bias_s
-
-  // first layer for the 32 features of K-step kt: w1[t] = weight rows
-  // 16t + l % 16 of the step (the MFMA's A operand)
-  auto layer1 = [&](const bf16x8(&w1)[2], int kt, bf16x8(&h)[TM16]) __attribute__((always_inline)) {
-    const float4 c0 = *(const float4 *)&b1_s[kt * 32 + hf];
-    const float4 c1 = *(const float4 *)&b1_s[kt * 32 + 16 + hf];
-#pragma unroll
-    for (int i = 0; i < TM16; ++i) {
-      f32x4 z0 = (f32x4){c0.x, c0.y, c0.z, c0.w}, z1 = (f32x4){c1.x, c1.y, c1.z, c1.w};
-      z0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[0], xin[i], z0, 0, 0, 0);
-      z1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[1], xin[i], z1, 0, 0, 0);
-      const bf16x2 a = __builtin_convertvector((f32x2){gelu(z0[0]), gelu(z0[1])}, bf16x2);
-      const bf16x2 b = __builtin_convertvector((f32x2){gelu(z0[2]), gelu(z0[3])}, bf16x2);
-      const bf16x2 c = __builtin_convertvector((f32x2){gelu(z1[0]), gelu(z1[1])}, bf16x2);
-      const bf16x2 d = __builtin_convertvector((f32x2){gelu(z1[2]), gelu(z1[3])}, bf16x2);
-      h[i] = (bf16x8){a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
-    }
-  };
-
-  // K-step 0 of the first layer straight from global memory
-  const int nk = g.K / BK;
-  bf16x8 h[TM16];
-  {
-    bf16x8 w1[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-      w1[t] = *(const bf16x8 *)(g.W1 + (t * 16 + (lane & 15)) * 32 + cc * 8);
-    layer1(w1, 0, h);
-  }
-
-  // DMA rows: the first R1 rows of a stage are the first layer's weights of
-  // the next K-step, then BN rows of the second layer's (all valid: N is a
-  // multiple of BN).  A 16-row group starts at a multiple of 16, so the
-  // swizzle of row 16 gi + l / 4 is swz(l / 4) for every group: one
-  // per-lane byte offset serves all of them, the rest is wave-uniform.
-  const u16 *const sB = g.W2p + n0 * BK;
-  const unsigned loff =
-      (unsigned)((lane >> 2) * BK * 2 + (((lane & 3) ^ swz(lane >> 2)) * 16));
-  const unsigned lds0 =
-      (unsigned)(uintptr_t)(__attribute__((address_space(3))) u16 *)(S);
-  auto issue = [&](int stage, int kt) __attribute__((always_inline)) {
-    const int k1 = kt + 1 < nk ? kt + 1 : nk - 1;
-#pragma unroll
-    for (int i = 0; i < NPW; ++i) {
-      const int gi = i * WM + wave;
-      if (gi < NI)
-        lds_dma16s(gi * 16 < R1 ? g.W1 + ((long)k1 * R1 + gi * 16) * BK
-                                : sB + kt * g.ldw2 + (long)(gi * 16 - R1) * BK,
-                   loff, lds0 + (unsigned)((stage * ROWS + gi * 16) * BK * 2));
-    }
-  };
-
-  f32x4 acc[TM16][TN16];
-#pragma unroll
-  for (int i = 0; i < TM16; ++i)
-#pragma unroll
-    for (int j = 0; j < TN16; ++j) acc[i][j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
-
-  issue(0, 0);
-  if (nk > 1) issue(1, 1);
-  for (int kt = 0; kt < nk; ++kt) {
-    // as in k_gemm_dma16: own loads of stage kt done, barrier publishes all
-    if (kt + 1 < nk)
-      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(NMIN) : "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" : : : "memory");
-    if (kt + 2 < nk) issue((kt + 2) % STAGES, kt + 2);
-    const u16 *T = S + (kt % STAGES) * ROWS * BK;
-    // the next K-step's first-layer features (the last step recomputes its
-    // own, unused): VALU-heavy
-    bf16x8 hn[TM16];
-    auto produce = [&]() __attribute__((always_inline)) {
-      bf16x8 w1[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int row = t * 16 + (lane & 15);
-        w1[t] = *(const bf16x8 *)&T[row * BK + ((cc ^ swz(row)) * 8)];
-      }
-      layer1(w1, kt + 1 < nk ? kt + 1 : kt, hn);
-    };
-    // this K-step of the second layer: MFMA-heavy; the weight fragments are
-    // read MLP12_PF feature tiles ahead of their MFMAs
-    auto bfrag = [&](int j) __attribute__((always_inline)) {
-      const int row = R1 + j * 16 + (lane & 15);
-      return *(const bf16x8 *)&T[row * BK + ((cc ^ swz(row)) * 8)];
-    };
-    auto multiply = [&]() __attribute__((always_inline)) {
-      bf16x8 wq[MLP12_PF];
-#pragma unroll
-      for (int q = 0; q < MLP12_PF; ++q) wq[q] = bfrag(q);
-#pragma unroll
-      for (int j = 0; j < TN16; ++j) {
-        const bf16x8 w = wq[j % MLP12_PF];
-        if (j + MLP12_PF < TN16) wq[j % MLP12_PF] = bfrag(j + MLP12_PF);
-#pragma unroll
-        for (int i = 0; i < TM16; ++i)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, h[i], acc[i][j], 0, 0, 0);
-      }
-    };
-    if (MULFIRST) {
-      multiply();
-      produce();
-    } else {
-      produce();
-      multiply();
-    }
-#pragma unroll
-    for (int i = 0; i < TM16; ++i) h[i] = hn[i];
-  }
-
-  // epilogue: bias + GELU, BF16 (lane: 4 consecutive features of one cell)
-  long rb[TM16];
-  bool live[TM16];
-#pragma unroll
-  for (int i = 0; i < TM16; ++i) {
-    rb[i] = m0 + wave * TM16 * 16 + i * 16 + (lane & 15);
-    live[i] = rb[i] < g.M;
-  }
-#pragma unroll
-  for (int j = 0; j < TN16; ++j) {
-    const long cj = n0 + j * 16;  // uniform
-    if (cj >= g.N) break;
-    const float4 b = *(const float4 *)&bias_s[j * 16 + hf];
-#pragma unroll
-    for (int i = 0; i < TM16; ++i) {
-      if (!live[i]) continue;
-      const long row = rb[i];
-      const bf16x2 lo = __builtin_convertvector(
-          (f32x2){gelu(acc[i][j][0] + b.x), gelu(acc[i][j][1] + b.y)}, bf16x2);
-      const bf16x2 hi = __builtin_convertvector(
-          (f32x2){gelu(acc[i][j][2] + b.z), gelu(acc[i][j][3] + b.w)}, bf16x2);
-      uint2 o;
-      o.x = __builtin_bit_cast(unsigned, lo);
-      o.y = __builtin_bit_cast(unsigned, hi);
-      u16 *const at = g.tiled ? g.H + (row * 32 + hf) + ((cj / 32) * g.ldh + cj % 32)
-                              : g.H + (row * g.ldh + hf) + cj;
-      *(uint2 *)at = o;
-    }
-  }
-}
-
-// waves (wave & PHASE) != 0 multiply before they produce: one wave's GELUs
-// can then overlap the other's MFMAs on the same SIMD
-template <int TN16>
-__global__ __launch_bounds__(MLP12_WM * 64) void k_mlp12(Mlp12Args g) {
-  using TL = Mlp12Tile<TN16>;
-  __shared__ __attribute__((aligned(1024))) u16 S[TL::STAGES * TL::ROWS * TL::BK];
-  __shared__ __attribute__((aligned(16))) float b1_s[MLP12_KMAX];
-  __shared__ __attribute__((aligned(16))) float bias_s[TL::BN];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave & PHASE)
-    mlp12_tile<TN16, true>(g, S, b1_s, bias_s, wave);
-  else
-    mlp12_tile<TN16, false>(g, S, b1_s, bias_s, wave);
-}
-
-// ------------------------------------ fused first two layers, paired halves
-// The same computation as k_mlp12 on a 128-cell x 800-feature tile: wave w
-// takes cells 32 (w & 3) .. + 31 and second-layer features 400 (w >> 2) ..
-// + 399, so the two waves of a SIMD (w and w + 4) share their cells.  Each
-// produces one of the two 16-feature halves of the next K-step's first layer
-// (one MFMA and eight GELUs per cell tile instead of two and sixteen: the
-// first layer is computed once per cell, not once per 400 features) and
-// leaves it in LDS (8 bytes per lane and tile); after the step's barrier the
-// partner's half completes the MFMA operand, in the order k_mlp12 builds it.
-// Within a K-step the first layer's GELUs, and the direct loads of the next stage, sit
-// between the second layer's MFMAs of the same wave: 2^20 cells 2.85 ms, 3.1 with the loads
-// issued together before them (their addresses are some 60 scalar instructions).  The
-// matrix cores are busy for 45 % of that at the 1.9 GHz the card holds here (the MFMAs
-// alone, from registers, take 1.4 ms); the epilogue's GELUs are 0.5 ms, without the loop's
-// GELUs it takes 2.55, without its loads 2.62, without both 2.2.  The 832-row stage (the first layer's 32 rows, the second's 800) allows a
-// ring of two, so each K-step prefetches only the next one.
+// The tile is 128 cells x 800 features: wave w takes cells 32 (w & 3) .. + 31 and
+// second-layer features 400 (w >> 2) .. + 399, so the two waves of a SIMD (w and
+// w + 4) share their cells.  Each produces one of the two 16-feature halves of the
+// next K-step's first layer (which is so computed once per cell, not once per 400
+// features) and leaves it in LDS (8 bytes per lane and tile); after the step's
+// barrier the partner's half completes the MFMA operand.  Within a K-step the first
+// layer's GELUs, and the direct loads of the next stage, sit between the second
+// layer's MFMAs of the same wave: 2^20 cells 2.85 ms, 3.1 with the loads issued
+// together before them (their addresses are some 60 scalar instructions), both on a
+// card whose MFMA chain reaches 2.03 PFLOP/s (3.13 ms on one of 1.93).  The matrix
+// cores are busy for 45 % of that at the 1.9 GHz the card holds here (the MFMAs
+// alone, from registers, take 1.4 ms); the epilogue's GELUs are 0.5 ms, without the
+// loop's GELUs it takes 2.55, without its loads 2.62, without both 2.2.  The 832-row
+// stage (the first layer's 32 rows, the second's 800) allows a ring of two, so each
+// K-step prefetches only the next one.
 template <int TN16>
 struct Mlp12PTile {
   static constexpr int WM = 8, TM16 = 2, BK = 32, STAGES = 2, RW = 4;
@@ -1063,8 +853,10 @@ __device__ __forceinline__ void mlp12p_tile(const Mlp12Args &g, u16 *S, float *b
     for (int i = 0; i < TM16; ++i) *xslot(0, i, cw) = hh[i];
   }
 
-  // DMA rows as in k_mlp12: the first R1 rows of a stage are the first
-  // layer's weights of the next K-step, then the BN rows of the second's
+  // DMA rows: the first R1 rows of a stage are the first layer's weights of the next
+  // K-step, then the BN rows of the second's.  A 16-row group starts at a multiple of 16,
+  // so the swizzle of row 16 gi + l / 4 is swz(l / 4) for every group: one per-lane byte
+  // offset serves all of them, the rest is wave-uniform.
   const u16 *const sB = g.W2p + n0 * BK;
   const unsigned loff =
       (unsigned)((lane >> 2) * BK * 2 + (((lane & 3) ^ swz(lane >> 2)) * 16));
@@ -1198,7 +990,7 @@ __global__ __launch_bounds__(8 * 64) void k_mlp12p(Mlp12Args g) {
   __shared__ __attribute__((aligned(16))) float bias_s[TL::BN];
   __shared__ __attribute__((aligned(16))) uint2 xb[TL::XB];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave & PHASE)
+  if (wave & 4)
     mlp12p_tile<TN16, 1>(g, S, b1_s, bias_s, xb, wave);
   else
     mlp12p_tile<TN16, 0>(g, S, b1_s, bias_s, xb, wave);
@@ -2942,7 +2734,7 @@ void gemm_tile_shape(int t, int *bm, int *bn) {
 
 bool mlp12_ok(const Mlp12Args &g) {
   auto al = [](const void *p, uintptr_t a) { return p && ((uintptr_t)p & (a - 1)) == 0; };
-  return g.K > 0 && g.K % 32 == 0 && g.K <= MLP12_KMAX && g.N > 0 && g.N % 400 == 0 &&
+  return g.K > 0 && g.K % 32 == 0 && g.K <= MLP12_KMAX && g.N > 0 && g.N % 800 == 0 &&
          g.ldw2 >= 32L * g.N && g.ldw2 % 8 == 0 &&
          (g.tiled ? g.ldh % 8 == 0 : (g.ldh >= g.N && g.ldh % 4 == 0)) && al(g.X, 16) &&
          al(g.W1, 16) && al(g.W2p, 16) && al(g.b1, 16) && al(g.b2, 16) && al(g.H, 8);
@@ -2955,18 +2747,10 @@ chem_status mlp12(const Mlp12Args &g, hipStream_t s, const char *label) {
     chem::set_error("mlp12: unsupported shape or misaligned operand");
     return CHEM_EUNSUPPORTED;
   }
-  if (g.N % 800 == 0) {
-    // paired halves: the first layer once per cell
-    constexpr int BM = Mlp12PTile<25>::BM;
-    const long total = (long)((g.M + BM - 1) / BM) * (g.N / 800);
-    hipLaunchKernelGGL((k_mlp12p<25>), dim3((unsigned)(((total + 7) / 8) * 8)), dim3(8 * 64), 0,
-                       s, g);
-  } else {
-    constexpr int BM = Mlp12Tile<25>::BM;
-    const long total = (long)((g.M + BM - 1) / BM) * (g.N / 400);
-    hipLaunchKernelGGL((k_mlp12<25>), dim3((unsigned)(((total + 7) / 8) * 8)),
-                       dim3(MLP12_WM * 64), 0, s, g);
-  }
+  constexpr int BM = Mlp12PTile<25>::BM;
+  const long total = (long)((g.M + BM - 1) / BM) * (g.N / 800);
+  hipLaunchKernelGGL((k_mlp12p<25>), dim3((unsigned)(((total + 7) / 8) * 8)), dim3(8 * 64), 0, s,
+                     g);
   CHEM_HIP(hipGetLastError());
   return CHEM_OK;
 }
@@ -2995,10 +2779,10 @@ chem_status gemm8(const GemmArgs &g, int epi, hipStream_t s, const char *label) 
   }
   if (g.K % 128 == 0 && g.N % 16 == 0 && ((uintptr_t)g.A8 & 15) == 0 &&
       ((uintptr_t)g.B8 & 15) == 0 && g.ldcb % 4 == 0 && g.ldcq % 4 == 0) {
-    // 128 x 160 tiles (N a multiple of 160), else 128 x 208 (N of 208): two
-    // blocks of eight waves per CU, so that one's GELUs run beside the other's
-    // products (second layer at 200003 cells 372 us; 256 x 160 tiles on three stages, one
-    // block per CU, 417; 256 x 272 on two 389; four waves 380)
+    // 128 x 160 tiles on two stages (N a multiple of 160): two blocks of eight waves
+    // per CU, so that one's GELUs run beside the other's products (second layer at 200003
+    // cells 372 us; 256 x 160 tiles on three stages, one block per CU, 417; 256 x 272 on two
+    // 389; four waves 380).  Else 128 x 208 on three (N of 208): 126 KB, one block per CU.
     const long mt = (g.M + 255) / 256;
     if (g.N % 160 == 0 && mt * (g.N / 160) >= 512) return gemm8_dma16_cfg<8, 1, 10, 2>(g, epi, s);
     if (g.N % 208 == 0 && mt * 2 * (g.N / 208) >= 512) return gemm8_dma16_cfg<8, 1, 13>(g, epi, s);
