@@ -88,7 +88,7 @@ struct ann_model {
   uint8_t *Wq1t = nullptr, *Wq2t = nullptr;  // the same, K-blocked by 128 bytes
   float *bq1 = nullptr;                    // layer-1 bias padded to N2p
   int n2p = 0, k3p = 0, kq1 = 0;           // FP8 widths: L2 out (x32), L3 in / L2 in (x128)
-  uint8_t *H1q = nullptr, *H2q = nullptr;  // inference workspace (E4M3 activations)
+  uint8_t *Hq[2][2] = {};  // inference workspace (E4M3 activations, see InferWs)
   uint8_t *ood = nullptr;                  // per-cell out-of-distribution bits
   int graph_refs = 0;  // live captured steps that use the inference workspace
   // tilings of the eleven training products at batch tt_B, from
@@ -119,11 +119,17 @@ size_t layer_elems(const ann::Layer &L) { return (size_t)L.doutp * L.dinp; }
 // output layer width, the assembled ensemble's otherwise.
 int uw(const ann_model *m) { return pad32(m->n_out); }
 
-// E4M3 layout: L2 reads H1q [cells][kq1] and Wq1 [n2p][kq1]; L3 reads H2q
+// E4M3 layout: L2 reads Hq[.][0] [cells][kq1] and Wq1 [n2p][kq1]; L3 reads Hq[.][1]
 // [cells][k3p] and Wq2 [L3 outputs][k3p]; K widths padded to 128 with zeros.
 int fp8_n2p(const ann_model *m) { return (m->L[1].dout + 31) / 32 * 32; }
 int fp8_kq1(const ann_model *m) { return (m->L[1].dinp + 127) / 128 * 128; }
 int fp8_k3p(const ann_model *m) { return (fp8_n2p(m) + 127) / 128 * 128; }
+// Whether batches from BLOCKED_CELLS on keep these activations K-blocked.
+constexpr int64_t BLOCKED_CELLS = 1 << 17;
+bool fp8_blocks(const ann_model *m) {
+  return m->L[0].dinp == 32 && m->L[0].doutp % 320 == 0 && fp8_n2p(m) % 160 == 0 &&
+         m->L[2].doutp % 208 == 0;
+}
 
 // The inference workspace of cap cells: input rows, activations, network
 // output, out-of-distribution bytes, the fallback count and (no-allocation
@@ -135,8 +141,15 @@ struct InferWs {
   float *Um = nullptr;  // one ensemble member's output [cap][32] before its column is taken
   uint8_t *ood = nullptr;
   unsigned long long *fb_count = nullptr;
-  uint8_t *H1q = nullptr, *H2q = nullptr;  // E4M3 activations, rows padded with zeros
-  size_t q_bytes = 0;                      // bytes from H1q to the end of H2q
+  // E4M3 activations, row-major and K-blocked, both padded with zeros that are never
+  // written.  A workspace that serves both layouts keeps them apart: what is padding in
+  // one would be data in the other, and a NaN there would reach later cells.  (335 MB for
+  // 1600 and 800 features.  In one place, with the next layer's last K-step reading data
+  // for the padding, the second layer took 1.3 % longer; writing the padding with every
+  // row cost the step 2.5 %.)
+  uint8_t *Hq[2][2] = {};  // [K-blocked][of layer 1, 2]
+  bool q_blocked = false;  // there are K-blocked ones, and the others have BLOCKED_CELLS rows
+  size_t q_bytes = 0;      // bytes from Hq[0][0] to the end of the last
   int32_t *fb_index = nullptr;
 };
 
@@ -158,10 +171,11 @@ size_t infer_layout(const ann_model *m, int64_t cap, bool fb_list, unsigned char
   const size_t oO = sect((size_t)cap);
   const size_t oC = sect(64);
   // E4M3 activations (the FP8 variant exists for single networks only)
-  const size_t q1 = m->G > 1 ? 0 : (size_t)cap * fp8_kq1(m);
-  const size_t q2 = m->G > 1 ? 0 : (size_t)cap * fp8_k3p(m);
-  const size_t oQ1 = sect(q1);
-  const size_t oQ2 = sect(q2);
+  const bool both = m->G == 1 && cap >= BLOCKED_CELLS && fp8_blocks(m);
+  const size_t rows = m->G > 1 ? 0 : both ? BLOCKED_CELLS : cap, blocked = both ? cap : 0;
+  const size_t oR1 = sect(rows * fp8_kq1(m)), oR2 = sect(rows * fp8_k3p(m));
+  const size_t oB1 = sect(blocked * fp8_kq1(m)), oB2 = sect(blocked * fp8_k3p(m));
+  const size_t oQ = off;
   const size_t oF = fb_list ? sect((size_t)cap * 4) : 0;
   if (base && w) {
     w->cap = cap;
@@ -171,9 +185,12 @@ size_t infer_layout(const ann_model *m, int64_t cap, bool fb_list, unsigned char
     w->Um = m->G > 1 ? (float *)(base + oUm) : nullptr;
     w->ood = base + oO;
     w->fb_count = (unsigned long long *)(base + oC);
-    w->H1q = base + oQ1;
-    w->H2q = base + oQ2;
-    w->q_bytes = oQ2 - oQ1 + q2;
+    w->Hq[0][0] = base + oR1;
+    w->Hq[0][1] = base + oR2;
+    w->Hq[1][0] = base + oB1;
+    w->Hq[1][1] = base + oB2;
+    w->q_blocked = both;
+    w->q_bytes = oQ - oR1;
     w->fb_index = fb_list ? (int32_t *)(base + oF) : nullptr;
   }
   return off;
@@ -189,8 +206,7 @@ InferWs model_ws(const ann_model *m) {
   w.Um = m->Um;
   w.ood = m->ood;
   w.fb_count = m->fb_count;
-  w.H1q = m->H1q;
-  w.H2q = m->H2q;
+  std::copy(&m->Hq[0][0], &m->Hq[0][0] + 4, &w.Hq[0][0]);
   w.fb_index = m->fb_index;
   return w;
 }
@@ -220,14 +236,24 @@ chem_status grow_infer(ann_model *m, int64_t n) {
   m->Um = w.Um;
   m->ood = w.ood;
   m->fb_count = w.fb_count;
-  m->H1q = w.H1q;
-  m->H2q = w.H2q;
-  // the E4M3 activation rows are padded to multiples of 128 bytes; the
-  // padding is never written and must read as zero
-  if (w.q_bytes && hipMemset(w.H1q, 0, w.q_bytes) != hipSuccess) {
-    set_error("ann: cannot clear the E4M3 activation workspace");
-    return CHEM_EHIP;
+  std::copy(&w.Hq[0][0], &w.Hq[0][0] + 4, &m->Hq[0][0]);
+  // the E4M3 activation rows are padded to multiples of 128 bytes; the padding is never
+  // written and must read as zero.  Cleared alone where the rest is large.
+  hipError_t e = hipSuccess;
+  if (!w.q_blocked) {
+    if (w.q_bytes) e = hipMemset(w.Hq[0][0], 0, w.q_bytes);
+  } else {
+    const size_t used[2] = {(size_t)m->L[1].dinp, (size_t)fp8_n2p(m)};
+    const size_t width[2] = {(size_t)fp8_kq1(m), (size_t)fp8_k3p(m)};
+    for (int l = 0; l < 2 && e == hipSuccess; ++l) {
+      const size_t pad = width[l] - used[l];
+      if (pad == 0) continue;
+      e = hipMemset2D(w.Hq[0][l] + used[l], width[l], 0, pad, BLOCKED_CELLS);
+      if (e == hipSuccess)  // the last block of 128 columns
+        e = hipMemset(w.Hq[1][l] + (width[l] - 128) * cap, 0, (size_t)cap * 128);
+    }
   }
+  if (e != hipSuccess) return hip_fail(e, "ann: clearing the E4M3 activations' padding");
   m->wi.bytes = off;
   m->wi.cap = cap;
   return CHEM_OK;
@@ -669,8 +695,8 @@ namespace {
 // (rows of one 32-wide K-step contiguous in HBM; 128 bytes for E4M3).
 bool tiled_path(const ann_model *m, int64_t n) {
   const ann::Layer &a = m->L[0], &b = m->L[1], &c = m->L[2];
-  if (n < (1 << 17) || a.dinp != 32 || a.doutp % 320 != 0) return false;
-  if (m->use_fp8) return m->n2p % 160 == 0 && c.doutp % 208 == 0;
+  if (n < BLOCKED_CELLS || a.dinp != 32 || a.doutp % 320 != 0) return false;
+  if (m->use_fp8) return fp8_blocks(m);
   return b.doutp % 400 == 0 && (c.doutp % 416 == 0 || c.doutp % 400 == 0);
 }
 
@@ -894,7 +920,7 @@ chem_status forward_chunk(ann_model *m, const InferWs &w, int64_t n, int64_t ld,
     g.B = m->Wb[0];
     g.ldb = L0.dinp;
     g.bias = m->bm[0];
-    g.Cq = w.H1q;
+    g.Cq = w.Hq[tl][0];
     g.ldcq = tl ? cap * 128 : m->kq1;
     g.tiled = tl ? ann::TILED_C : 0;
     g.qinv = 1.0f / m->sa[1];
@@ -903,13 +929,13 @@ chem_status forward_chunk(ann_model *m, const InferWs &w, int64_t n, int64_t ld,
     h.M = (int)n;
     h.N = m->n2p;
     h.K = m->kq1;
-    h.A8 = w.H1q;
+    h.A8 = w.Hq[tl][0];
     h.lda = tl ? cap * 128 : m->kq1;
     h.B8 = tl ? m->Wq1t : m->Wq1;
     h.ldb = tl ? (long)m->n2p * 128 : m->kq1;
     h.bias = m->bq1;
     h.scale = m->sa[1] * m->sw[1];
-    h.Cq = w.H2q;
+    h.Cq = w.Hq[tl][1];
     h.ldcq = tl ? cap * 128 : m->k3p;
     h.qinv = 1.0f / m->sa[2];
     h.tiled = tl ? (ann::TILED_A | ann::TILED_B | ann::TILED_C) : 0;
@@ -918,7 +944,7 @@ chem_status forward_chunk(ann_model *m, const InferWs &w, int64_t n, int64_t ld,
     q.M = (int)n;
     q.N = L2.doutp;
     q.K = m->k3p;
-    q.A8 = w.H2q;
+    q.A8 = w.Hq[tl][1];
     q.lda = tl ? cap * 128 : m->k3p;
     q.B8 = tl ? m->Wq2t : m->Wq2;
     q.ldb = tl ? (long)L2.doutp * 128 : m->k3p;
@@ -1345,7 +1371,7 @@ extern "C" chem_status ann_step_noalloc(ann_model *m, const chem_mech *mech, che
   if (m->use_fp8) {
     // the E4M3 rows' padding must read as zero; earlier calls may have left
     // other data there
-    hipLaunchKernelGGL(k_fill_zero, dim3(1024), dim3(256), 0, s, w.H1q, w.q_bytes);
+    hipLaunchKernelGGL(k_fill_zero, dim3(1024), dim3(256), 0, s, w.Hq[0][0], w.q_bytes);
     CHEM_HIP(hipGetLastError());
   }
   const StepOpts fo = resolve_opts(fb_opts);
