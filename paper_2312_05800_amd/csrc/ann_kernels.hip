@@ -302,8 +302,6 @@ __global__ __launch_bounds__(WM *WN * 64) void k_gemm(GemmArgs g) {
           if (g.Z) g.Z[row * g.ldz + col] = z;
           if (g.Cb) g.Cb[row * g.ldcb + col] = f2bf(gelu(z));
           if (g.Cf) g.Cf[row * g.ldcf + col] = gelu(z);
-        } else if (EPI == EPI_GELU_Q8) {
-          g.Cq[row * g.ldcq + col] = f2e4m3(gelu(v + bias) * g.qinv);
         } else {
           const float d = v * gelu_grad(zt[r]);
           if (g.Cb) g.Cb[row * g.ldcb + col] = f2bf(d);
@@ -1003,9 +1001,6 @@ chem_status gemm_launch(const GemmArgs &g, bool AK, bool BKC, int epi, dim3 grid
     hipLaunchKernelGGL((k_gemm<WM, WN, TM, TN, true, true, EPI_GELU, BK>), grid, block, 0, s, g);
   else if (AK && BKC && epi == EPI_F32)
     hipLaunchKernelGGL((k_gemm<WM, WN, TM, TN, true, true, EPI_F32, BK>), grid, block, 0, s, g);
-  else if (AK && BKC && epi == EPI_GELU_Q8)
-    hipLaunchKernelGGL((k_gemm<WM, WN, TM, TN, true, true, EPI_GELU_Q8, BK>), grid, block, 0, s,
-                       g);
   else if (AK && !BKC && epi == EPI_GELUGRAD)
     hipLaunchKernelGGL((k_gemm<WM, WN, TM, TN, true, false, EPI_GELUGRAD, BK>), grid, block, 0,
                        s, g);
