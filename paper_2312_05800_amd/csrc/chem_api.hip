@@ -117,6 +117,18 @@ std::vector<std::pair<int, std::array<int, 4>>> pass_order(const chem_mech_desc 
       if (species(r, t) >= 0) common[r] = std::max(common[r], uses[species(r, t)]);
   }
   std::stable_sort(rank.begin(), rank.end(), [&](int a, int b) { return common[a] > common[b]; });
+  // more reactions than any LDS has room for (see launch_step) stay as they are listed
+  if ((size_t)(64 / G) * R * 16 > 160 * 1024) {
+    std::vector<std::pair<int, std::array<int, 4>>> listed;
+    for (int r = 0; r < R; ++r) {
+      const int f = species(r, 0) < 0, g = species(r, 2) < 0;
+      listed.push_back({r, {f, 1 - f, 2 + g, 3 - g}});
+    }
+    return listed;
+  }
+  double weight[201];  // 4^count
+  weight[0] = 1.0;
+  for (int q = 1; q <= 200; ++q) weight[q] = 4.0 * weight[q - 1];
   std::vector<int> count((size_t)P * 4 * K, 0);
   std::vector<std::vector<std::pair<int, std::array<int, 4>>>> pass(P);
   for (int r : rank) {
@@ -136,7 +148,7 @@ std::vector<std::pair<int, std::array<int, 4>>> pass_order(const chem_mech_desc 
         double c = 0.0;
         for (int t = 0; t < 4; ++t)
           if (species(r, o[t]) >= 0)
-            c += pow(4.0, std::min(count[((size_t)p * 4 + t) * K + species(r, o[t])], 200));
+            c += weight[std::min(count[((size_t)p * 4 + t) * K + species(r, o[t])], 200)];
         if (best < 0.0 || c < best) {
           best = c;
           bp = p;

@@ -118,11 +118,12 @@ int main(int argc, char **argv) {
                         const double *, const double *, const double *, const double *,
                         const chem_sample_opts *, double *, double *, double *, uint8_t *, void *) =
       dlsym(lib, "chem_sample_states");
-  /* two isomers over C, H, O, N and R copies of the reaction between them */
-  const int32_t comp[8] = {1, 1, 1, 1, 1, 1, 1, 1};
-  const double W[2] = {0.043, 0.043}, awt[4] = {0.012, 0.001, 0.016, 0.014};
-  double nasa[34] = {0};
-  for (int k = 0; k < 2; ++k) {
+  /* four isomers over C, H, O, N and R copies of a reaction between two and two of them */
+  int32_t comp[16];
+  double W[4], awt[4] = {0.012, 0.001, 0.016, 0.014}, nasa[68] = {0};
+  for (int k = 0; k < 4; ++k) {
+    for (int e = 0; e < 4; ++e) comp[4 * k + e] = 1;
+    W[k] = 0.043;
     nasa[17 * k] = 200.0;
     nasa[17 * k + 1] = 1000.0;
     nasa[17 * k + 2] = 3000.0;
@@ -131,12 +132,12 @@ int main(int argc, char **argv) {
   int32_t *rsp = malloc(R * 16), *rnu = malloc(R * 16);
   double *A = malloc(R * 8), *b = calloc(R, 8), *Ea = calloc(R, 8);
   for (int r = 0; r < R; ++r) {
-    const int32_t sp[4] = {0, -1, 1, -1}, nu[4] = {1, 0, 1, 0};
+    const int32_t sp[4] = {0, 1, 2, 3}, nu[4] = {1, 1, 1, 1};
     memcpy(rsp + 4 * r, sp, 16);
     memcpy(rnu + 4 * r, nu, 16);
     A[r] = 1.0;
   }
-  const chem_mech_desc d = {2, R, 4, W, comp, awt, nasa, rsp, rnu, A, b, Ea};
+  const chem_mech_desc d = {4, R, 4, W, comp, awt, nasa, rsp, rnu, A, b, Ea};
   chem_mech *m = NULL;
   if (create(&d, &m) != CHEM_OK) return 2;
   double *const x = (double *)64; /* never followed */

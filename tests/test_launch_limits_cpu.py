@@ -2,6 +2,7 @@
 (launch_probe.c; no GPU): every grid stays within what a launch may have."""
 import os
 import subprocess
+import time
 
 import pytest
 
@@ -64,3 +65,12 @@ def test_step_grid_can_be_resident(probe):
     (_, status, launches), = probe("step", [1 << 20])
     grid = [g for name, g, _ in launches if "k_step" in name]
     assert status == 0 and grid == [(256 * 8, 1, 1)]
+
+
+def test_large_mechanisms_are_made_quickly(probe):
+    """The order of the reactions is a search over passes; the most reactions a lane group's LDS holds
+    (and as many as the descriptor may have, refused at their first use) take no minutes."""
+    t0 = time.monotonic()
+    probe("rates", [64], reactions=2528, lds=163840)
+    probe("rates", [64], reactions=65535)
+    assert time.monotonic() - t0 < 5.0
