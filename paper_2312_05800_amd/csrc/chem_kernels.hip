@@ -955,10 +955,10 @@ __device__ __forceinline__ bool gj_factor_diag(const GLds<G> &L, int l, int n,
   if ((bad >> gbase) & ((1ull << G) - 1ull)) {
     // the search's elimination leaves the rows in their places: L.h takes the row of each
     // unknown, L.wa the reciprocal pivots.  It holds the rows in registers as well: H2/air
-    // with shifted enthalpies, dt = 1e-2 s, 4096 cells, where about half of the attempts come
-    // here, 18.4 ms (searching every attempt 19.0, the retry on rows in LDS 19.9); CH4/air
-    // likewise, 1e-4 s, 8192 cells 22.4 ms (29.1, 28.1).  Not trying the diagonal after an
-    // attempt that came here: 19.4 and 28.0 with the rows in LDS.
+    // with shifted enthalpies, dt = 1e-2 s, 4096 cells, where 44 % of the attempts come here,
+    // 18.4 ms (searching every attempt 19.0, the repetition on rows in LDS 19.9); CH4/air
+    // likewise, 1e-4 s, 8192 cells, 32 %: 22.4 ms (29.1, 28.1).  Not trying the diagonal
+    // after an attempt that came here: 19.4 and 28.0 with the rows in LDS.
     newton_lds<G>(L, l, n, nr);
     double id;
     ok = gj_factor_reg<G>(L.J, L.wa, l, n, mystep, id);
