@@ -2224,7 +2224,8 @@ __global__ __launch_bounds__(POST_WAVES * 64, EP <= 4 ? 4 : 1) void k_post(chem:
         lam_s[e][lane] = v;
       }
     }
-    bad = bad || !ok;
+    // T0 = 0 (or so small that h/T0 is not finite): no temperature the cell could have had
+    bad = bad || !ok || !isfinite(h0 / T0);
     T_s[lane] = T0;
   }
   __syncthreads();
