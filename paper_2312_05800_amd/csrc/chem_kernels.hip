@@ -391,8 +391,11 @@ struct NewtonRow {
 // species lanes hold wdot_k in wdl.  With jac, the LDS matrix holds d wdot_k/dC_j at
 // the species' components, and in row 0 the temperature's entries of M times W_j, so that
 // all rows of the Newton matrix M = I dg - J follow from NewtonRow.  With KOUT the rate
-// constants are left in L.J (k_f at [r], k_r at [R + r]).
-template <int G, bool KOUT>
+// constants are left in L.J (k_f at [r], k_r at [R + r]).  With RATES (chem_rates, which
+// takes any state and flags none) zero, infinite and subnormal arguments take the library's
+// logarithm and division, which have their limits there; in a step such a state is no
+// solution, and NaN ends it as well.
+template <int G, bool RATES, bool KOUT>
 __device__ __forceinline__ void eval_cell(const DevMech &M, const GLds<G> &L, int l, int k,
                                           double p, double yl, double &f, double &wdl, bool jac, double dg,
                                           NewtonRow &nr) {
@@ -402,7 +405,16 @@ __device__ __forceinline__ void eval_cell(const DevMech &M, const GLds<G> &L, in
   RxnIn in0 = rxn_load(M, min(l, last)), in1 = rxn_load(M, min(l + G, last));
   const double T = grp_first<G>(yl);
   double miss;
-  const double lnT = T > 0.0 ? ln_f64(T) : NAN, invT = rcp_newton(T, miss);
+  auto div = [&](double a, double x) __attribute__((always_inline)) {
+    const double r = a * rcp_newton(x, miss);
+    if constexpr (RATES)
+      if (!(fabs(miss) <= 1e-12)) return a / x;
+    return r;
+  };
+  double lnT = T > 0.0 ? ln_f64(T) : NAN;
+  if constexpr (RATES)
+    if (!(T >= 0x1p-1022 && T < INFINITY)) lnT = log(T);
+  const double invT = div(1.0, T);
   const bool isSp = (l >= 1) && (l <= K);
   double cpR = 0.0, hRT = 0.0, sR = 0.0, dcpR = 0.0, Wk = 1.0, iWk = 1.0, Yk = 0.0;
   if (isSp) {
@@ -420,7 +432,7 @@ __device__ __forceinline__ void eval_cell(const DevMech &M, const GLds<G> &L, in
     dcpR = a[K] + T * (2.0 * a[2 * K] + T * (3.0 * a[3 * K] + T * (4.0 * a[4 * K])));
   }
   const double S = grp_sum<G>(Yk * iWk);
-  const double rho = p * rcp_newton(RG * T * S, miss);
+  const double rho = div(p, RG * T * S);
   const double Ck = rho * Yk * iWk;
   const double cp = grp_sum<G>(Yk * RG * cpR * iWk);
   // component 0 is the empty slots' dummy
@@ -479,7 +491,7 @@ __device__ __forceinline__ void eval_cell(const DevMech &M, const GLds<G> &L, in
   wdl = wd;
   const double Hk = isSp ? RG * T * hRT : 0.0;
   const double Q = grp_sum<G>(Hk * wd);
-  const double irho = rcp_newton(rho, miss), icp = rcp_newton(cp, miss);
+  const double irho = div(1.0, rho), icp = div(1.0, cp);
   const double fT = -Q * irho * icp;
   f = (l == 0) ? fT : (isSp ? Wk * wd * irho : 0.0);
   if (KOUT || !jac) return;
@@ -1094,9 +1106,9 @@ __global__ __launch_bounds__(64) void k_rates(DevMech M, int64_t N, int64_t ld, 
     const double pc = p[cell];
     double f, wd;
     if (kfkr)
-      eval_cell<G, true>(M, L, l, k, pc, yl, f, wd, false, 0.0, nr);
+      eval_cell<G, true, true>(M, L, l, k, pc, yl, f, wd, false, 0.0, nr);
     else
-      eval_cell<G, false>(M, L, l, k, pc, yl, f, wd, false, 0.0, nr);
+      eval_cell<G, true, false>(M, L, l, k, pc, yl, f, wd, false, 0.0, nr);
     if (l >= 1 && l <= M.K) wdot[(int64_t)k * ld + cell] = wd;
     if (l == 0 && dTdt) dTdt[cell] = f;
     if (kfkr) {
@@ -1245,7 +1257,7 @@ void k_step(DevMech M, StepArgs A) {
           asm volatile("" : "+v"(l));
           if (s != 1) {
             const double v = yl + TA_S(s, 0) * K0 + TA_S(s, 1) * K1 + TA_S(s, 2) * K2;
-            eval_cell<G, false>(M, L, l, k, p, v, F, wd, s == 0, ih / GAMMA, nr);
+            eval_cell<G, false, false>(M, L, l, k, p, v, F, wd, s == 0, ih / GAMMA, nr);
           }
           if (s == 0) {
             if constexpr (G <= 32) {
