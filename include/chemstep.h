@@ -254,7 +254,8 @@ typedef struct {
  * with bit 0 if an input lies outside the widened training range or dt
  * differs from dt_model, bit 1 if the element residual of the network's own
  * state Y' (max_e |(M Y')_e - (M Y0)_e|, M the element mass fractions per
- * unit mass fraction) or of the projected state exceeds residual_tol;
+ * unit mass fraction) or of the projected state exceeds residual_tol, or no
+ * temperature follows (the input's is zero or subnormal, or Newton's ends at none);
  * flagged cells keep their input state and, with fallback on, are integrated
  * by chem_step (fb_opts) on the same stream without a host round trip; bit 2
  * marks a failed fallback.  n_fallback (device int64, nullable) receives the
